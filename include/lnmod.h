@@ -123,6 +123,17 @@ int lnmod_backward_varlen(const void* dy, const void* x, const void* shift, cons
                           void* workspace, size_t workspace_bytes, int dtype);
 
 /*
+ * lnmod_backward (cu_seqlens NULL: B samples of S tokens) or lnmod_backward_varlen (cu_seqlens given:
+ * nseg segments, T tokens) with modulation rows per sample / segment, whose dshift and dscale are
+ * [B_or_nseg, D] in the I/O element type: the float32 sums are rounded once where they are formed.
+ * For callers that keep the gradients in the parameters' own type.
+ */
+int lnmod_backward_io(const void* dy, const void* x, const void* scale, const int32_t* cu_seqlens,
+                      int64_t B_or_nseg, int64_t S_or_T, int64_t D, float eps, void* stream,
+                      const float* mean, const float* rstd, void* dx, void* dshift, void* dscale,
+                      void* workspace, size_t workspace_bytes, int dtype);
+
+/*
  * lnmod_backward for callers that cannot allocate device memory and have no workspace to pass:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments and results as lnmod_backward (bit for bit: the same kernels and launch plan) without
@@ -192,6 +203,14 @@ int lnmod_gated_backward(const void* dy, const void* dh, const void* h, const vo
                          void* dx, void* du, float* dgate, float* dshift, float* dscale,
                          void* workspace, size_t workspace_bytes, int dtype);
 
+/* lnmod_gated_backward with dgate, dshift, dscale [B_or_nseg, D] in the I/O element type (see lnmod_backward_io). */
+int lnmod_gated_backward_io(const void* dy, const void* dh, const void* h, const void* u,
+                            const void* gate, const void* scale, const int32_t* cu_seqlens,
+                            int64_t B_or_nseg, int64_t S_or_T, int64_t D, float eps, void* stream,
+                            const float* mean, const float* rstd,
+                            void* dx, void* du, void* dgate, void* dshift, void* dscale,
+                            void* workspace, size_t workspace_bytes, int dtype);
+
 /* Bytes of device workspace lnmod_gated_backward needs (0 for invalid arguments).  Host-only. */
 size_t lnmod_gated_backward_workspace_bytes(int64_t B_or_nseg, int64_t total_tokens, int64_t D);
 
@@ -224,6 +243,13 @@ int lnmod_qknorm_backward(const void* dq_out, const void* dk_out, const void* q,
                           void* stream, const float* rstd_q, const float* rstd_k,
                           void* dq, void* dk, float* dwq, float* dwk,
                           void* workspace, size_t workspace_bytes, int dtype);
+
+/* lnmod_qknorm_backward with dwq, dwk [D] in the I/O element type, 16-byte aligned (see lnmod_backward_io). */
+int lnmod_qknorm_backward_io(const void* dq_out, const void* dk_out, const void* q, const void* k,
+                             const void* wq, const void* wk, int64_t N, int64_t D, float eps,
+                             void* stream, const float* rstd_q, const float* rstd_k,
+                             void* dq, void* dk, void* dwq, void* dwk,
+                             void* workspace, size_t workspace_bytes, int dtype);
 
 /* Bytes of device workspace lnmod_qknorm_backward needs (0 for invalid arguments).  Host-only. */
 size_t lnmod_qknorm_backward_workspace_bytes(int64_t N, int64_t D);

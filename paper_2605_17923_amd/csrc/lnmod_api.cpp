@@ -42,6 +42,78 @@ bool gated_shape(const int32_t* cu, int64_t B_or_nseg, int64_t S_or_T, int64_t* 
     return *T >= 0;
 }
 
+int gated_backward_impl(const void* dy, const void* dh, const void* h, const void* u,
+                         const void* gate, const void* scale, const int32_t* cu_seqlens,
+                         int64_t B_or_nseg, int64_t S_or_T, int64_t D, float eps, void* stream,
+                         const float* mean, const float* rstd, void* dx, void* du, void* dgate,
+                         void* dshift, void* dscale, void* workspace, size_t workspace_size,
+                         int dtype, bool io_grads) {
+    int64_t S, T;
+    if (!gated_shape(cu_seqlens, B_or_nseg, S_or_T, &S, &T)) return LNMOD_EINVAL;
+    const int st = check_shape(B_or_nseg, S_or_T, D, eps, dtype, T);
+    if (st != LNMOD_OK) return st;
+    const hipStream_t hs = static_cast<hipStream_t>(stream);
+    if (T == 0) {
+        if (B_or_nseg > 0) {                                  // empty sums are zeros
+            if (!dgate || !dshift || !dscale) return LNMOD_EINVAL;
+            const auto zero = [&](void* p) {
+                return lnmod::launch_zero_f32(static_cast<float*>(p), grad_floats(B_or_nseg * D, dtype, io_grads), hs);
+            };
+            hipError_t e = zero(dgate);
+            if (e == hipSuccess) e = zero(dshift);
+            if (e == hipSuccess) e = zero(dscale);
+            return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+        }
+        return LNMOD_OK;
+    }
+    if (B_or_nseg == 0) return LNMOD_EINVAL;
+    if (!dy || !dh || !h || !u || !gate || !scale || !mean || !rstd || !dx || !du || !dgate ||
+        !dshift || !dscale)
+        return LNMOD_EINVAL;
+    if (!aligned16(dy) || !aligned16(dh) || !aligned16(h) || !aligned16(u) || !aligned16(gate) ||
+        !aligned16(scale) || !aligned16(dx) || !aligned16(du) || !aligned16(dgate) ||
+        !aligned16(dshift) || !aligned16(dscale))
+        return LNMOD_EALIGN;
+    if (!workspace || workspace_size < gated_workspace_bytes(B_or_nseg, T, D)) return LNMOD_EWORKSPACE;
+    if (!aligned16(workspace)) return LNMOD_EALIGN;
+    const Problem p{dtype, cu_seqlens, B_or_nseg, S, T, D, eps};
+    const hipError_t e = lnmod::launch_gated_bwd(p, dy, dh, h, u, gate, scale, mean, rstd, dx, du,
+                                                 dgate, dshift, dscale, io_grads,
+                                                 static_cast<float*>(workspace), hs);
+    return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+}
+
+int qknorm_backward_impl(const void* dq_out, const void* dk_out, const void* q, const void* k,
+                          const void* wq, const void* wk, int64_t N, int64_t D, float eps,
+                          void* stream, const float* rstd_q, const float* rstd_k, void* dq, void* dk,
+                          void* dwq, void* dwk, void* workspace, size_t workspace_size, int dtype, bool io_grads) {
+    const int st = check_shape(1, N, D, eps, dtype, N);
+    if (st != LNMOD_OK) return st;
+    const hipStream_t hs = static_cast<hipStream_t>(stream);
+    if (N == 0) {                                             // empty sums are zeros
+        if (!dwq || !dwk) return LNMOD_EINVAL;
+        if (io_grads && (!aligned16(dwq) || !aligned16(dwk))) return LNMOD_EALIGN;
+        const auto zero = [&](void* p) {
+            return lnmod::launch_zero_f32(static_cast<float*>(p), grad_floats(D, dtype, io_grads), hs);
+        };
+        hipError_t e = zero(dwq);
+        if (e == hipSuccess) e = zero(dwk);
+        return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+    }
+    if (!dq_out || !dk_out || !q || !k || !wq || !wk || !rstd_q || !rstd_k || !dq || !dk || !dwq || !dwk)
+        return LNMOD_EINVAL;
+    if (!aligned16(dq_out) || !aligned16(dk_out) || !aligned16(q) || !aligned16(k) || !aligned16(wq) ||
+        !aligned16(wk) || !aligned16(dq) || !aligned16(dk) ||
+        (io_grads && (!aligned16(dwq) || !aligned16(dwk))))
+        return LNMOD_EALIGN;
+    if (!workspace || workspace_size < qknorm_workspace_bytes(N, D)) return LNMOD_EWORKSPACE;
+    if (!aligned16(workspace)) return LNMOD_EALIGN;
+    const hipError_t e = lnmod::launch_qknorm_bwd(dtype, dq_out, dk_out, q, k, wq, wk, N, D, rstd_q,
+                                                  rstd_k, dq, dk, dwq, dwk, io_grads,
+                                                  static_cast<float*>(workspace), hs);
+    return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+}
+
 }  // namespace
 
 extern "C" {
@@ -116,6 +188,17 @@ int lnmod_backward_static(const void* dy, const void* x, const void* shift, cons
                          dshift, dscale, ws, ws_bytes, dtype, mod, nullptr, /*exact_workspace=*/true);
 }
 
+int lnmod_backward_io(const void* dy, const void* x, const void* scale, const int32_t* cu_seqlens,
+                      int64_t B_or_nseg, int64_t S_or_T, int64_t D, float eps, void* stream,
+                      const float* mean, const float* rstd, void* dx, void* dshift, void* dscale,
+                      void* workspace, size_t workspace_size, int dtype) {
+    int64_t S, T;
+    if (!gated_shape(cu_seqlens, B_or_nseg, S_or_T, &S, &T)) return LNMOD_EINVAL;
+    return backward_impl(dy, x, scale, cu_seqlens, cu_seqlens != nullptr, B_or_nseg, S, T, D, eps, stream, mean,
+                         rstd, dx, dshift, dscale, workspace, workspace_size, dtype, LNMOD_PER_SAMPLE, nullptr,
+                         false, /*io_grads=*/true);
+}
+
 size_t lnmod_backward_workspace_bytes(int64_t B_or_nseg, int64_t total, int64_t D, int mod) {
     if (mod != LNMOD_PER_SAMPLE) return 0;
     if (B_or_nseg < 0 || total < 0 || total >= (int64_t(1) << 31)) return 0;
@@ -161,36 +244,18 @@ int lnmod_gated_backward(const void* dy, const void* dh, const void* h, const vo
                          const float* mean, const float* rstd, void* dx, void* du, float* dgate,
                          float* dshift, float* dscale, void* workspace, size_t workspace_size,
                          int dtype) {
-    int64_t S, T;
-    if (!gated_shape(cu_seqlens, B_or_nseg, S_or_T, &S, &T)) return LNMOD_EINVAL;
-    const int st = check_shape(B_or_nseg, S_or_T, D, eps, dtype, T);
-    if (st != LNMOD_OK) return st;
-    const hipStream_t hs = static_cast<hipStream_t>(stream);
-    if (T == 0) {
-        if (B_or_nseg > 0) {                                  // empty sums are zeros
-            if (!dgate || !dshift || !dscale) return LNMOD_EINVAL;
-            hipError_t e = lnmod::launch_zero_f32(dgate, B_or_nseg * D, hs);
-            if (e == hipSuccess) e = lnmod::launch_zero_f32(dshift, B_or_nseg * D, hs);
-            if (e == hipSuccess) e = lnmod::launch_zero_f32(dscale, B_or_nseg * D, hs);
-            return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
-        }
-        return LNMOD_OK;
-    }
-    if (B_or_nseg == 0) return LNMOD_EINVAL;
-    if (!dy || !dh || !h || !u || !gate || !scale || !mean || !rstd || !dx || !du || !dgate ||
-        !dshift || !dscale)
-        return LNMOD_EINVAL;
-    if (!aligned16(dy) || !aligned16(dh) || !aligned16(h) || !aligned16(u) || !aligned16(gate) ||
-        !aligned16(scale) || !aligned16(dx) || !aligned16(du) || !aligned16(dgate) ||
-        !aligned16(dshift) || !aligned16(dscale))
-        return LNMOD_EALIGN;
-    if (!workspace || workspace_size < gated_workspace_bytes(B_or_nseg, T, D)) return LNMOD_EWORKSPACE;
-    if (!aligned16(workspace)) return LNMOD_EALIGN;
-    const Problem p{dtype, cu_seqlens, B_or_nseg, S, T, D, eps};
-    const hipError_t e = lnmod::launch_gated_bwd(p, dy, dh, h, u, gate, scale, mean, rstd, dx, du,
-                                                 dgate, dshift, dscale,
-                                                 static_cast<float*>(workspace), hs);
-    return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+    return gated_backward_impl(dy, dh, h, u, gate, scale, cu_seqlens, B_or_nseg, S_or_T, D, eps, stream, mean, rstd,
+                               dx, du, dgate, dshift, dscale, workspace, workspace_size, dtype, false);
+}
+
+int lnmod_gated_backward_io(const void* dy, const void* dh, const void* h, const void* u,
+                            const void* gate, const void* scale, const int32_t* cu_seqlens,
+                            int64_t B_or_nseg, int64_t S_or_T, int64_t D, float eps, void* stream,
+                            const float* mean, const float* rstd, void* dx, void* du, void* dgate,
+                            void* dshift, void* dscale, void* workspace, size_t workspace_size,
+                            int dtype) {
+    return gated_backward_impl(dy, dh, h, u, gate, scale, cu_seqlens, B_or_nseg, S_or_T, D, eps, stream, mean, rstd,
+                               dx, du, dgate, dshift, dscale, workspace, workspace_size, dtype, true);
 }
 
 size_t lnmod_gated_backward_workspace_bytes(int64_t B_or_nseg, int64_t total, int64_t D) {
@@ -218,26 +283,16 @@ int lnmod_qknorm_backward(const void* dq_out, const void* dk_out, const void* q,
                           const void* wq, const void* wk, int64_t N, int64_t D, float eps,
                           void* stream, const float* rstd_q, const float* rstd_k, void* dq, void* dk,
                           float* dwq, float* dwk, void* workspace, size_t workspace_size, int dtype) {
-    const int st = check_shape(1, N, D, eps, dtype, N);
-    if (st != LNMOD_OK) return st;
-    const hipStream_t hs = static_cast<hipStream_t>(stream);
-    if (N == 0) {                                             // empty sums are zeros
-        if (!dwq || !dwk) return LNMOD_EINVAL;
-        hipError_t e = lnmod::launch_zero_f32(dwq, D, hs);
-        if (e == hipSuccess) e = lnmod::launch_zero_f32(dwk, D, hs);
-        return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
-    }
-    if (!dq_out || !dk_out || !q || !k || !wq || !wk || !rstd_q || !rstd_k || !dq || !dk || !dwq || !dwk)
-        return LNMOD_EINVAL;
-    if (!aligned16(dq_out) || !aligned16(dk_out) || !aligned16(q) || !aligned16(k) || !aligned16(wq) ||
-        !aligned16(wk) || !aligned16(dq) || !aligned16(dk))
-        return LNMOD_EALIGN;
-    if (!workspace || workspace_size < qknorm_workspace_bytes(N, D)) return LNMOD_EWORKSPACE;
-    if (!aligned16(workspace)) return LNMOD_EALIGN;
-    const hipError_t e = lnmod::launch_qknorm_bwd(dtype, dq_out, dk_out, q, k, wq, wk, N, D, rstd_q,
-                                                  rstd_k, dq, dk, dwq, dwk,
-                                                  static_cast<float*>(workspace), hs);
-    return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
+    return qknorm_backward_impl(dq_out, dk_out, q, k, wq, wk, N, D, eps, stream, rstd_q, rstd_k, dq, dk, dwq, dwk,
+                                workspace, workspace_size, dtype, false);
+}
+
+int lnmod_qknorm_backward_io(const void* dq_out, const void* dk_out, const void* q, const void* k,
+                             const void* wq, const void* wk, int64_t N, int64_t D, float eps,
+                             void* stream, const float* rstd_q, const float* rstd_k, void* dq, void* dk,
+                             void* dwq, void* dwk, void* workspace, size_t workspace_size, int dtype) {
+    return qknorm_backward_impl(dq_out, dk_out, q, k, wq, wk, N, D, eps, stream, rstd_q, rstd_k, dq, dk, dwq, dwk,
+                                workspace, workspace_size, dtype, true);
 }
 
 size_t lnmod_qknorm_backward_workspace_bytes(int64_t N, int64_t D) {

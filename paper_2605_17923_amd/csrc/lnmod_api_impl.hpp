@@ -65,11 +65,14 @@ inline int forward_impl(const void* x, const void* shift, const void* scale, con
     return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
 }
 
+// 4-byte words of n parameter gradients (n is a multiple of D, which is a multiple of 8 in bf16)
+inline int64_t grad_floats(int64_t n, int dtype, bool io_grads) { return io_grads && dtype == LNMOD_BF16 ? n / 2 : n; }
+
 inline int backward_impl(const void* dy, const void* x, const void* scale, const int32_t* cu, bool varlen,
                          int64_t nseg, int64_t S, int64_t T, int64_t D, float eps, void* stream,
                          const float* mean, const float* rstd, void* dx, void* dshift, void* dscale,
                          void* workspace, size_t workspace_size, int dtype, int mod,
-                         const Shape* force = nullptr, bool exact_workspace = false) {
+                         const Shape* force = nullptr, bool exact_workspace = false, bool io_grads = false) {
     if (mod != LNMOD_PER_SAMPLE && mod != LNMOD_PER_TOKEN) return LNMOD_EINVAL;
     const int st = check_shape(nseg, varlen ? T : S, D, eps, dtype, T);
     if (st != LNMOD_OK) return st;
@@ -78,8 +81,9 @@ inline int backward_impl(const void* dy, const void* x, const void* scale, const
         if (mod == LNMOD_PER_SAMPLE && nseg > 0) {      // empty sums are zeros
             if (!dshift || !dscale) return LNMOD_EINVAL;
             if (!aligned16(dshift) || !aligned16(dscale)) return LNMOD_EALIGN;
-            hipError_t e = launch_zero_f32(static_cast<float*>(dshift), nseg * D, hs);
-            if (e == hipSuccess) e = launch_zero_f32(static_cast<float*>(dscale), nseg * D, hs);
+            hipError_t e = launch_zero_f32(static_cast<float*>(dshift), grad_floats(nseg * D, dtype, io_grads), hs);
+            if (e == hipSuccess)
+                e = launch_zero_f32(static_cast<float*>(dscale), grad_floats(nseg * D, dtype, io_grads), hs);
             return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
         }
         return LNMOD_OK;
@@ -103,8 +107,8 @@ inline int backward_impl(const void* dy, const void* x, const void* scale, const
                             : workspace_bytes(nseg, T, D, force);
         if (!workspace || workspace_size < need) return LNMOD_EWORKSPACE;
         if (!aligned16(workspace)) return LNMOD_EALIGN;
-        e = launch_bwd_seg(p, dy, x, scale, mean, rstd, dx, static_cast<float*>(dshift),
-                                  static_cast<float*>(dscale), static_cast<float*>(workspace), hs);
+        e = launch_bwd_seg(p, dy, x, scale, mean, rstd, dx, dshift, dscale, io_grads,
+                           static_cast<float*>(workspace), hs);
     }
     return e == hipSuccess ? LNMOD_OK : LNMOD_ELAUNCH;
 }

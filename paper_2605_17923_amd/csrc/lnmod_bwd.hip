@@ -166,8 +166,8 @@ RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, 
 }
 
 hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const void* scale,
-                          const float* mean, const float* rstd, void* dx, float* dshift,
-                          float* dscale, float* ws, hipStream_t st) {
+                          const float* mean, const float* rstd, void* dx, void* dshift,
+                          void* dscale, bool io_grads, float* ws, hipStream_t st) {
     const int E = p.dtype == 0 ? 8 : 4;
     BwdArgs a = make_args(p, dy, x, scale, mean, rstd, dx, nullptr, nullptr, ws, E);
     const bool rc = mean == nullptr;
@@ -189,6 +189,7 @@ hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const
     r.out[0] = dshift;
     r.out[1] = dscale;
     r.out[2] = nullptr;
+    r.out_bf16 = io_grads && p.dtype == 0;
     r.seg = a.seg;
     r.T = p.T;
     r.rows_per_cluster = a.rows_per_cluster;

@@ -113,8 +113,8 @@ RowPlan gated_bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype) {
 
 hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, const void* h,
                             const void* u, const void* gate, const void* scale, const float* mean,
-                            const float* rstd, void* dx, void* du, float* dgate, float* dshift,
-                            float* dscale, float* ws, hipStream_t st) {
+                            const float* rstd, void* dx, void* du, void* dgate, void* dshift,
+                            void* dscale, bool io_grads, float* ws, hipStream_t st) {
     const int E = p.dtype == 0 ? 8 : 4;
     GatedBwdArgs a;
     a.dy = dy;
@@ -149,6 +149,7 @@ hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, co
     r.out[0] = dshift;
     r.out[1] = dscale;
     r.out[2] = dgate;
+    r.out_bf16 = io_grads && p.dtype == 0;
     r.seg = a.seg;
     r.T = p.T;
     r.rows_per_cluster = a.rows_per_cluster;

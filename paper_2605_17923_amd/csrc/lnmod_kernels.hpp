@@ -926,7 +926,8 @@ void bwd_seg_kernel(const BwdArgs a) {
 // from the shapes alone, so results repeat bit for bit.
 struct ReduceArgs {
     const float* ws;         // [nslots][nsum][D]
-    float* out[3];           // [nseg, D] each
+    void* out[3];            // [nseg, D] each, float32 or bf16
+    int32_t out_bf16;        // 1: the sums are rounded once, here, to bf16
     Segments seg;
     int64_t T;
     int64_t rows_per_cluster;
@@ -936,6 +937,24 @@ struct ReduceArgs {
     int32_t nsum;            // 2 or 3
     int64_t total;           // nseg * nsum * dblocks: (segment, sum, feature block) triples
 };
+
+// Stores V consecutive sums.  A caller that keeps the gradients in the tensors' own type used to
+// cast the float32 sums with a kernel per gradient (4.4 us each on top of a 5 us second pass); the
+// rounding to nearest even is the same one.
+template <int V, typename VEC>
+__device__ inline void store_sums(void* out, int64_t at, const VEC& v, bool bf16) {
+    if (!bf16) {
+        *reinterpret_cast<VEC*>(static_cast<float*>(out) + at) = v;
+        return;
+    }
+    __bf16* p = static_cast<__bf16*>(out) + at;
+    if constexpr (V == 1) {
+        *p = static_cast<__bf16>(v);
+    } else {
+        typedef __bf16 half_vec __attribute__((ext_vector_type(V)));
+        *reinterpret_cast<half_vec*>(p) = __builtin_convertvector(v, half_vec);
+    }
+}
 
 constexpr int kReduceWaves = 16;     // most waves a reduce block may have
 constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 16 / V slot loads
@@ -1006,7 +1025,7 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
             __syncthreads();                      // red is written again in the next round
         }
         if (wave == 0 && grp == 0 && d < a.D)
-            *reinterpret_cast<vec*>(a.out[which] + m * a.D + d) = acc;
+            store_sums<V>(a.out[which], m * a.D + d, acc, a.out_bf16 != 0);
     }
 }
 

@@ -418,9 +418,10 @@ hipError_t launch_fwd_seg(const Problem& p, const void* x, const void* shift, co
                           void* y, float* mean, float* rstd, hipStream_t st);
 hipError_t launch_fwd_tok(const Problem& p, const void* x, const void* shift, const void* scale,
                           void* y, float* mean, float* rstd, hipStream_t st);
+// io_grads: the reduced parameter gradients are written in the I/O element type instead of float32.
 hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const void* scale,
-                          const float* mean, const float* rstd, void* dx, float* dshift,
-                          float* dscale, float* ws, hipStream_t st);
+                          const float* mean, const float* rstd, void* dx, void* dshift,
+                          void* dscale, bool io_grads, float* ws, hipStream_t st);
 hipError_t launch_bwd_tok(const Problem& p, const void* dy, const void* x, const void* scale,
                           const float* mean, const float* rstd, void* dx, void* dshift,
                           void* dscale, hipStream_t st);
@@ -442,8 +443,8 @@ hipError_t launch_gate_residual(const Problem& p, const void* x, const void* u, 
                                 void* h, hipStream_t st);
 hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, const void* h,
                             const void* u, const void* gate, const void* scale, const float* mean,
-                            const float* rstd, void* dx, void* du, float* dgate, float* dshift,
-                            float* dscale, float* ws, hipStream_t st);
+                            const float* rstd, void* dx, void* du, void* dgate, void* dshift,
+                            void* dscale, bool io_grads, float* ws, hipStream_t st);
 hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t st);
 
 
@@ -456,6 +457,6 @@ hipError_t launch_qknorm_fwd(int dtype, const void* q, const void* k, const void
 hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, const void* q,
                              const void* k, const void* wq, const void* wk, int64_t N, int64_t D,
                              const float* rstd_q, const float* rstd_k, void* dq, void* dk,
-                             float* dwq, float* dwk, float* ws, hipStream_t st);
+                             void* dwq, void* dwk, bool io_grads, float* ws, hipStream_t st);
 
 }  // namespace lnmod

@@ -208,7 +208,7 @@ hipError_t launch_qknorm_fwd(int dtype, const void* q, const void* k, const void
 hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, const void* q,
                              const void* k, const void* wq, const void* wk, int64_t N, int64_t D,
                              const float* rstd_q, const float* rstd_k, void* dq, void* dk,
-                             float* dwq, float* dwk, float* ws, hipStream_t st) {
+                             void* dwq, void* dwk, bool io_grads, float* ws, hipStream_t st) {
     const int E = dtype == 0 ? 8 : 4;
     QkBwdArgs a;
     a.dy[0] = dq_out; a.dy[1] = dk_out;
@@ -249,6 +249,7 @@ hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, 
     r.ws = ws;
     r.dw[0] = dwq;
     r.dw[1] = dwk;
+    r.out_bf16 = io_grads && dtype == 0;
     r.nb = slots;
     r.D = a.D;
     r.dblocks = static_cast<int32_t>((D + kWave - 1) / kWave);

@@ -560,7 +560,8 @@ void qknorm_short_bwd_kernel(const QkBwdArgs a) {
 // waves, the 16 wave sums then added in wave order.  grid.x = 2 * dblocks.
 struct QkReduceArgs {
     const float* ws;
-    float* dw[2];
+    void* dw[2];             // float32 or bf16
+    int32_t out_bf16;        // see ReduceArgs
     int32_t nb;
     int32_t D;
     int32_t dblocks;
@@ -595,7 +596,7 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void qknorm_reduce_kernel(cons
         float s = 0.0f;
 #pragma unroll
         for (int w = 0; w < kReduceWaves; ++w) s += red[w][lane];
-        (t ? a.dw[1] : a.dw[0])[d] = s;
+        store_sums<1>(t ? a.dw[1] : a.dw[0], d, s, a.out_bf16 != 0);
     }
 }
 

@@ -1,7 +1,8 @@
 """torch.autograd wrappers over the C ABI: the three fused operators as differentiable functions.
 
 Everything numerical runs in the HIP kernels; this module only allocates outputs with torch,
-keeps what the backward needs and casts the float32 parameter gradients to the parameters' dtype.
+keeps what the backward needs; the kernels round the float32 sums of the parameter gradients to the
+parameters' dtype where they form them.
 Inputs must be contiguous CUDA tensors in bfloat16 or float32; work is enqueued on torch's
 current stream.  Without the built library every call raises (there is no fallback).
 
@@ -33,7 +34,6 @@ class _LnModulate(torch.autograd.Function):
             y, mean, rstd = lnmod.forward_varlen(x, shift, scale, cu_seqlens, eps)
         ctx.eps = eps
         ctx.has_cu = cu_seqlens is not None
-        ctx.param_dtype = shift.dtype
         if save_stats:
             ctx.save_for_backward(x, scale, cu_seqlens, mean, rstd)
         else:                                   # the backward forms them again from x
@@ -45,10 +45,10 @@ class _LnModulate(torch.autograd.Function):
         x, scale, cu, mean, rstd = ctx.saved_tensors
         dy = dy.contiguous()
         if ctx.has_cu:
-            dx, dshift, dscale = lnmod.backward_varlen(dy, x, scale, cu, mean, rstd, ctx.eps)
+            dx, dshift, dscale = lnmod._backward_varlen(dy, x, scale, cu, mean, rstd, ctx.eps, io_grads=True)
         else:
-            dx, dshift, dscale = lnmod.backward(dy, x, scale, mean, rstd, ctx.eps)
-        return dx, dshift.to(ctx.param_dtype), dscale.to(ctx.param_dtype), None, None, None
+            dx, dshift, dscale = lnmod._backward(dy, x, scale, mean, rstd, ctx.eps, io_grads=True)
+        return dx, dshift, dscale, None, None, None
 
 
 def ln_modulate(x, shift, scale, eps=1e-6, cu_seqlens=None, save_stats=True):
@@ -65,17 +65,15 @@ class _GatedLnModulate(torch.autograd.Function):
         _contig(x, u, gate, shift, scale, cu_seqlens)
         h, y, mean, rstd = lnmod.gated_forward(x, u, gate, shift, scale, cu_seqlens, eps)
         ctx.eps = eps
-        ctx.param_dtype = gate.dtype
         ctx.save_for_backward(h, u, gate, scale, cu_seqlens, mean, rstd)
         return h, y
 
     @staticmethod
     def backward(ctx, dh, dy):
         h, u, gate, scale, cu, mean, rstd = ctx.saved_tensors
-        dx, du, dgate, dshift, dscale = lnmod.gated_backward(dy.contiguous(), dh.contiguous(), h, u, gate,
-                                                             scale, mean, rstd, cu, ctx.eps)
-        pd = ctx.param_dtype
-        return dx, du, dgate.to(pd), dshift.to(pd), dscale.to(pd), None, None
+        dx, du, dgate, dshift, dscale = lnmod._gated_backward(dy.contiguous(), dh.contiguous(), h, u, gate,
+                                                              scale, mean, rstd, cu, ctx.eps, io_grads=True)
+        return dx, du, dgate, dshift, dscale, None, None
 
 
 def gated_ln_modulate(x, u, gate, shift, scale, eps=1e-6, cu_seqlens=None):
@@ -91,16 +89,15 @@ class _QkNorm(torch.autograd.Function):
         _contig(q, k, wq, wk)
         qn, kn, rq, rk = lnmod.qknorm_forward(q, k, wq, wk, eps)
         ctx.eps = eps
-        ctx.param_dtype = wq.dtype
         ctx.save_for_backward(q, k, wq, wk, rq, rk)
         return qn, kn
 
     @staticmethod
     def backward(ctx, dqn, dkn):
         q, k, wq, wk, rq, rk = ctx.saved_tensors
-        dq, dk, dwq, dwk = lnmod.qknorm_backward(dqn.contiguous(), dkn.contiguous(), q, k, wq, wk, rq, rk,
-                                                 ctx.eps)
-        return dq, dk, dwq.to(ctx.param_dtype), dwk.to(ctx.param_dtype), None
+        dq, dk, dwq, dwk = lnmod._qknorm_backward(dqn.contiguous(), dkn.contiguous(), q, k, wq, wk, rq, rk,
+                                                  ctx.eps, io_grads=True)
+        return dq, dk, dwq, dwk, None
 
 
 def qk_norm(q, k, wq, wk, eps=1e-6):

@@ -24,7 +24,8 @@ LNMOD_STATIC_WORKSPACE_BYTES = 64 << 20
 EXPORTS = ("lnmod_forward", "lnmod_backward", "lnmod_forward_varlen", "lnmod_backward_varlen",
            "lnmod_backward_static", "lnmod_backward_workspace_bytes", "lnmod_status_string", "lnmod_gated_forward",
            "lnmod_gated_backward", "lnmod_gated_backward_workspace_bytes", "lnmod_qknorm_forward",
-           "lnmod_qknorm_backward", "lnmod_qknorm_backward_workspace_bytes")
+           "lnmod_qknorm_backward", "lnmod_qknorm_backward_workspace_bytes", "lnmod_backward_io",
+           "lnmod_gated_backward_io", "lnmod_qknorm_backward_io")
 
 _lib = None
 
@@ -76,6 +77,12 @@ def library() -> ctypes.CDLL:
     lib.lnmod_qknorm_backward.restype = cint
     lib.lnmod_qknorm_backward.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, f32, vp, vp, vp,
                                           vp, vp, vp, vp, vp, sz, cint]
+    lib.lnmod_backward_io.restype = cint
+    lib.lnmod_backward_io.argtypes = [vp, vp, vp, vp, i64, i64, i64, f32, vp, vp, vp, vp, vp, vp, vp, sz, cint]
+    lib.lnmod_gated_backward_io.restype = cint
+    lib.lnmod_gated_backward_io.argtypes = lib.lnmod_gated_backward.argtypes
+    lib.lnmod_qknorm_backward_io.restype = cint
+    lib.lnmod_qknorm_backward_io.argtypes = lib.lnmod_qknorm_backward.argtypes
     lib.lnmod_qknorm_backward_workspace_bytes.restype = sz
     lib.lnmod_qknorm_backward_workspace_bytes.argtypes = [i64, i64]
     _lib = lib
@@ -133,6 +140,13 @@ def lnmod_backward_varlen(dy, x, shift, scale, cu_seqlens, nseg, T, D, eps, stre
                                            dtype)
 
 
+def lnmod_backward_io(dy, x, scale, cu_seqlens, B_or_nseg, S_or_T, D, eps, stream, mean, rstd, dx, dshift,
+                      dscale, workspace, workspace_bytes, dtype):
+    return library().lnmod_backward_io(_p(dy), _p(x), _p(scale), _p(cu_seqlens), B_or_nseg, S_or_T, D,
+                                       eps, stream, _p(mean), _p(rstd), _p(dx), _p(dshift), _p(dscale),
+                                       _p(workspace), workspace_bytes, dtype)
+
+
 def lnmod_backward_workspace_bytes(B_or_nseg, total_tokens, D, mod):
     return int(library().lnmod_backward_workspace_bytes(B_or_nseg, total_tokens, D, mod))
 
@@ -158,6 +172,16 @@ def lnmod_gated_backward(dy, dh, h, u, gate, scale, cu_seqlens, B_or_nseg, S_or_
                                           dtype)
 
 
+def lnmod_gated_backward_io(dy, dh, h, u, gate, scale, cu_seqlens, B_or_nseg, S_or_T, D, eps, stream,
+                            mean, rstd, dx, du, dgate, dshift, dscale, workspace, workspace_bytes,
+                            dtype):
+    return library().lnmod_gated_backward_io(_p(dy), _p(dh), _p(h), _p(u), _p(gate), _p(scale),
+                                             _p(cu_seqlens), B_or_nseg, S_or_T, D, eps, stream,
+                                             _p(mean), _p(rstd), _p(dx), _p(du), _p(dgate),
+                                             _p(dshift), _p(dscale), _p(workspace), workspace_bytes,
+                                             dtype)
+
+
 def lnmod_gated_backward_workspace_bytes(B_or_nseg, total_tokens, D):
     return int(library().lnmod_gated_backward_workspace_bytes(B_or_nseg, total_tokens, D))
 
@@ -173,6 +197,14 @@ def lnmod_qknorm_backward(dq_out, dk_out, q, k, wq, wk, N, D, eps, stream, rstd_
                                            N, D, eps, stream, _p(rstd_q), _p(rstd_k), _p(dq),
                                            _p(dk), _p(dwq), _p(dwk), _p(workspace),
                                            workspace_bytes, dtype)
+
+
+def lnmod_qknorm_backward_io(dq_out, dk_out, q, k, wq, wk, N, D, eps, stream, rstd_q, rstd_k, dq, dk,
+                             dwq, dwk, workspace, workspace_bytes, dtype):
+    return library().lnmod_qknorm_backward_io(_p(dq_out), _p(dk_out), _p(q), _p(k), _p(wq), _p(wk),
+                                              N, D, eps, stream, _p(rstd_q), _p(rstd_k), _p(dq),
+                                              _p(dk), _p(dwq), _p(dwk), _p(workspace),
+                                              workspace_bytes, dtype)
 
 
 def lnmod_qknorm_backward_workspace_bytes(N, D):
@@ -328,6 +360,11 @@ def workspace(B_or_nseg, total_tokens, D, device):
 def backward(dy, x, scale, mean, rstd, eps=1e-6, stream=None, ws=None):
     """-> dx, dshift, dscale (float32 [B,D] per sample; I/O dtype [B,S,D] per token).
     mean = rstd = None: the statistics are formed again from x with eps."""
+    return _backward(dy, x, scale, mean, rstd, eps, stream, ws)
+
+
+def _backward(dy, x, scale, mean, rstd, eps, stream=None, ws=None, io_grads=False):
+    """backward(); with io_grads dshift and dscale come in the I/O dtype in either mode."""
     import torch
     code = _dtype_code(x)
     mod, mshape = _mod_rows(x, scale, "scale")
@@ -351,11 +388,16 @@ def backward(dy, x, scale, mean, rstd, eps=1e-6, stream=None, ws=None):
             dshift, dscale = torch.empty_like(x), torch.empty_like(x)
             ws_ptr, ws_bytes = None, 0
         else:
-            dshift = torch.empty(B, D, dtype=torch.float32, device=x.device)
-            dscale = torch.empty(B, D, dtype=torch.float32, device=x.device)
+            dt = x.dtype if io_grads else torch.float32
+            dshift = torch.empty(B, D, dtype=dt, device=x.device)
+            dscale = torch.empty(B, D, dtype=dt, device=x.device)
             if ws is None:
                 ws = workspace(B, B * S, D, x.device)
             ws_ptr, ws_bytes = ws, ws.numel()
+        if io_grads and mod == LNMOD_PER_SAMPLE:
+            _check(lnmod_backward_io(dy, x, scale, None, B, S, D, eps, handle, mean, rstd, dx, dshift,
+                                     dscale, ws_ptr, ws_bytes, code), "lnmod_backward_io")
+            return dx, dshift, dscale
         _check(lnmod_backward(dy, x, None, scale, B, S, D, eps, handle, mean, rstd, dx, dshift,
                               dscale, ws_ptr, ws_bytes, code, mod), "lnmod_backward")
     return dx, dshift, dscale
@@ -388,6 +430,11 @@ def forward_varlen(x, shift, scale, cu_seqlens, eps=1e-6, stream=None):
 
 
 def backward_varlen(dy, x, scale, cu_seqlens, mean, rstd, eps=1e-6, stream=None, ws=None):
+    return _backward_varlen(dy, x, scale, cu_seqlens, mean, rstd, eps, stream, ws)
+
+
+def _backward_varlen(dy, x, scale, cu_seqlens, mean, rstd, eps, stream=None, ws=None, io_grads=False):
+    """backward_varlen(); with io_grads dshift and dscale come in the I/O dtype."""
     import torch
     code = _dtype_code(x)
     T, D = _packed(x)
@@ -401,10 +448,15 @@ def backward_varlen(dy, x, scale, cu_seqlens, mean, rstd, eps=1e-6, stream=None,
     a.on_gpu()
     with _on_stream(stream) as handle:
         dx = torch.empty_like(x)
-        dshift = torch.empty(nseg, D, dtype=torch.float32, device=x.device)
-        dscale = torch.empty(nseg, D, dtype=torch.float32, device=x.device)
+        dt = x.dtype if io_grads else torch.float32
+        dshift = torch.empty(nseg, D, dtype=dt, device=x.device)
+        dscale = torch.empty(nseg, D, dtype=dt, device=x.device)
         if ws is None:
             ws = workspace(nseg, T, D, x.device)
+        if io_grads:
+            _check(lnmod_backward_io(dy, x, scale, cu_seqlens, nseg, T, D, eps, handle, mean, rstd, dx,
+                                     dshift, dscale, ws, ws.numel(), code), "lnmod_backward_io")
+            return dx, dshift, dscale
         _check(lnmod_backward_varlen(dy, x, None, scale, cu_seqlens, nseg, T, D, eps, handle, mean,
                                      rstd, dx, dshift, dscale, ws, ws.numel(), code),
                "lnmod_backward_varlen")
@@ -453,6 +505,12 @@ def gated_forward(x, u, gate, shift, scale, cu_seqlens=None, eps=1e-6, stream=No
 def gated_backward(dy, dh, h, u, gate, scale, mean, rstd, cu_seqlens=None, eps=1e-6, stream=None,
                    ws=None):
     """-> dx, du (I/O dtype) and dgate, dshift, dscale (float32 [B,D] / [nseg,D])."""
+    return _gated_backward(dy, dh, h, u, gate, scale, mean, rstd, cu_seqlens, eps, stream, ws)
+
+
+def _gated_backward(dy, dh, h, u, gate, scale, mean, rstd, cu_seqlens, eps, stream=None, ws=None,
+                    io_grads=False):
+    """gated_backward(); with io_grads dgate, dshift and dscale come in the I/O dtype."""
     import torch
     code = _dtype_code(h)
     a = _Args(h)
@@ -468,14 +526,13 @@ def gated_backward(dy, dh, h, u, gate, scale, mean, rstd, cu_seqlens=None, eps=1
     a.on_gpu()
     with _on_stream(stream) as handle:
         dx, du = torch.empty_like(h), torch.empty_like(h)
-        dgate = torch.empty(n, D, dtype=torch.float32, device=h.device)
-        dshift = torch.empty(n, D, dtype=torch.float32, device=h.device)
-        dscale = torch.empty(n, D, dtype=torch.float32, device=h.device)
+        dt = h.dtype if io_grads else torch.float32
+        dgate, dshift, dscale = (torch.empty(n, D, dtype=dt, device=h.device) for _ in range(3))
         if ws is None:
             ws = gated_workspace(n, T, D, h.device)
-        _check(lnmod_gated_backward(dy, dh, h, u, gate, scale, cu_seqlens, n, s_or_t, D, eps, handle,
-                                    mean, rstd, dx, du, dgate, dshift, dscale, ws, ws.numel(), code),
-               "lnmod_gated_backward")
+        call = lnmod_gated_backward_io if io_grads else lnmod_gated_backward
+        _check(call(dy, dh, h, u, gate, scale, cu_seqlens, n, s_or_t, D, eps, handle, mean, rstd, dx, du,
+                    dgate, dshift, dscale, ws, ws.numel(), code), call.__name__)
     return dx, du, dgate, dshift, dscale
 
 
@@ -509,6 +566,12 @@ def qknorm_forward(q, k, wq, wk, eps=1e-6, stream=None):
 
 def qknorm_backward(dq_out, dk_out, q, k, wq, wk, rstd_q, rstd_k, eps=1e-6, stream=None, ws=None):
     """-> dq, dk (I/O dtype) and dwq, dwk (float32 [D])."""
+    return _qknorm_backward(dq_out, dk_out, q, k, wq, wk, rstd_q, rstd_k, eps, stream, ws)
+
+
+def _qknorm_backward(dq_out, dk_out, q, k, wq, wk, rstd_q, rstd_k, eps, stream=None, ws=None,
+                     io_grads=False):
+    """qknorm_backward(); with io_grads dwq and dwk come in the I/O dtype."""
     import torch
     code = _dtype_code(q)
     N, D = _qk_rows(q)
@@ -525,10 +588,11 @@ def qknorm_backward(dq_out, dk_out, q, k, wq, wk, rstd_q, rstd_k, eps=1e-6, stre
     a.on_gpu()
     with _on_stream(stream) as handle:
         dq, dk = torch.empty_like(q), torch.empty_like(k)
-        dwq = torch.empty(D, dtype=torch.float32, device=q.device)
-        dwk = torch.empty(D, dtype=torch.float32, device=q.device)
+        dwq, dwk = (torch.empty(D, dtype=q.dtype if io_grads else torch.float32, device=q.device)
+                    for _ in range(2))
         if ws is None:
             ws = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
-        _check(lnmod_qknorm_backward(dq_out, dk_out, q, k, wq, wk, N, D, eps, handle, rstd_q, rstd_k,
-                                     dq, dk, dwq, dwk, ws, ws.numel(), code), "lnmod_qknorm_backward")
+        call = lnmod_qknorm_backward_io if io_grads else lnmod_qknorm_backward
+        _check(call(dq_out, dk_out, q, k, wq, wk, N, D, eps, handle, rstd_q, rstd_k, dq, dk, dwq, dwk, ws,
+                    ws.numel(), code), call.__name__)
     return dq, dk, dwq, dwk
