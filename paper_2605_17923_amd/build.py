@@ -1,14 +1,17 @@
-"""Builds the two shared libraries (gfx950 only) in-tree with hipcc: one object per translation
-unit, compiled in parallel, then linked twice.  liblnmod.so is the operator library (include/lnmod.h,
+"""Builds the shared libraries in-tree: the two HIP libraries (gfx950 only) with hipcc, one object per
+translation unit, compiled in parallel, then linked twice, and the host-only extension module that holds
+the autograd functions with the C++ compiler.  liblnmod.so is the operator library (include/lnmod.h,
 include/lnmod_sched.h); liblnmod_tools.so is its measurement companion (include/lnmod_tools.h): the
 same kernel objects plus the bandwidth probes, the unfused comparators and the calls that take their
-launch shape as an argument.  Both export their C entry points only.
+launch shape as an argument.  Both export their C entry points only.  _lnmod_torch.so calls liblnmod.so
+through that C interface and contains no device code.
 `python -m paper_2605_17923_amd.build` rebuilds from scratch."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -16,8 +19,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 LIBRARY = os.path.join(HERE, "liblnmod.so")
 TOOLS_LIBRARY = os.path.join(HERE, "liblnmod_tools.so")
+TORCH_MODULE = os.path.join(HERE, "_lnmod_torch.so")
 
 KERNEL_SOURCES = ["lnmod_fwd.hip", "lnmod_bwd.hip", "lnmod_gated_fwd.hip", "lnmod_gated_bwd.hip",
                   "lnmod_qknorm.hip"]
@@ -83,15 +88,50 @@ def _link(target: str, objs, force: bool) -> None:
     os.replace(tmp, target)
 
 
+def _compile_torch(force: bool) -> str:
+    """Object of the host-only extension module (needs torch's headers, not its build tools)."""
+    src, obj = os.path.join(CSRC, "lnmod_torch.cpp"), os.path.join(BUILD_DIR, "lnmod_torch.o")
+    if force or _stale(obj, [src, os.path.join(INCLUDE, "lnmod.h")]):
+        import torch
+        inc = os.path.join(os.path.dirname(torch.__file__), "include")
+        dirs = [INCLUDE, inc, os.path.join(inc, "torch", "csrc", "api", "include"), os.path.join(ROCM, "include"),
+                sysconfig.get_paths()["include"]]
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-fPIC", "-std=c++17", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+               "-DTORCH_API_INCLUDE_EXTENSION_H", "-DTORCH_EXTENSION_NAME=_lnmod_torch",
+               "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+        cmd += [f for d in dirs for f in ("-I", d)] + ["-c", src, "-o", obj]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("the C++ compiler failed for lnmod_torch.cpp:\n%s" % res.stderr[-4000:])
+    return obj
+
+
+def _link_torch(obj: str, force: bool) -> None:
+    if not (force or _stale(TORCH_MODULE, [obj])):
+        return
+    import torch
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = TORCH_MODULE + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-shared", "-o", tmp, obj, "-L" + HERE, "-l:liblnmod.so", "-Wl,-rpath,$ORIGIN",
+           "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("link failed:\n%s" % res.stderr[-4000:])
+    os.replace(tmp, TORCH_MODULE)
+
+
 def build_library(force: bool = False, verbose: bool = False) -> str:
-    """Compile every HIP source for gfx950 and link both libraries; returns liblnmod.so's path."""
+    """Compile every source, link both HIP libraries and the extension module; returns liblnmod.so's path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as pool:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:
+        torch_obj = pool.submit(_compile_torch, force)
         objs = dict(zip(SOURCES, pool.map(lambda s: _compile(s, force), SOURCES)))
+        torch_obj = torch_obj.result()
     _link(LIBRARY, [objs[s] for s in LIBRARY_SOURCES], force)
     _link(TOOLS_LIBRARY, [objs[s] for s in TOOLS_SOURCES], force)
+    _link_torch(torch_obj, force)
     if verbose:
-        print("built", LIBRARY, TOOLS_LIBRARY)
+        print("built", LIBRARY, TOOLS_LIBRARY, TORCH_MODULE)
     return LIBRARY
 
 

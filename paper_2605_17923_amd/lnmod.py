@@ -18,6 +18,7 @@ LNMOD_PER_SAMPLE, LNMOD_PER_TOKEN = 0, 1
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIBRARY = os.path.join(_HERE, "liblnmod.so")
+TORCH_MODULE = os.path.join(_HERE, "_lnmod_torch.so")
 
 LNMOD_STATIC_WORKSPACE_BYTES = 64 << 20
 
@@ -28,6 +29,7 @@ EXPORTS = ("lnmod_forward", "lnmod_backward", "lnmod_forward_varlen", "lnmod_bac
            "lnmod_gated_backward_io", "lnmod_qknorm_backward_io")
 
 _lib = None
+_native = None
 
 
 class LnmodError(RuntimeError):
@@ -87,6 +89,23 @@ def library() -> ctypes.CDLL:
     lib.lnmod_qknorm_backward_workspace_bytes.argtypes = [i64, i64]
     _lib = lib
     return lib
+
+
+def native():
+    """The host path in C++ (_lnmod_torch.so), or None while torch.compile traces (which leaves the Python
+    path, as every call does for which one of the module's functions returns None)."""
+    global _native
+    import torch
+    if torch.compiler.is_compiling():
+        return None
+    if _native is None:
+        library()
+        if not os.path.exists(TORCH_MODULE):
+            raise RuntimeError("_lnmod_torch.so is not built (run `python -m paper_2605_17923_amd.build` "
+                               "or __graft_entry__.build())")
+        from . import _lnmod_torch
+        _native = _lnmod_torch
+    return _native
 
 
 def _p(t):
@@ -331,9 +350,20 @@ def _mod_rows(x, shift_or_scale, name):
     raise ValueError("%s must be [B, D] or [B, S, D], got %s" % (name, tuple(shift_or_scale.shape)))
 
 
+def _native_forward(x, shift, scale, cu_seqlens, eps, stream):
+    """The plain case on torch's current stream, or None."""
+    if stream is not None or type(eps) is not float or not getattr(x, "is_cuda", False):
+        return None
+    host = native()
+    return None if host is None else host.forward(x, shift, scale, cu_seqlens, eps)
+
+
 def forward(x, shift, scale, eps=1e-6, stream=None):
     """x [B,S,D]; shift, scale [B,D] (per sample) or [B,S,D] (per token) -> y, mean, rstd."""
     import torch
+    r = _native_forward(x, shift, scale, None, eps, stream)
+    if r is not None:
+        return r
     code = _dtype_code(x)
     mod, mshape = _mod_rows(x, scale, "scale")
     B, S, D = x.shape
@@ -412,6 +442,9 @@ def _packed(x):
 def forward_varlen(x, shift, scale, cu_seqlens, eps=1e-6, stream=None):
     """x [T,D] packed; shift, scale [nseg,D]; cu_seqlens int32 [nseg+1] on the device."""
     import torch
+    r = None if cu_seqlens is None else _native_forward(x, shift, scale, cu_seqlens, eps, stream)
+    if r is not None:
+        return r
     code = _dtype_code(x)
     T, D = _packed(x)
     a = _Args(x)

@@ -1,0 +1,100 @@
+"""The C++ host path of the autograd functions and of the plain forward against the Python path it stands in
+for: the same outputs and gradients bit for bit, the same errors, and everything that is not the plain case
+(hooks apart, which both paths serve) handed back to the Python path."""
+import pytest
+import torch
+
+from paper_2605_17923_amd import functional as F
+from paper_2605_17923_amd import lnmod
+
+pytestmark = pytest.mark.gpu
+
+
+def _leaves(dtype, *shapes):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    return [torch.randn(*s, generator=g, device="cuda").to(dtype).requires_grad_() for s in shapes]
+
+
+def _case(op, dtype):
+    """(the native call, the Python class's call, leaves)"""
+    if op in ("sample", "token", "recompute"):
+        mod = (2, 37, 264) if op == "token" else (2, 264)
+        ts = _leaves(dtype, (2, 37, 264), mod, mod)
+        a = (None, 1e-6, op != "recompute")
+        return lambda x, sh, sc: F.ln_modulate(x, sh, sc, 1e-6, None, a[2]), lambda *t: F._LnModulate.apply(*t, *a), ts
+    cu = torch.tensor([0, 0, 30, 31, 74], dtype=torch.int32, device="cuda")
+    if op == "packed":
+        ts = _leaves(dtype, (74, 264), (4, 264), (4, 264))
+        return lambda x, sh, sc: F.ln_modulate(x, sh, sc, cu_seqlens=cu), lambda *t: F._LnModulate.apply(*t, cu, 1e-6, True), ts
+    if op in ("gated", "gated packed"):
+        c, rows, n = (cu, (74, 264), 4) if op == "gated packed" else (None, (2, 37, 264), 2)
+        ts = _leaves(dtype, rows, rows, (n, 264), (n, 264), (n, 264))
+        return lambda *t: F.gated_ln_modulate(*t, cu_seqlens=c), lambda *t: F._GatedLnModulate.apply(*t, c, 1e-6), ts
+    ts = _leaves(dtype, (3, 5, 264), (3, 5, 264), (264,), (264,))
+    return lambda *t: F.qk_norm(*t), lambda *t: F._QkNorm.apply(*t, 1e-6), ts
+
+
+def _results(call, ts, out_grads=True):
+    outs = call(*ts)
+    outs = outs if isinstance(outs, tuple) else (outs,)
+    loss = sum((o.float() * (i + 1.5)).sum() for i, o in enumerate(outs[:None if out_grads else 1]))
+    return [o.detach() for o in outs] + list(torch.autograd.grad(loss, ts, allow_unused=True)), outs
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("op", ["sample", "token", "recompute", "packed", "gated", "gated packed", "qk"])
+def test_same_results_as_the_python_path(op, dtype):
+    native, python, ts = _case(op, dtype)
+    for both in (True, False):                        # False: one of two outputs has no gradient
+        a, outs = _results(native, ts, both)
+        b, ref = _results(python, ts, both)
+        assert type(outs[0].grad_fn) is not type(ref[0].grad_fn)
+        assert len(a) == len(b)
+        for u, v in zip(a, b):
+            assert (u is None) == (v is None)
+            assert u is None or (u.dtype == v.dtype and u.shape == v.shape and torch.equal(u, v))
+    with torch.autograd.graph.save_on_cpu():          # saved tensors go through the hooks
+        c, _ = _results(native, ts)
+    for u, v in zip(c, _results(python, ts)[0]):
+        assert torch.equal(u, v)
+    with torch.no_grad():
+        out = native(*ts)
+        assert not (out[0] if isinstance(out, tuple) else out).requires_grad
+
+
+def test_plain_forward_matches_the_python_path():
+    x, sh, sc = (t.detach() for t in _leaves(torch.bfloat16, (2, 37, 264), (2, 264), (2, 264)))
+    for u, v in zip(lnmod.forward(x, sh, sc), lnmod.forward(x, sh, sc, stream=torch.cuda.current_stream())):
+        assert u.shape == v.shape and u.dtype == v.dtype and torch.equal(u, v)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        got = lnmod.forward(x, sh, sc)
+    s.synchronize()
+    assert torch.equal(got[0], lnmod.forward(x, sh, sc)[0])
+
+
+def test_errors_are_those_of_the_python_path():
+    x, sh, sc = _leaves(torch.bfloat16, (2, 8, 64), (2, 64), (2, 64))
+    for bad in ((x, sh[:1], sc), (x, sh, sc.float()), (x.transpose(0, 1), sh, sc), (x, sh, None), (x.cpu(), sh, sc)):
+        with pytest.raises((ValueError, AttributeError)):
+            F.ln_modulate(*bad)
+    wide = _leaves(torch.bfloat16, (1, 2, 12), (1, 12), (1, 12))      # not a multiple of 16 bytes
+    with pytest.raises(lnmod.LnmodError) as e:
+        F.ln_modulate(*wide)
+    assert e.value.status == lnmod.LNMOD_EUNSUPPORTED
+    y = F.ln_modulate(x, sh, sc)
+    flat = torch.zeros(2 * 8 * 64 + 1, dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(lnmod.LnmodError) as e:        # a gradient that is dense but not 16-byte aligned
+        torch.autograd.grad(y, (x,), flat[1:].view(2, 8, 64))
+    assert e.value.status == lnmod.LNMOD_EALIGN
+
+
+def test_transforms_are_refused_as_before():
+    x, sh, sc = (t.detach() for t in _leaves(torch.float32, (3, 2, 8, 64), (3, 2, 64), (3, 2, 64)))
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(F.ln_modulate)(x, sh, sc)
+    with pytest.raises(RuntimeError):
+        torch.func.grad(lambda t: F.ln_modulate(t, sh[0], sc[0]).sum())(x[0])
+    with torch.autograd.forward_ad.dual_level(), pytest.raises(RuntimeError):
+        F.ln_modulate(torch.autograd.forward_ad.make_dual(x[0], x[0]), sh[0], sc[0])
