@@ -95,6 +95,7 @@ BwdArgs make_args(const Problem& p, const void* dy, const void* x, const void* s
     a.rows_per_cluster = 0;
     a.nb = 1;
     a.interleave = 0;
+    a.split = 1;
     a.D = static_cast<int32_t>(p.D);
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.inv_D = 1.0f / static_cast<float>(p.D);
@@ -110,8 +111,8 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* p, int64_t n) {
 
 }  // namespace
 
-// Grid of the second pass: one block per (segment, sum, feature block) triple, at most
-// kReduceMaxGrid blocks; beyond that the blocks walk the triples with a stride of the grid.
+// Grid of the second pass: (sum, feature block) by segment, at most kReduceMaxGrid blocks and 65 535 of
+// them along the segments; beyond that the blocks walk the segments with a stride of the grid.
 constexpr int64_t kReduceMaxGrid = int64_t(1) << 20;
 
 hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
@@ -119,9 +120,11 @@ hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     const int V = sh.V, W = sh.W, G = sh.G;
     const int per_block = kWave / G * V;
     r.dblocks = static_cast<int32_t>((r.D + per_block - 1) / per_block);
-    r.total = r.seg.nseg * r.nsum * r.dblocks;
-    const int64_t g = r.total < kReduceMaxGrid ? r.total : kReduceMaxGrid;
-    const dim3 grid(static_cast<unsigned>(g)), block(W * kWave);
+    const int64_t gx = static_cast<int64_t>(r.nsum) * r.dblocks;
+    int64_t gy = kReduceMaxGrid / gx;
+    if (gy > 65535) gy = 65535;
+    if (gy > r.seg.nseg) gy = r.seg.nseg;
+    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), block(W * kWave);
     if (G == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 4>), grid, block, 0, st, r);
     else if (G == 2) hipLaunchKernelGGL((bwd_reduce_kernel<4, 2>), grid, block, 0, st, r);
     else if (V == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 1>), grid, block, 0, st, r);
@@ -178,6 +181,7 @@ hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
     a.interleave = cluster_interleave(p.force, pl);
+    a.split = cluster_split(a.interleave, pl);
     const bool ok = p.dtype == 0 ? dispatch_seg<bf16_io, false>(a, sh.VPL, sh.K, sh.R, pl.blocks, st)
                                  : dispatch_seg<f32_io, false>(a, sh.VPL, sh.K, sh.R, pl.blocks, st);
     if (!ok) return hipErrorInvalidConfiguration;
@@ -210,6 +214,7 @@ hipError_t launch_bwd_tok(const Problem& p, const void* dy, const void* x, const
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
+    a.split = cluster_split(0, pl);
     const bool ok = p.dtype == 0 ? dispatch_seg<bf16_io, true>(a, sh.VPL, sh.K, sh.R, pl.blocks, st)
                                  : dispatch_seg<f32_io, true>(a, sh.VPL, sh.K, sh.R, pl.blocks, st);
     return ok ? hipGetLastError() : hipErrorInvalidConfiguration;

@@ -24,6 +24,7 @@ FwdArgs make_args(const Problem& p, const void* x, const void* shift, const void
     a.rows_per_cluster = 0;
     a.nb = 1;
     a.interleave = 0;
+    a.split = 1;
     a.D = static_cast<int32_t>(p.D);
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.eps = p.eps;
@@ -173,6 +174,7 @@ hipError_t launch_mode(const Problem& p, const void* x, const void* shift, const
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
     a.interleave = cluster_interleave(p.force, pl);
+    a.split = cluster_split(a.interleave, pl);
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     const bool ok = p.dtype == 0 ? dispatch<bf16_io, MODE>(a, sh.VPL, sh.K, sh.R, pl.blocks, st)
                                  : dispatch<f32_io, MODE>(a, sh.VPL, sh.K, sh.R, pl.blocks, st);

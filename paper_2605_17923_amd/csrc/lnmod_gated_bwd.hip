@@ -138,6 +138,8 @@ hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, co
     const RowPlan pl = gated_bwd_plan(p.T, p.nseg, p.D, p.dtype);
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
+    a.interleave = cluster_interleave(nullptr, pl);
+    a.split = cluster_split(a.interleave, pl);
     const bool ok = p.dtype == 0 ? dispatch<bf16_io, 1>(a, sh, pl.blocks, st)
                                  : dispatch<f32_io, 2>(a, sh, pl.blocks, st);
     if (!ok) return hipErrorInvalidConfiguration;

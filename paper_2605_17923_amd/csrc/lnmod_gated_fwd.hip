@@ -147,6 +147,8 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
                                           pick_clusters(stream_us, p.nseg));
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
+    a.interleave = cluster_interleave(nullptr, pl);
+    a.split = cluster_split(a.interleave, pl);
     const bool ok = p.dtype == 0 ? dispatch<bf16_io, LN>(a, sh, pl.blocks, st)
                                  : dispatch<f32_io, LN>(a, sh, pl.blocks, st);
     return ok ? hipGetLastError() : hipErrorInvalidConfiguration;

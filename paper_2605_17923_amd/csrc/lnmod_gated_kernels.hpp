@@ -38,6 +38,8 @@ struct GatedFwdArgs {
     int64_t T;
     int64_t rows_per_cluster;
     int32_t nb;
+    int32_t interleave;      // 1: cluster = block index modulo the cluster count
+    int32_t split;           // see place_of
     int32_t D;
     int32_t nchunks;
     float eps;
@@ -88,8 +90,8 @@ void gated_fwd_kernel(const GatedFwdArgs a) {
     for (int w = 1; w < K; ++w) my_cnt = wave == w ? cnt[w] : my_cnt;
     const float inv_my_cnt = my_cnt > 0.0f ? 1.0f / my_cnt : 0.0f;
 
-    const int64_t cluster = blockIdx.x / a.nb;
-    const int64_t member = blockIdx.x - cluster * a.nb;
+    const Place at = place_of(a.split, a.interleave);
+    const int64_t cluster = at.cluster, member = at.member;
     int64_t r0 = cluster * a.rows_per_cluster;
     int64_t r1 = r0 + a.rows_per_cluster;
     if (r1 > a.T) r1 = a.T;
@@ -287,6 +289,8 @@ struct GatedBwdArgs {
     int64_t T;
     int64_t rows_per_cluster;
     int32_t nb;
+    int32_t interleave;      // 1: cluster = block index modulo the cluster count
+    int32_t split;           // see place_of
     int32_t D;
     int32_t nchunks;
     float inv_D;
@@ -321,8 +325,8 @@ void gated_bwd_kernel(const GatedBwdArgs a) {
         ok[i] = EXACT || chunk[i] < a.nchunks;
     }
 
-    const int64_t cluster = blockIdx.x / a.nb;
-    const int64_t member = blockIdx.x - cluster * a.nb;
+    const Place at = place_of(a.split, a.interleave);
+    const int64_t cluster = at.cluster, member = at.member;
     int64_t r0 = cluster * a.rows_per_cluster;
     int64_t r1 = r0 + a.rows_per_cluster;
     if (r1 > a.T) r1 = a.T;

@@ -205,10 +205,27 @@ __device__ inline int64_t seg_begin(const Segments& s, int64_t m) {
     return s.cu ? static_cast<int64_t>(table_at(s.cu, m)) : m * s.S;
 }
 
+// Rows, samples, blocks and steps number fewer than 2^32 (the interface admits fewer than 2^31 rows), so
+// every division in these kernels is one of 32 bits.  The 64-bit ones that used to stand here are a
+// chain of about 120 dependent instructions each, and a block went through five of them before it could
+// request its first row (bwd_seg_kernel) or slot (bwd_reduce_kernel).
+
+// Which cluster a block belongs to and its place in it.  split: the cluster count when cluster = block
+// index modulo the cluster count (interleave), else the blocks per cluster.
+struct Place {
+    int64_t cluster, member;
+};
+__device__ inline Place place_of(int32_t split, int32_t interleave) {
+    const uint32_t q = blockIdx.x / static_cast<uint32_t>(split), r = blockIdx.x - q * static_cast<uint32_t>(split);
+    return interleave ? Place{static_cast<int64_t>(r), static_cast<int64_t>(q)}
+                      : Place{static_cast<int64_t>(q), static_cast<int64_t>(r)};
+}
+
 // Largest m in [0, nseg-1] whose first token is <= row (skips empty segments in front of row).
 // Terminates and stays in range for any table contents.
 __device__ inline int64_t find_segment(const Segments& s, int64_t row) {
-    if (!s.cu) return row / s.S;
+    if (s.nseg == 1) return 0;
+    if (!s.cu) return static_cast<uint32_t>(row) / static_cast<uint32_t>(s.S);
     int64_t lo = 0, hi = s.nseg - 1;
     while (lo < hi) {
         const int64_t mid = (lo + hi + 1) >> 1;
@@ -231,7 +248,8 @@ struct FwdArgs {
     int64_t T;               // total token rows
     int64_t rows_per_cluster; // rows of the contiguous region one cluster of blocks streams through
     int32_t nb;              // blocks per cluster (per-token kernels: unused)
-    int32_t interleave;      // 1: cluster = block index modulo the cluster count (measurement only)
+    int32_t interleave;      // 1: cluster = block index modulo the cluster count
+    int32_t split;           // see place_of
     int32_t D;
     int32_t nchunks;         // D / E
     float eps;
@@ -249,7 +267,7 @@ template <int R>
 __device__ __forceinline__ int64_t take_turn(uint32_t& turn, int64_t r0, int64_t stop, int64_t member, int32_t nb) {
     const uint32_t nbu = static_cast<uint32_t>(nb), mine = static_cast<uint32_t>(member);
     const int64_t first = r0 + static_cast<int64_t>(mine >= turn ? mine - turn : mine + nbu - turn) * R;
-    turn = static_cast<uint32_t>((turn + static_cast<uint64_t>((stop - r0 + R - 1) / R) % nbu) % nbu);
+    turn = (turn + static_cast<uint32_t>(stop - r0 + R - 1) / R) % nbu;       // nb and the steps: below 2^31
     return first;
 }
 
@@ -319,13 +337,8 @@ void fwd_split_kernel(const FwdArgs a) {
     for (int w = 1; w < K; ++w) my_cnt = wave == w ? cnt[w] : my_cnt;
     const float inv_my_cnt = my_cnt > 0.0f ? 1.0f / my_cnt : 0.0f;
 
-    int64_t cluster = blockIdx.x / a.nb;
-    int64_t member = blockIdx.x - cluster * a.nb;
-    if (a.interleave) {
-        const int64_t nclusters = gridDim.x / a.nb;
-        member = blockIdx.x / nclusters;
-        cluster = blockIdx.x - member * nclusters;
-    }
+    const Place at = place_of(a.split, a.interleave);
+    const int64_t cluster = at.cluster, member = at.member;
     int64_t r0 = cluster * a.rows_per_cluster;
     int64_t r1 = r0 + a.rows_per_cluster;
     if (r1 > a.T) r1 = a.T;
@@ -557,7 +570,8 @@ struct BwdArgs {
     int64_t T;
     int64_t rows_per_cluster;
     int32_t nb;              // blocks per cluster
-    int32_t interleave;      // 1: cluster = block index modulo the cluster count (measurement only)
+    int32_t interleave;      // 1: cluster = block index modulo the cluster count
+    int32_t split;           // see place_of
     int32_t D;
     int32_t nchunks;
     float inv_D;
@@ -615,13 +629,8 @@ void bwd_seg_kernel(const BwdArgs a) {
         inv_own = own > 0 ? 1.0f / static_cast<float>(own * E) : 0.0f;
     }
 
-    int64_t cluster = blockIdx.x / a.nb;
-    int64_t member = blockIdx.x - cluster * a.nb;
-    if (a.interleave) {
-        const int64_t nclusters = gridDim.x / a.nb;
-        member = blockIdx.x / nclusters;
-        cluster = blockIdx.x - member * nclusters;
-    }
+    const Place at = place_of(a.split, a.interleave);
+    const int64_t cluster = at.cluster, member = at.member;
     int64_t r0 = cluster * a.rows_per_cluster;
     int64_t r1 = r0 + a.rows_per_cluster;
     if (r1 > a.T) r1 = a.T;
@@ -935,7 +944,6 @@ struct ReduceArgs {
     int32_t D;
     int32_t dblocks;         // ceil(D / (64 * V))
     int32_t nsum;            // 2 or 3
-    int64_t total;           // nseg * nsum * dblocks: (segment, sum, feature block) triples
 };
 
 // Stores V consecutive sums.  A caller that keeps the gradients in the tensors' own type used to
@@ -962,9 +970,8 @@ constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 
 template <int V> struct FVec { typedef float type __attribute__((ext_vector_type(V))); };
 template <> struct FVec<1> { typedef float type; };
 
-// Block b takes the triples b, b + gridDim.x, ... below a.total, each decoded as (segment, which
-// sum, block of 64 * V features); the grid is min(total, a bound), so that any segment count the
-// interface admits stays inside the launch limits.
+// blockIdx.x is (which sum, block of 64 * V features); the segments are blockIdx.y, blockIdx.y + gridDim.y,
+// ..., so that any segment count the interface admits stays inside the launch limits.
 template <int V, int G = 1>
 __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const ReduceArgs a) {
     using vec = typename FVec<V>::type;
@@ -975,17 +982,17 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
     const int wave = threadIdx.x >> 6;
     const int W = blockDim.x >> 6;
     const int fl = lane % FL, grp = lane / FL;
-    for (int64_t bid = blockIdx.x; bid < a.total; bid += gridDim.x) {
-        const int d = (static_cast<int>(bid % a.dblocks) * FL + fl) * V;
-        const int which = static_cast<int>((bid / a.dblocks) % a.nsum);
-        const int64_t m = bid / (static_cast<int64_t>(a.nsum) * a.dblocks);
+    const uint32_t which = blockIdx.x / static_cast<uint32_t>(a.dblocks);
+    const int d = (static_cast<int>(blockIdx.x - which * static_cast<uint32_t>(a.dblocks)) * FL + fl) * V;
+    for (int64_t m = blockIdx.y; m < a.seg.nseg; m += gridDim.y) {
         int64_t n0 = seg_begin(a.seg, m), n1 = seg_begin(a.seg, m + 1);
         if (n0 < 0) n0 = 0;                       // a malformed table must not lead outside ws
         if (n1 > a.T) n1 = a.T;
         vec acc = vec(0.0f);
         if (n1 > n0 && d < a.D) {
             // clusters c_lo..c_hi touch this segment; (cluster c, segment m) owns slots (c+m)*nb ..
-            const int64_t c_lo = n0 / a.rows_per_cluster, c_hi = (n1 - 1) / a.rows_per_cluster;
+            const uint32_t rpc = static_cast<uint32_t>(a.rows_per_cluster);
+            const int64_t c_lo = static_cast<uint32_t>(n0) / rpc, c_hi = static_cast<uint32_t>(n1 - 1) / rpc;
             const int64_t s_lo = (c_lo + m) * a.nb, s_hi = (c_hi + m + 1) * a.nb;
             const float* base = a.ws + static_cast<int64_t>(which) * a.D + d;
             const int64_t pitch = static_cast<int64_t>(a.nsum) * a.D;

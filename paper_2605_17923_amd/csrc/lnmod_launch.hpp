@@ -363,6 +363,11 @@ inline int cluster_interleave(const Shape* force, const RowPlan& pl) {
     return force ? force->interleave : (pl.clusters > 1 ? 1 : 0);
 }
 
+// What a block's index is divided by to find its cluster and its place in it (place_of).
+inline int32_t cluster_split(int interleave, const RowPlan& pl) {
+    return interleave ? static_cast<int32_t>(pl.clusters) : pl.nb;
+}
+
 // The backward's plan for this problem: the same function sizes the workspace, drives the main
 // kernel's grid and tells the second pass which partial-sum slots belong to a segment.
 RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, const Shape* force = nullptr);
