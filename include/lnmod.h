@@ -134,6 +134,14 @@ int lnmod_backward_io(const void* dy, const void* x, const void* scale, const in
                       void* workspace, size_t workspace_bytes, int dtype);
 
 /*
+ * lnmod_backward with LNMOD_PER_TOKEN for callers that use dy itself as dshift, which it equals bit for
+ * bit: dx and dscale are written, the copy of dy is not.
+ */
+int lnmod_backward_token(const void* dy, const void* x, const void* scale, int64_t B, int64_t S, int64_t D,
+                         float eps, void* stream, const float* mean, const float* rstd, void* dx,
+                         void* dscale, int dtype);
+
+/*
  * lnmod_backward for callers that cannot allocate device memory and have no workspace to pass:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments and results as lnmod_backward (bit for bit: the same kernels and launch plan) without

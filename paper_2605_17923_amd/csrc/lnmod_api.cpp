@@ -199,6 +199,15 @@ int lnmod_backward_io(const void* dy, const void* x, const void* scale, const in
                          false, /*io_grads=*/true);
 }
 
+int lnmod_backward_token(const void* dy, const void* x, const void* scale, int64_t B, int64_t S, int64_t D,
+                         float eps, void* stream, const float* mean, const float* rstd, void* dx,
+                         void* dscale, int dtype) {
+    const int64_t T = total_tokens(B, S);
+    if (T < 0) return LNMOD_EINVAL;
+    return backward_impl(dy, x, scale, nullptr, false, B, S, T, D, eps, stream, mean, rstd, dx, nullptr, dscale,
+                         nullptr, 0, dtype, LNMOD_PER_TOKEN, nullptr, false, false, /*no_dshift=*/true);
+}
+
 size_t lnmod_backward_workspace_bytes(int64_t B_or_nseg, int64_t total, int64_t D, int mod) {
     if (mod != LNMOD_PER_SAMPLE) return 0;
     if (B_or_nseg < 0 || total < 0 || total >= (int64_t(1) << 31)) return 0;

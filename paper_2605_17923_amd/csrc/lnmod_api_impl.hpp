@@ -72,7 +72,8 @@ inline int backward_impl(const void* dy, const void* x, const void* scale, const
                          int64_t nseg, int64_t S, int64_t T, int64_t D, float eps, void* stream,
                          const float* mean, const float* rstd, void* dx, void* dshift, void* dscale,
                          void* workspace, size_t workspace_size, int dtype, int mod,
-                         const Shape* force = nullptr, bool exact_workspace = false, bool io_grads = false) {
+                         const Shape* force = nullptr, bool exact_workspace = false, bool io_grads = false,
+                         bool no_dshift = false) {
     if (mod != LNMOD_PER_SAMPLE && mod != LNMOD_PER_TOKEN) return LNMOD_EINVAL;
     const int st = check_shape(nseg, varlen ? T : S, D, eps, dtype, T);
     if (st != LNMOD_OK) return st;
@@ -89,7 +90,7 @@ inline int backward_impl(const void* dy, const void* x, const void* scale, const
         return LNMOD_OK;
     }
     if (nseg == 0) return LNMOD_EINVAL;
-    if (!dy || !x || !scale || !dx || !dshift || !dscale || (varlen && !cu)) return LNMOD_EINVAL;
+    if (!dy || !x || !scale || !dx || (!dshift && !no_dshift) || !dscale || (varlen && !cu)) return LNMOD_EINVAL;
     if ((mean == nullptr) != (rstd == nullptr)) return LNMOD_EINVAL;    // both, or neither (recompute)
     if (!aligned16(dy) || !aligned16(x) || !aligned16(scale) || !aligned16(dx) ||
         !aligned16(dshift) || !aligned16(dscale))

@@ -563,7 +563,7 @@ struct BwdArgs {
     const float* mean;
     const float* rstd;
     void* dx;
-    void* dshift;            // per-token mode only (I/O dtype)
+    void* dshift;            // per-token mode only (I/O dtype); may be null there
     void* dscale;            // per-token mode only
     float* ws;               // [nslots][2][D] fp32 partial sums
     Segments seg;
@@ -885,8 +885,9 @@ void bwd_seg_kernel(const BwdArgs a) {
                             const uint32_t lo = static_cast<uint32_t>(chunk[i]) * 16u;
                             store16_u(a.dx, row * row_bytes, lo, io::pack(o));
                             if (TOK) {
-                                // per token: dshift = dy (the packed registers as loaded), dscale = dy * xhat
-                                store16_u(a.dshift, row * row_bytes, lo, raw[0][j][i]);
+                                // per token: dshift = dy (the packed registers as loaded; not written for a
+                                // caller that uses dy itself), dscale = dy * xhat
+                                if (a.dshift != nullptr) store16_u(a.dshift, row * row_bytes, lo, raw[0][j][i]);
                                 store16_u(a.dscale, row * row_bytes, lo, io::pack(ds));
                             }
                         }

@@ -351,6 +351,37 @@ inline Shape tok_bwd_shape(int nchunks, int dtype) {
     return table_entry(tab32, nchunks, dtype);
 }
 
+// The per-token backward without the copy of dy (five streams): what is best for six is 2 to 14 % behind,
+// because with one write less fewer, wider waves keep up.  Timed at every multiple of 512 features on 400 MB
+// and 48 MB tensors (six-stream entry -> this one, 400 MB bf16: D = 1024 354 -> 333 us, 1536 341 -> 322, 2048
+// 378 -> 334, 2560 365 -> 324, 4096 362 -> 334, 5120 345 -> 335, 5632 372 -> 346, 6144 362 -> 337; fp32: D = 512
+// 346 -> 330, 2560 356 -> 339, 3072 361 -> 338, 3584 355 -> 339, 5120 358 -> 346).  Up to 32 Mi elements bf16 rows go
+// one per step, rows wider than 6144 with two blocks per CU (48 MB tensors: D = 6656 52 -> 44 us; above, at
+// 400 MB, the two-row shape takes 359 against 373).
+inline Shape tok_bwd_noshift_shape(int nchunks, int dtype, int64_t T) {
+    if (dtype == 0) {
+        static const Shape tab[17] = {
+            {1, 1, 1, 8},
+            {1, 1, 1, 8}, {1, 2, 1, 4}, {3, 1, 2, 2}, {4, 1, 1, 2},
+            {6, 1, 1, 2}, {8, 1, 1, 2}, {4, 2, 2, 2}, {4, 2, 2, 2},
+            {6, 2, 1, 2}, {8, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 1, 1}};
+        Shape sh = table_entry(tab, nchunks, dtype);
+        if (T * nchunks * 8 <= (int64_t(32) << 20)) {
+            if (nchunks > 768) return {8, 2, 1, 2};
+            if (sh.R == 2) sh.R = 1;
+            if (sh.K == 3) sh.per_cu = 4;              // D = 1536: 48 MB 45.5 -> 41.4 us
+        }
+        return sh;
+    }
+    Shape sh = tok_bwd_shape(nchunks, dtype);
+    const int cols = (nchunks + 127) / 128;
+    if (cols == 1 && nchunks > 64) sh = {1, 4, 1, 4};
+    if (cols >= 5 && cols <= 7) sh = {4, 4, 1, 2};
+    if (cols == 9 || cols == 10) sh = {6, 4, 1, 1};
+    return sh;
+}
+
 // Which blocks form a cluster.  Consecutive blocks go to the eight XCDs in turn, so with
 // cluster = block index modulo the cluster count (and a count that is a multiple of 8) all blocks
 // of a cluster sit on one XCD and that XCD streams through one contiguous region; clusters of

@@ -26,7 +26,7 @@ EXPORTS = ("lnmod_forward", "lnmod_backward", "lnmod_forward_varlen", "lnmod_bac
            "lnmod_backward_static", "lnmod_backward_workspace_bytes", "lnmod_status_string", "lnmod_gated_forward",
            "lnmod_gated_backward", "lnmod_gated_backward_workspace_bytes", "lnmod_qknorm_forward",
            "lnmod_qknorm_backward", "lnmod_qknorm_backward_workspace_bytes", "lnmod_backward_io",
-           "lnmod_gated_backward_io", "lnmod_qknorm_backward_io")
+           "lnmod_gated_backward_io", "lnmod_qknorm_backward_io", "lnmod_backward_token")
 
 _lib = None
 _native = None
@@ -81,6 +81,8 @@ def library() -> ctypes.CDLL:
                                           vp, vp, vp, vp, vp, sz, cint]
     lib.lnmod_backward_io.restype = cint
     lib.lnmod_backward_io.argtypes = [vp, vp, vp, vp, i64, i64, i64, f32, vp, vp, vp, vp, vp, vp, vp, sz, cint]
+    lib.lnmod_backward_token.restype = cint
+    lib.lnmod_backward_token.argtypes = [vp, vp, vp, i64, i64, i64, f32, vp, vp, vp, vp, vp, cint]
     lib.lnmod_gated_backward_io.restype = cint
     lib.lnmod_gated_backward_io.argtypes = lib.lnmod_gated_backward.argtypes
     lib.lnmod_qknorm_backward_io.restype = cint
@@ -164,6 +166,11 @@ def lnmod_backward_io(dy, x, scale, cu_seqlens, B_or_nseg, S_or_T, D, eps, strea
     return library().lnmod_backward_io(_p(dy), _p(x), _p(scale), _p(cu_seqlens), B_or_nseg, S_or_T, D,
                                        eps, stream, _p(mean), _p(rstd), _p(dx), _p(dshift), _p(dscale),
                                        _p(workspace), workspace_bytes, dtype)
+
+
+def lnmod_backward_token(dy, x, scale, B, S, D, eps, stream, mean, rstd, dx, dscale, dtype):
+    return library().lnmod_backward_token(_p(dy), _p(x), _p(scale), B, S, D, eps, stream, _p(mean),
+                                          _p(rstd), _p(dx), _p(dscale), dtype)
 
 
 def lnmod_backward_workspace_bytes(B_or_nseg, total_tokens, D, mod):

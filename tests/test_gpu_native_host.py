@@ -98,3 +98,27 @@ def test_transforms_are_refused_as_before():
         torch.func.grad(lambda t: F.ln_modulate(t, sh[0], sc[0]).sum())(x[0])
     with torch.autograd.forward_ad.dual_level(), pytest.raises(RuntimeError):
         F.ln_modulate(torch.autograd.forward_ad.make_dual(x[0], x[0]), sh[0], sc[0])
+
+
+@pytest.mark.parametrize("stats", [True, False])
+def test_per_token_shift_gradient_is_handed_on_without_sharing(stats):
+    """dshift is dy; a leaf's .grad must not share memory with a gradient that others still hold."""
+    x, sh, sc = _leaves(torch.bfloat16, (2, 37, 264), (2, 37, 264), (2, 37, 264))
+    y = F.ln_modulate(x, sh, sc, save_stats=stats)
+    y.retain_grad()
+    other = torch.zeros_like(y).requires_grad_()
+    dy = torch.randn_like(y)
+    keep = dy.clone()
+    (y + other).backward(dy)
+    assert torch.equal(sh.grad, keep)
+    sh.grad.mul_(2)
+    for t in (dy, y.grad, other.grad):
+        assert torch.equal(t, keep)
+    # a recorded backward keeps its copy: no half-connected second derivative
+    y = F.ln_modulate(x, sh, sc, save_stats=stats)
+    g = torch.randn_like(y).requires_grad_()
+    for t in torch.autograd.grad(y, (x, sh, sc), g, create_graph=True):
+        assert not t.requires_grad
+    # an expanded gradient
+    (got,) = torch.autograd.grad(F.ln_modulate(x, sh, sc, save_stats=stats).sum(), (sh,))
+    assert torch.equal(got, torch.ones_like(sh)) and got.is_contiguous()
