@@ -144,12 +144,13 @@ int lnmod_backward_token(const void* dy, const void* x, const void* scale, int64
 /*
  * lnmod_backward for callers that cannot allocate device memory and have no workspace to pass:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments and results as lnmod_backward (bit for bit: the same kernels and launch plan) without
- * `workspace` / `workspace_bytes`: the per-block partial sums go to a static device array of
+ * arguments and results as lnmod_backward (bit for bit: the same kernels and launch plan, as long as
+ * that plan's partial sums fit; else a plan of fewer blocks per sample, whose dshift and dscale are
+ * added in another order) without `workspace` / `workspace_bytes`: the per-block partial sums go to a static device array of
  * LNMOD_STATIC_WORKSPACE_BYTES inside the library (one per GPU, held from the time the library's
  * code is loaded on that GPU until the process ends).  The call allocates nothing, frees nothing
- * and never synchronises.  A LNMOD_PER_SAMPLE problem whose partial sums need more than that
- * (about 1600 slots of 2*D floats at D = 5120) is refused with LNMOD_EWORKSPACE before anything is
+ * and never synchronises.  A LNMOD_PER_SAMPLE problem whose partial sums need more than that in
+ * every plan (about 1600 slots of 2*D floats at D = 5120) is refused with LNMOD_EWORKSPACE before anything is
  * enqueued; LNMOD_PER_TOKEN needs no workspace and is never refused for it.  Every call on a GPU
  * uses that GPU's one array: calls that may overlap in time on the same GPU (different streams,
  * different host threads) race on it and must be serialised by the caller; calls on one stream

@@ -167,13 +167,15 @@ int lnmod_backward_static(const void* dy, const void* x, const void* shift, cons
     if (st != LNMOD_OK) return st;
     void* ws = nullptr;
     size_t ws_bytes = 0;
+    lnmod::Shape shape{};
+    const lnmod::Shape* force = nullptr;
     if (mod == LNMOD_PER_SAMPLE && T > 0 && B > 0) {
         // the slots of exactly this call's plan (element type and whether the statistics are
         // recomputed are known here), not the query's upper bound over all plans
         if ((mean == nullptr) != (rstd == nullptr)) return LNMOD_EINVAL;
-        const lnmod::RowPlan pl = lnmod::bwd_plan(T, B, D, dtype, mean == nullptr);
-        const size_t need = static_cast<size_t>(lnmod::bwd_slots(pl, B)) * 2u * static_cast<size_t>(D) * sizeof(float);
-        if (need > lnmod::kStaticWorkspaceBytes) return LNMOD_EWORKSPACE;
+        const int64_t max_slots = static_cast<int64_t>(lnmod::kStaticWorkspaceBytes / (2u * static_cast<size_t>(D) * sizeof(float)));
+        if (!lnmod::bwd_shape_within(T, B, D, dtype, mean == nullptr, max_slots, &shape)) return LNMOD_EWORKSPACE;
+        if (shape.clusters > 0) force = &shape;      // not the plan lnmod_backward takes: fewer slots
         // every other argument is checked before the first HIP call
         if (!dy || !x || !scale || !dx || !dshift || !dscale) return LNMOD_EINVAL;
         if (!aligned16(dy) || !aligned16(x) || !aligned16(scale) || !aligned16(dx) ||
@@ -185,7 +187,7 @@ int lnmod_backward_static(const void* dy, const void* x, const void* shift, cons
         ws_bytes = lnmod::kStaticWorkspaceBytes;
     }
     return backward_impl(dy, x, scale, nullptr, false, B, S, T, D, eps, stream, mean, rstd, dx,
-                         dshift, dscale, ws, ws_bytes, dtype, mod, nullptr, /*exact_workspace=*/true);
+                         dshift, dscale, ws, ws_bytes, dtype, mod, force, /*exact_workspace=*/true);
 }
 
 int lnmod_backward_io(const void* dy, const void* x, const void* scale, const int32_t* cu_seqlens,

@@ -68,6 +68,7 @@ bool dispatch_seg(const BwdArgs& a, int VPL, int K, int R, int64_t blocks, hipSt
             case 106: go_seg<Tag, 1, 6, TOK>(a, R, blocks, st); return true;
             case 304: go_seg<Tag, 3, 4, TOK>(a, R, blocks, st); return true;
             case 306: go_seg<Tag, 3, 6, TOK>(a, R, blocks, st); return true;
+            case 108: go_seg<Tag, 1, 8, TOK>(a, R, blocks, st); return true;
             default: break;
         }
     }
@@ -159,13 +160,13 @@ BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool per_token
     const int E = dtype == 0 ? 8 : 4;
     L.nchunks = static_cast<int>(D / E);
     if (per_token) {
-        // (the recompute form keeps the table's shapes either way: 98 against 109 us on 32 760 x 1536)
-        L.sh = pick_shape(force, writes_dshift || recompute ? tok_bwd_shape(L.nchunks, dtype)
-                                                            : tok_bwd_noshift_shape(L.nchunks, dtype, T));
+        // (the recompute form keeps shapes of its own: 32 760 x 1536 98 us, 109 with the others)
+        L.sh = pick_shape(force, recompute ? tok_rc_bwd_shape(L.nchunks, dtype)
+                                           : tok_bwd_shape(L.nchunks, dtype, writes_dshift, T));
         L.pl = plan_rows(T, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R);
         return L;
     }
-    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype) : bwd_shape(L.nchunks, dtype));
+    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T) : bwd_shape(L.nchunks, dtype, T));
     // a row moves 3 D elements (dy, x, dx), a slot 2 D floats that are written and read back
     const double elem = dtype == 0 ? 2.0 : 4.0;
     const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 3.0 * elem / 5.8e6;
@@ -178,6 +179,26 @@ BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool per_token
 
 RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, const Shape* force) {
     return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
+}
+
+bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots, Shape* out) {
+    const BwdLaunch own = plan_bwd(T, nseg, D, dtype, false, recompute, nullptr);
+    *out = own.sh;
+    if (bwd_slots(own.pl, nseg) <= max_slots) return true;
+    for (int per_cu = own.sh.per_cu; per_cu >= 1; --per_cu) {
+        Shape sh = own.sh;
+        sh.per_cu = per_cu;
+        const int64_t g = grid_blocks(T, static_cast<int64_t>(kNumCU) * per_cu, sh.R);
+        for (int64_t nb = own.pl.nb < g ? own.pl.nb : g; nb >= 1; nb /= 2) {
+            sh.clusters = static_cast<int>(g / nb);
+            sh.interleave = 1;
+            if (bwd_slots(plan_bwd(T, nseg, D, dtype, false, recompute, &sh).pl, nseg) <= max_slots) {
+                *out = sh;
+                return true;
+            }
+        }
+    }
+    return false;
 }
 
 hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const void* scale,

@@ -79,6 +79,11 @@ bool dispatch(const FwdArgs& a, int VPL, int K, int R, int64_t blocks, hipStream
                 case 302: go<Tag, 3, 2, MODE>(a, R, blocks, st); return true;
                 case 304: go<Tag, 3, 4, MODE>(a, R, blocks, st); return true;
                 case 306: go<Tag, 3, 6, MODE>(a, R, blocks, st); return true;
+                case 208: go<Tag, 2, 8, MODE>(a, R, blocks, st); return true;
+                case 305:                                    // compiled for one row per step only
+                    if (R != 1) return false;
+                    go_r<Tag, 3, 5, 1, MODE>(a, blocks, st);
+                    return true;
                 default: break;
             }
         }
@@ -98,27 +103,38 @@ bool dispatch(const FwdArgs& a, int VPL, int K, int R, int64_t blocks, hipStream
     return false;                                        // no such instantiation
 }
 
+// Segments of at most 1024 rows in the mean: most steps of a block of a flat launch then change segment.
+bool many_short(const Problem& p) { return p.nseg > 1 && p.T <= 1024 * p.nseg; }
+
 // Whether a forward with one modulation row per sample / segment runs one loop over all rows of a
 // block's region (kModFlat) or one loop per segment (kModSegment).  With several segments the flat
 // loop wins wherever few blocks share a CU, because a block that drains its pipeline at a segment's
-// end leaves the CU idle: bf16 rows shared by three or more waves (D >= 2560) and D = 1536 gained 1
-// to 11 % on 8 to 480 segments (D = 5120, 24 mixed segments: 514 against 530 us; 3 x 75 600 rows: 766
-// against 819; D = 1536, 24 mixed: 159 against 178, 480 x 312: 170 against 244); D = 1024 and 2048
-// lost 2 to 9 % on 96 segments and fp32 was mixed, so those keep the loop per segment.
-bool fwd_flat(const Problem& p, const Shape& table) {
+// end leaves the CU idle: bf16 rows of D > 2560 and D = 1536 gained 1 to 11 % on 8 to 480 segments
+// (D = 5120, 24 mixed segments: 514 against 530 us; 3 x 75 600 rows: 766 against 819; D = 1536, 24 mixed:
+// 159 against 178).  At the other widths it wins on short launches (the blocks of the short tables: 64
+// segments of 64 rows at D = 2048 13.0 -> 10.3 us, 8 x 2048 rows 27.0 -> 25.8) and on segments of 1024
+// rows and less (96 segments, 52 000 rows at D = 1024 51 -> 43, 2560 109 -> 104), except at D = 1544 ... 2048
+// (200 segments 147.5 us with the loop per segment, 148.8 flat); on longer segments it lost 2 to 9 %, and
+// fp32 was mixed, so those keep the loop per segment.
+bool fwd_flat(const Problem& p) {
     if (p.force && p.force->flat != 0) return p.force->flat == 1;
     if (p.nseg <= 1 || p.dtype != 0) return false;
-    return table.K >= 3 || p.D == 1536;
+    const int nchunks = static_cast<int>(p.D / 8);
+    return nchunks > 320 || p.D == 1536 || short_launch(p.T, nchunks) ||
+           (many_short(p) && (nchunks <= 192 || nchunks > 256));
 }
 
 // Clusters of a flat launch: every block reloads its modulation registers once per segment of its
 // cluster's region (about 0.3 us each, the next rows being already in flight), and every further
-// window costs bandwidth, so the count is the smallest power of two that leaves a block at most 32
-// segments, between 2 and 32 (D = 5120: 2, 4, 8 clusters best on 24, 96, 480 segments; D = 1536:
-// 2, 4, 16).
-int64_t flat_clusters(int64_t nseg) {
+// window costs bandwidth, so the count is the smallest power of two, between 2 and 32, that leaves a
+// block at most 32 segments (D = 5120: 2, 4, 8 clusters best on 24, 96, 480 segments of 150 000 rows), or
+// at most 8 where three or more blocks share a CU and either the launch is short or most steps change segment
+// (96 segments, 52 000 rows: D = 1536 67.5 -> 61.8 us together with the blocks of the short table, 3072
+// 129 -> 123; 200 segments of 490 rows at D = 3072 233 -> 226).
+int64_t flat_clusters(const Problem& p, int per_cu) {
+    const bool few = per_cu > 2 && (many_short(p) || short_launch(p.T, static_cast<int>(p.D / (p.dtype == 0 ? 8 : 4))));
     int64_t c = 2;
-    while (c < 32 && nseg > 32 * c) c *= 2;
+    while (c < 32 && p.nseg > (few ? 8 : 32) * c) c *= 2;
     return c;
 }
 
@@ -139,7 +155,10 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
         Shape tab = fwd_shape(L.nchunks, p.dtype, p.T);
         // D = 1536, flat: four blocks per CU at every token count (24 mixed segments, 152 880 rows:
         // 159 us against 182 with three)
-        if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0) tab.per_cu = 4;
+        if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0 && !short_launch(p.T, L.nchunks)) tab.per_cu = 4;
+        // rows of one wave whose segments change at most steps: the reload of one block hides behind the
+        // others of the CU, so as many as a short launch has (200 segments of 490 rows at D = 1536 117.3 -> 115.5)
+        if (mode == kModFlat && L.nchunks <= 192 && many_short(p)) tab = fwd_shape(L.nchunks, p.dtype, 1);
         sh = pick_shape(p.force, tab);
     }
     if ((mode == kLnOnly || mode == kModOnly) && p.dtype == 0) {
@@ -155,7 +174,7 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
     L.sh = sh;
     if (mode == kModFlat)
         L.pl = plan_rows_clusters(p.T, p.nseg, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R,
-                                  flat_clusters(p.nseg), sh.clusters);
+                                  flat_clusters(p, sh.per_cu), sh.clusters);
     else
         L.pl = plan_rows_clusters(p.T, per_segment ? p.nseg : 1, static_cast<int64_t>(kNumCU) * sh.per_cu,
                                   sh.R, per_segment ? pick_clusters(stream_us, p.nseg) : 1,
@@ -185,7 +204,7 @@ hipError_t launch_mode(const Problem& p, const void* x, const void* shift, const
 
 hipError_t launch_fwd_seg(const Problem& p, const void* x, const void* shift, const void* scale,
                           void* y, float* mean, float* rstd, hipStream_t st) {
-    if (fwd_flat(p, fwd_shape(static_cast<int>(p.D / (p.dtype == 0 ? 8 : 4)), p.dtype, p.T)))
+    if (fwd_flat(p))
         return launch_mode<kModFlat>(p, x, shift, scale, y, mean, rstd, st);
     return launch_mode<kModSegment>(p, x, shift, scale, y, mean, rstd, st);
 }
@@ -206,8 +225,7 @@ hipError_t launch_unfused(const Problem& p, const void* x, const void* shift, co
 // Text that names the kernel instantiation and grid a forward call with these arguments launches
 // (template arguments in the order of fwd_split_kernel's parameter list).
 int describe_fwd(const Problem& p, bool per_token, char* buf, size_t n) {
-    const Shape tab = fwd_shape(static_cast<int>(p.D / (p.dtype == 0 ? 8 : 4)), p.dtype, p.T);
-    const int mode = per_token ? kModToken : fwd_flat(p, tab) ? kModFlat : kModSegment;
+    const int mode = per_token ? kModToken : fwd_flat(p) ? kModFlat : kModSegment;
     const FwdLaunch L = plan_fwd(p, mode);
     const bool exact = L.nchunks == L.sh.K * L.sh.VPL * kWave;
     return std::snprintf(buf, n, "fwd_split_kernel<%s, %d, %d, %d, %s, %d, true> grid=%lld block=%d clusters=%lld",

@@ -12,42 +12,35 @@ namespace {
 // running sums) and four packed input streams prefetched one step ahead, that is what fits
 // without spilling.  bf16 rows of 9 to 16 times 512 features take two chunks per lane on 6 or 8
 // waves instead (whole multiples of the four SIMDs; D = 5120: 798 against 819 us, and sixteen
-// waves would halve the registers a wave may use).  One block per CU once a row needs three
-// waves; two rows per step for rows up to 8 KB.  Timed like the other tables (D = 1536 ... 8192).
-constexpr int kWaveCounts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-
-Shape gated_bwd_shape(int nchunks, int dtype, int64_t row_bytes) {
-    const int vpl = dtype == 0 ? 1 : 2;
-    const int need = (nchunks + kWave * vpl - 1) / (kWave * vpl);
-    int K = 16;
-    for (int k : kWaveCounts)
-        if (k >= need) {
-            K = k;
-            break;
-        }
-    int per_cu = 6 / K;
-    if (per_cu < 1 || K >= 3) per_cu = 1;
-    Shape sh{K, vpl, row_bytes <= 8192 ? 2 : 1, per_cu};
+// waves would halve the registers a wave may use).  The shapes are a table per 256 features from a sweep of
+// every compiled shape on 32 and 200 MB tensors (fp32: 150 MB); against the rule with overrides per 512
+// features that stood here they take 0.97 of the time in the mean over 32 widths (200 MB bf16: D = 256 341 ->
+// 221 us, 768 267 -> 211, 1280 233 -> 207, 1792 244 -> 222; fp32 D = 1280 186 -> 154, 2304 178 -> 160).
+Shape gated_bwd_shape(int nchunks, int dtype) {
     if (dtype == 0) {
-        const int cols = (nchunks + kWave - 1) / kWave;
-        if (cols == 1) sh = {1, 1, 2, 3};                // D = 512: 800 against 880 us for six blocks per CU
-        if (cols == 2) sh = {2, 1, 1, 2};                // D = 1024: 809 against 856 us
-        if (cols == 4) sh.R = 1;                         // D = 2048: 5.97 against 5.6 TB/s
-        if (cols == 5) sh = {5, 1, 1, 1};                // D = 2560: 773 against 801 us for two rows
-        if (cols == 6) sh = {8, 1, 1, 1};                // D = 3072: 768 against 805 us for six waves
-        if (cols >= 9 && cols <= 10) sh = {8, 2, 1, 1};
-        if (cols >= 11 && cols <= 12) sh = {6, 2, 1, 1};
-        if (cols >= 13) sh = {8, 2, 1, 1};
+        static const Shape tab[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 1, 2, 3}, {2, 1, 2, 3}, {2, 1, 1, 2},   // D <= 1024
+            {4, 1, 2, 2}, {3, 1, 2, 1}, {4, 1, 2, 1}, {4, 1, 1, 1},   // D <= 2048
+            {6, 1, 2, 1}, {5, 1, 1, 1}, {8, 1, 1, 1}, {8, 1, 1, 1},   // D <= 3072
+            {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 2, 1},   // D <= 4096
+            {10, 1, 1, 1}, {8, 2, 1, 1}, {10, 1, 1, 1}, {8, 2, 1, 1},   // D <= 5120
+            {6, 2, 1, 1}, {6, 2, 1, 1}, {6, 2, 1, 1}, {12, 1, 1, 1},   // D <= 6144
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 7168
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {16, 1, 1, 1}};   // D <= 8192
+        return fine_entry(tab, nchunks, dtype);
     }
-    if (dtype == 1) {
-        // fp32, per 512 features: D = 512: 774 against 880 us, D = 1024: 783 against 863 us,
-        // D = 3584: 819 against 857 us
-        const int cols = (nchunks + 127) / 128;
-        if (cols == 1) sh = {1, 2, 1, 3};
-        if (cols == 2) sh = {3, 2, 1, 2};
-        if (cols == 7) sh = {8, 2, 2, 1};
-    }
-    return sh;
+    static const Shape tab32[33] = {
+        {1, 2, 1, 6},
+        {1, 2, 1, 6}, {1, 2, 1, 3}, {3, 2, 1, 2}, {3, 2, 1, 2},   // D <= 1024
+        {3, 2, 1, 2}, {4, 2, 1, 2}, {4, 2, 2, 2}, {4, 2, 2, 2},   // D <= 2048
+        {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 1, 1},   // D <= 3072
+        {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 4096
+        {10, 2, 1, 1}, {10, 2, 1, 1}, {10, 2, 1, 1}, {10, 2, 1, 1},   // D <= 5120
+        {12, 2, 1, 1}, {12, 2, 1, 1}, {12, 2, 1, 1}, {12, 2, 1, 1},   // D <= 6144
+        {16, 2, 1, 1}, {16, 2, 1, 1}, {16, 2, 1, 1}, {16, 2, 1, 1},   // D <= 7168
+        {16, 2, 1, 1}, {16, 2, 1, 1}, {16, 2, 1, 1}, {16, 2, 1, 1}};   // D <= 8192
+    return fine_entry(tab32, nchunks, dtype);
 }
 
 template <typename Tag, int VPL, int K, int R>
@@ -98,12 +91,12 @@ bool dispatch(const GatedBwdArgs& a, Shape sh, int64_t blocks, hipStream_t st) {
 }  // namespace
 
 Shape gated_bwd_table_shape(int nchunks, int dtype) {
-    return gated_bwd_shape(nchunks, dtype, static_cast<int64_t>(nchunks) * 16);
+    return gated_bwd_shape(nchunks, dtype);
 }
 
 RowPlan gated_bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype) {
     const int E = dtype == 0 ? 8 : 4;
-    const Shape sh = gated_bwd_shape(static_cast<int>(D / E), dtype, D * (dtype == 0 ? 2 : 4));
+    const Shape sh = gated_bwd_shape(static_cast<int>(D / E), dtype);
     // a row moves 6 D elements (dy, dh, h, u, dx, du), a slot 3 D floats written and read back
     const double elem = dtype == 0 ? 2.0 : 4.0;
     const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 6.0 * elem / 5.8e6;
@@ -133,7 +126,7 @@ hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, co
     a.D = static_cast<int32_t>(p.D);
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.inv_D = 1.0f / static_cast<float>(p.D);
-    const Shape sh = gated_bwd_shape(a.nchunks, p.dtype, p.D * (p.dtype == 0 ? 2 : 4));
+    const Shape sh = gated_bwd_shape(a.nchunks, p.dtype);
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     const RowPlan pl = gated_bwd_plan(p.T, p.nseg, p.D, p.dtype);
     a.rows_per_cluster = pl.rows_per_cluster;

@@ -6,10 +6,8 @@
 namespace lnmod {
 namespace {
 
-// Launch shape (see Shape in lnmod_launch.hpp).  The rule: the split of choose_split, two rows per
-// step, about five waves per CU.  The widths where a sweep of every compiled shape (multiples of
-// 512 features, 774 MB per tensor, both element types) beat the rule override it; the winners
-// again are multiples of the four SIMDs of a CU or one block of five waves.
+// Launch shape (see Shape in lnmod_launch.hpp) of the residual-only kernel at the widths below has this
+// rule: the split of choose_split, two rows per step, about five waves per CU.
 int blocks_per_cu(int K) {
     if (K == 1) return 4;
     if (K == 3) return 2;              // three waves alone leave a CU short
@@ -17,43 +15,53 @@ int blocks_per_cu(int K) {
     return b < 1 ? 1 : b;
 }
 
-Shape gated_fwd_shape(int nchunks, int dtype, bool ln) {
+// (K, VPL, R, blocks per CU) of the fused kernel: a table per 256 features, from a sweep of every compiled
+// shape on 200 MB tensors (fp32: 150 MB), and one for short launches (see short_launch) from 32 MB ones.
+// Against the rule with overrides per 512 features that stood here: bf16 0.96 of the time in the mean over 32
+// widths, short launches 0.94, fp32 0.95 (D = 768 167 -> 136 us, 1280 150 -> 136, 5888 145 -> 138; 32 MB: D =
+// 768 31.5 -> 25.5, 4352 28.6 -> 25.3; fp32 D = 1280 113 -> 102, with one row per step as in bf16).
+Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
+    if (ln && dtype == 0) {
+        static const Shape tab[33] = {
+            {1, 1, 1, 16},
+            {1, 1, 1, 16}, {1, 1, 2, 4}, {1, 2, 1, 6}, {2, 2, 1, 4},   // D <= 1024
+            {2, 2, 1, 4}, {2, 2, 1, 3}, {2, 2, 1, 3}, {2, 2, 1, 3},   // D <= 2048
+            {3, 2, 1, 2}, {3, 2, 1, 2}, {3, 2, 1, 2}, {3, 2, 1, 2},   // D <= 3072
+            {4, 2, 2, 1}, {4, 2, 2, 1}, {5, 2, 1, 1}, {4, 3, 1, 1},   // D <= 4096
+            {4, 3, 1, 1}, {6, 2, 1, 1}, {4, 3, 1, 1}, {4, 3, 1, 1},   // D <= 5120
+            {4, 3, 1, 1}, {4, 3, 1, 1}, {6, 2, 2, 1}, {8, 2, 2, 1},   // D <= 6144
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 2}};   // D <= 8192
+        static const Shape tab_short[33] = {
+            {1, 1, 2, 16},
+            {1, 1, 2, 16}, {1, 1, 1, 8}, {1, 2, 1, 6}, {1, 2, 2, 12},   // D <= 1024
+            {2, 2, 1, 8}, {1, 3, 1, 8}, {2, 2, 1, 6}, {2, 2, 1, 4},   // D <= 2048
+            {3, 2, 1, 4}, {3, 2, 1, 2}, {4, 2, 1, 3}, {4, 2, 1, 3},   // D <= 3072
+            {4, 2, 1, 2}, {4, 2, 2, 2}, {4, 2, 1, 2}, {5, 2, 1, 2},   // D <= 4096
+            {4, 3, 1, 2}, {4, 3, 2, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 5120
+            {4, 3, 1, 1}, {4, 3, 1, 4}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
+            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 1, 1},   // D <= 7168
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 2}};   // D <= 8192
+        return short_launch(T, nchunks) ? fine_entry(tab_short, nchunks, dtype) : fine_entry(tab, nchunks, dtype);
+    }
+    if (ln) {
+        static const Shape tab32[33] = {
+            {1, 1, 1, 8},
+            {1, 1, 1, 8}, {1, 2, 2, 4}, {1, 3, 2, 4}, {1, 4, 1, 4},   // D <= 1024
+            {2, 4, 1, 3}, {2, 4, 1, 2}, {2, 4, 1, 3}, {2, 4, 1, 3},   // D <= 2048
+            {3, 4, 1, 2}, {3, 4, 2, 2}, {4, 4, 1, 2}, {3, 4, 1, 2},   // D <= 3072
+            {5, 4, 1, 1}, {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},   // D <= 4096
+            {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 2}, {5, 4, 1, 1},   // D <= 5120
+            {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 6144
+            {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 2}, {8, 4, 1, 2},   // D <= 7168
+            {8, 4, 1, 1}, {8, 4, 1, 2}, {8, 4, 1, 2}, {8, 4, 1, 2}};   // D <= 8192
+        Shape sh = fine_entry(tab32, nchunks, dtype);
+        // few rows for each of 256 blocks: two per step (976 x 5120: 15.7 us against 18.4)
+        if (sh.per_cu == 1 && short_launch(T, nchunks)) sh.R = 2;
+        return sh;
+    }
     const Split sp = choose_split(nchunks, dtype);
     Shape sh{sp.K, sp.VPL, 2, blocks_per_cu(sp.K)};
-    if (dtype == 0 && ln) {
-        const int cols = (nchunks + kWave - 1) / kWave;
-        switch (cols) {
-            case 2: sh = {2, 2, 1, 4}; break;       // D = 1024: 523 against 549 us for one wave
-            case 3:                                 // D = 1536: 524 against 542 us for one wave x 3
-            case 4: sh = {2, 2, 1, 3}; break;
-            case 5:
-            case 6: sh = {3, 2, 1, 2}; break;
-            case 7: sh = {4, 2, 2, 1}; break;       // D = 3584: 531 against 557 us for five waves
-            case 8: sh = {4, 3, 1, 1}; break;       // D = 4096: 515 against 521 us for five waves x 2
-            case 9: sh = {5, 2, 2, 1}; break;       // D = 4608: 517 against 546 us for four waves x 3
-            case 10:
-            case 11:
-            case 12: sh = {4, 3, 1, 1}; break;      // D = 5120: 537 against 560 us for five waves x 2
-            case 13:
-            case 14: sh = {8, 2, 2, 1}; break;      // D = 6656, 7168: 530 against 583 us for one row, two blocks
-            case 15: sh = {8, 2, 1, 1}; break;      // D = 7680: 541 against 582 us for two blocks
-            default:                                // D = 8192: 527 against 572 us for two rows, one block
-                if (cols >= 16) sh = {8, 2, 1, 2};
-                break;
-        }
-    }
-    if (dtype == 1 && ln) {
-        // fp32, per 512 features (128 chunks): the widths where the sweep beat the rule by 2 % or more
-        switch ((nchunks + 127) / 128) {
-            case 1: sh = {1, nchunks <= 64 ? 1 : 4, 2, 4}; break;    // D = 512: 515 against 535 us
-            case 3: sh = {2, 4, 1, 2}; break;                        // D = 1536: 556 against 576 us
-            case 4: sh = {3, 4, 2, 2}; break;                        // D = 2048: 527 against 541 us
-            case 6: sh = {5, 4, 2, 1}; break;                        // D = 3072: 538 against 565 us
-            case 8: sh = {5, 4, 1, 3}; break;                        // D = 4096: 528 against 555 us
-            case 16: sh = {8, 4, 2, 2}; break;                       // D = 8192: 568 against 592 us
-            default: break;
-        }
-    }
     if (dtype == 0 && !ln) {
         // the residual-only kernel (first half of the unfused comparator) at the two model widths:
         // D = 1536: 366 against 393 us, D = 5120: 385 against 401 us on 774 MB per tensor
@@ -75,7 +83,7 @@ void go_r(const GatedFwdArgs& a, int64_t blocks, hipStream_t st) {
 
 template <typename Tag, int VPL, int K, bool LN>
 void go(const GatedFwdArgs& a, int R, int64_t blocks, hipStream_t st) {
-    if constexpr (LN && IO<Tag>::E == 8) {               // only the bf16 table asks for one row
+    if constexpr (LN) {
         if (R == 1) {
             go_r<Tag, VPL, K, 1, LN>(a, blocks, st);
             return;
@@ -139,7 +147,7 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.eps = p.eps;
     a.inv_D = 1.0f / static_cast<float>(p.D);
-    const Shape sh = gated_fwd_shape(a.nchunks, p.dtype, LN);
+    const Shape sh = gated_fwd_shape(a.nchunks, p.dtype, LN, p.T);
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     // bytes of x, u, h and y at 6 TB/s
     const double stream_us = static_cast<double>(p.T) * static_cast<double>(p.D) * (p.dtype == 0 ? 8.0 : 16.0) / 6.0e6;
@@ -156,7 +164,7 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
 
 }  // namespace
 
-Shape gated_fwd_table_shape(int nchunks, int dtype) { return gated_fwd_shape(nchunks, dtype, true); }
+Shape gated_fwd_table_shape(int nchunks, int dtype, int64_t T) { return gated_fwd_shape(nchunks, dtype, true, T); }
 
 hipError_t launch_gated_fwd(const Problem& p, const void* x, const void* u, const void* gate,
                             const void* shift, const void* scale, void* h, void* y, float* mean,

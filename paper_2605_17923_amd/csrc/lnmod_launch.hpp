@@ -207,16 +207,14 @@ inline Split choose_split(int nchunks, int dtype) {
     return {k, per_feat16};
 }
 
-// Launch shape of the per-sample / per-segment kernels: K waves per row, VPL chunks per lane, R
-// rows per block and step, per_cu resident blocks per CU.  The shape comes from a table per element
-// type, indexed by the row length in units of 512 features.  The tables were measured, not
-// derived: every instantiated (K, VPL, R, per_cu) that covers the row with at most 60 % padding
-// and 3 to 16 waves per CU was timed on one sample of about 770 MB per tensor at every multiple of
-// 512 features from 512 to 8192 (the widths of the models of Sec. 4.1, D = 1536 and 5120, three
-// times on different machines, the others twice), and the entry is the shape with the best worst
-// run.  What the winners share: a wave count that is a multiple of the four SIMDs of a CU (or a
-// single block of 5 or 6 waves), and 16 to 32 KB of row data in flight per CU.  Neighbouring
-// widths do not share winners: an entry that is best at D = 4096 loses 28 % at D = 3584.
+// Launch shape of the row kernels: K waves per row, VPL chunks per lane, R rows per block and step,
+// per_cu resident blocks per CU.  The shape comes from a table per element type, indexed by the row length.
+// The tables were measured, not derived: every instantiated (K, VPL, R, per_cu) that covers the row with at
+// most 50 to 60 % padding and 3 to 16 waves per CU (short forwards: up to 24) was timed on one sample, and the
+// entry is the shape with the best run (D = 1536 and 5120 on 770 MB, three times on different machines).  What
+// the winners on long launches share: a wave count that is a multiple of the four SIMDs of a CU (or a single
+// block of 5 or 6 waves), and 16 to 32 KB of row data in flight per CU.  Neighbouring widths do not share
+// winners: an entry that is best at D = 4096 loses 28 % at D = 3584.
 
 // Entry of a per-512-features table (index 1 ... 16; [0] is unused).  A row of at most 64 chunks
 // on a single wave needs one chunk per lane whatever the first entry says.
@@ -228,75 +226,179 @@ inline Shape table_entry(const Shape (&tab)[17], int nchunks, int dtype) {
     return sh;
 }
 
-// T: the token count if known (0: not known); only the D = 1536 entry looks at it.
+// The tables of the per-sample forward, the backward and the recompute backward have an entry per 256
+// features, because what is best at a multiple of 512 can be far off half a step below it, where a quarter
+// or a third of the lanes have no chunk (D = 768 forward on 400 MB 175 -> 135 us, 3840 165 -> 134, 4864
+// 203 -> 135; backward D = 768 333 -> 221, 2304 242 -> 211, 4864 222 -> 200), and the forward wider than 6144
+// features gained shapes that cover it more closely (eight waves of two chunks: 6400 199 -> 147).  Mean
+// over the 32 widths of 256 features, new over old time: forward bf16 0.91, fp32 0.97; backward 0.96 and 0.98;
+// recompute 0.96 and 0.98.  Entries that the sweep moved by less than 1.5 % stayed as they were.
+//
+// Short launches have tables of their own: a block then runs a handful of steps, so the latency of its
+// first rows counts more than how the blocks' windows line up, and more, smaller blocks per CU win
+// (forward on 16 and 64 MB tensors: 0.87 of the former time in the mean, fp32 0.92; D = 5120 x 1560 rows 10.6 ->
+// 8.8 us, 1536 x 5208 8.8 -> 7.5; on 400 MB the same shapes lose up to 14 %).  The line is 72 MB of x: at 64 MB
+// the short entry is the better one at nearly every width, at 96 MB it has lost at half of them.
+constexpr int64_t kShortBytes = 72000000;
+inline bool short_launch(int64_t T, int nchunks) { return T > 0 && T * nchunks * 16 <= kShortBytes; }
+
+// Entry of a per-256-features table (index 1 ... 32; [0] is unused).
+inline Shape fine_entry(const Shape (&tab)[33], int nchunks, int dtype) {
+    const int per256 = dtype == 0 ? 32 : 64;
+    const int cols = (nchunks + per256 - 1) / per256;
+    return tab[cols < 1 ? 1 : cols > 32 ? 32 : cols];
+}
+
+// A forward whose rows all find a block of their own takes one row per step: 366 rows at D = 2680 4.8 us
+// against 5.5 with two.
+inline Shape one_step(Shape sh, int64_t T) {
+    if (T <= static_cast<int64_t>(kNumCU) * sh.per_cu) sh.R = 1;
+    return sh;
+}
+
+// T: the token count if known (0: not known, a long launch).
 inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
     if (dtype == 0) {
-        static const Shape tab[17] = {
-            {1, 1, 2, 8},                                                    // (unused)
-            {1, 1, 2, 8}, {1, 2, 2, 4}, {1, 3, 1, 8}, {2, 2, 1, 4},          // D <=  512 ... 2048
-            {2, 3, 1, 4}, {4, 2, 1, 3}, {4, 2, 1, 3}, {4, 2, 2, 1},          //      2560 ... 4096
-            {4, 3, 1, 2}, {5, 2, 2, 1}, {4, 3, 1, 2}, {4, 3, 1, 2},          //      4608 ... 6144
-            {6, 3, 1, 2}, {6, 3, 1, 2}, {6, 3, 1, 1}, {6, 3, 1, 1}};         //      6656 ... 8192
+        static const Shape tab[33] = {
+            {1, 1, 2, 16},
+            {1, 1, 2, 16}, {1, 1, 2, 8}, {1, 2, 1, 12}, {1, 2, 2, 4},   // D <= 1024
+            {1, 3, 1, 8}, {1, 3, 2, 4}, {2, 2, 1, 6}, {2, 2, 1, 4},   // D <= 2048
+            {2, 3, 1, 4}, {2, 3, 1, 4}, {2, 3, 1, 4}, {4, 2, 1, 3},   // D <= 3072
+            {4, 2, 1, 3}, {4, 2, 1, 3}, {4, 2, 1, 3}, {4, 2, 2, 1},   // D <= 4096
+            {4, 3, 2, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {5, 2, 2, 1},   // D <= 5120
+            {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
+            {8, 2, 1, 2}, {8, 2, 2, 2}, {5, 3, 1, 1}, {5, 3, 1, 1},   // D <= 7168
+            {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
+        static const Shape tab_short[33] = {
+            {1, 1, 2, 16},
+            {1, 1, 2, 16}, {1, 1, 2, 16}, {1, 2, 2, 16}, {1, 2, 2, 12},   // D <= 1024
+            {1, 3, 1, 12}, {1, 3, 2, 8}, {2, 2, 2, 8}, {2, 2, 1, 8},   // D <= 2048
+            {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 12},   // D <= 3072
+            {4, 2, 1, 4}, {4, 2, 1, 3}, {4, 2, 2, 3}, {4, 2, 2, 2},   // D <= 4096
+            {4, 3, 2, 3}, {4, 3, 1, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 5120
+            {4, 3, 2, 6}, {4, 3, 1, 3}, {4, 3, 2, 2}, {4, 3, 1, 2},   // D <= 6144
+            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2},   // D <= 7168
+            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};   // D <= 8192
+        if (short_launch(T, nchunks)) return one_step(fine_entry(tab_short, nchunks, dtype), T);
         // D = 1536: four blocks per CU are 4 % faster on the 32 760 rows of the Wan-1.3B workload,
         // the two tie on 65 520 rows, three are 3 % faster on 131 040 rows and 5 % on 252 000
         if (nchunks == 192) return {1, 3, 2, T >= 98304 ? 3 : 4};
-        return table_entry(tab, nchunks, dtype);
+        return fine_entry(tab, nchunks, dtype);
     }
     // fp32: one row per step and two blocks per CU once several waves share a row (a wave's four
     // chunks carry twice the bytes of a bf16 wave's two: 266 against 287 us on 37800 x 5120)
-    static const Shape tab32[17] = {
-        {1, 2, 2, 8},
-        {1, 2, 2, 8}, {1, 4, 1, 8}, {1, 6, 2, 4}, {2, 4, 2, 2},
-        {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},
-        {5, 4, 1, 2}, {5, 4, 1, 2}, {8, 4, 1, 2}, {6, 4, 1, 1},
-        {8, 4, 1, 2}, {8, 4, 1, 2}, {8, 4, 1, 2}, {8, 4, 1, 2}};
-    return table_entry(tab32, nchunks, dtype);
+    static const Shape tab32[33] = {
+        {1, 1, 2, 8},
+        {1, 1, 2, 8}, {1, 2, 2, 8}, {1, 4, 1, 8}, {1, 4, 1, 8},   // D <= 1024
+        {1, 6, 1, 6}, {1, 6, 1, 6}, {2, 4, 2, 4}, {2, 4, 2, 2},   // D <= 2048
+        {3, 4, 2, 2}, {3, 4, 1, 4}, {4, 4, 1, 2}, {4, 4, 1, 2},   // D <= 3072
+        {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},   // D <= 4096
+        {5, 4, 1, 2}, {5, 4, 1, 2}, {5, 4, 1, 2}, {5, 4, 1, 2},   // D <= 5120
+        {6, 4, 1, 2}, {8, 4, 1, 2}, {6, 4, 1, 1}, {6, 4, 1, 1},   // D <= 6144
+        {8, 4, 2, 3}, {8, 4, 2, 3}, {8, 4, 2, 3}, {8, 4, 2, 3},   // D <= 7168
+        {8, 4, 2, 3}, {8, 4, 2, 3}, {8, 4, 2, 3}, {8, 4, 1, 2}};   // D <= 8192
+    static const Shape tab32_short[33] = {
+        {1, 1, 2, 16},
+        {1, 1, 2, 16}, {1, 2, 2, 8}, {1, 3, 2, 8}, {1, 4, 2, 12},   // D <= 1024
+        {1, 6, 2, 8}, {1, 6, 2, 8}, {2, 4, 2, 12}, {2, 4, 2, 6},   // D <= 2048
+        {3, 4, 2, 4}, {3, 4, 2, 8}, {4, 4, 1, 4}, {3, 4, 2, 3},   // D <= 3072
+        {4, 4, 1, 3}, {4, 4, 1, 3}, {4, 4, 1, 3}, {4, 4, 1, 2},   // D <= 4096
+        {5, 4, 1, 2}, {5, 4, 1, 2}, {5, 4, 1, 2}, {5, 4, 1, 2},   // D <= 5120
+        {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2},   // D <= 6144
+        {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 1, 1},   // D <= 7168
+        {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 2}, {8, 4, 2, 2}};   // D <= 8192
+    if (short_launch(T, nchunks)) return one_step(fine_entry(tab32_short, nchunks, dtype), T);
+    return fine_entry(tab32, nchunks, dtype);
 }
 
-inline Shape bwd_shape(int nchunks, int dtype) {
+inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
     if (dtype == 0) {
-        static const Shape tab[17] = {
+        static const Shape tab[33] = {
             {1, 1, 2, 8},
-            {1, 1, 2, 8}, {1, 2, 2, 3}, {3, 1, 1, 4}, {4, 1, 2, 2},
-            {5, 1, 2, 1}, {6, 1, 2, 1}, {4, 2, 1, 3}, {4, 2, 2, 1},
-            {5, 2, 2, 1}, {4, 3, 2, 1}, {6, 2, 1, 1}, {4, 3, 2, 1},
-            {8, 2, 1, 1}, {6, 3, 2, 1}, {6, 3, 2, 1}, {6, 3, 2, 1}};
+            {1, 1, 2, 8}, {1, 1, 1, 8}, {1, 2, 2, 8}, {1, 2, 2, 3},   // D <= 1024
+            {3, 1, 1, 4}, {3, 1, 1, 4}, {4, 1, 2, 3}, {4, 1, 2, 2},   // D <= 2048
+            {5, 1, 2, 2}, {5, 1, 2, 2}, {3, 2, 1, 2}, {6, 1, 2, 1},   // D <= 3072
+            {8, 1, 2, 1}, {4, 2, 1, 3}, {4, 2, 2, 1}, {8, 1, 1, 1},   // D <= 4096
+            {5, 2, 2, 1}, {5, 2, 2, 1}, {6, 2, 2, 1}, {4, 3, 2, 1},   // D <= 5120
+            {8, 2, 2, 1}, {6, 2, 1, 1}, {6, 2, 1, 1}, {4, 3, 2, 1},   // D <= 6144
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {6, 3, 2, 1}, {6, 3, 2, 1},   // D <= 7168
+            {6, 3, 2, 1}, {6, 3, 2, 1}, {6, 3, 2, 1}, {6, 3, 2, 1}};   // D <= 8192
+        static const Shape tab_short[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 1, 2, 4}, {1, 2, 2, 4}, {1, 2, 2, 3},   // D <= 1024
+            {3, 1, 1, 4}, {3, 1, 2, 2}, {4, 1, 2, 2}, {4, 1, 1, 2},   // D <= 2048
+            {5, 1, 2, 1}, {5, 1, 2, 1}, {6, 1, 2, 1}, {6, 1, 2, 1},   // D <= 3072
+            {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 1, 1},   // D <= 4096
+            {6, 2, 1, 1}, {6, 2, 1, 1}, {5, 2, 2, 1}, {5, 2, 2, 1},   // D <= 5120
+            {6, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 6144
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 7168
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
         if (nchunks == 192) return {3, 1, 1, 3};
-        return table_entry(tab, nchunks, dtype);
+        return fine_entry(tab, nchunks, dtype);
     }
     // fp32, rows of 1 KB and more: mostly one row per step (a wave's four chunks of one row are as
     // many bytes as two bf16 rows) and, for the wide rows, more waves than the chunks need
-    static const Shape tab32[17] = {
-        {1, 2, 2, 3},
-        {1, 2, 2, 3}, {1, 4, 1, 3}, {2, 4, 1, 2}, {2, 4, 1, 2},
-        {3, 4, 2, 1}, {4, 4, 1, 1}, {5, 4, 2, 1}, {4, 4, 1, 2},
-        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1},
-        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}};
-    return table_entry(tab32, nchunks, dtype);
+    static const Shape tab32[33] = {
+        {1, 1, 1, 8},
+        {1, 1, 1, 8}, {1, 2, 2, 3}, {1, 4, 1, 3}, {1, 4, 1, 3},   // D <= 1024
+        {2, 4, 2, 2}, {2, 4, 1, 2}, {2, 4, 1, 3}, {2, 4, 1, 2},   // D <= 2048
+        {3, 4, 2, 1}, {3, 4, 2, 1}, {4, 4, 1, 1}, {4, 4, 1, 1},   // D <= 3072
+        {5, 4, 1, 1}, {5, 4, 2, 1}, {5, 4, 2, 1}, {6, 4, 1, 1},   // D <= 4096
+        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1},   // D <= 5120
+        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {8, 4, 1, 1},   // D <= 6144
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}};   // D <= 8192
+    static const Shape tab32_short[33] = {
+        {1, 1, 2, 6},
+        {1, 1, 2, 6}, {1, 2, 2, 3}, {1, 3, 2, 3}, {1, 4, 1, 3},   // D <= 1024
+        {2, 4, 1, 2}, {2, 4, 1, 2}, {2, 4, 1, 2}, {3, 4, 2, 1},   // D <= 2048
+        {3, 4, 2, 1}, {3, 4, 2, 1}, {4, 4, 1, 1}, {4, 4, 1, 1},   // D <= 3072
+        {5, 4, 2, 1}, {5, 4, 1, 1}, {5, 4, 1, 1}, {4, 4, 2, 1},   // D <= 4096
+        {6, 4, 1, 1}, {6, 4, 2, 1}, {6, 4, 1, 1}, {6, 4, 1, 1},   // D <= 5120
+        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 2, 1},   // D <= 6144
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 2, 1}};   // D <= 8192
+    return short_launch(T, nchunks) ? fine_entry(tab32_short, nchunks, dtype) : fine_entry(tab32, nchunks, dtype);
 }
 
 // Backward that forms the statistics again from x.  It has one more dependent chain per step
 // (per-wave mean, four wave sums, the merge with a division and a square root), which fewer waves per
-// row with more chunks each, or two blocks per CU, hide better than the shapes above; timed at
-// D = 512 ... 8192 like the tables above; it then runs 2 to 20 % behind the backward that reads
-// the saved statistics (D = 5120: 14 %).
-inline Shape rc_bwd_shape(int nchunks, int dtype) {
+// row with more chunks each, or two blocks per CU, hide better than the shapes above; it runs 2 to 20 %
+// behind the backward that reads the saved statistics (D = 5120: 14 %).
+inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0) {
     if (dtype == 0) {
-        static const Shape tab[17] = {
+        static const Shape tab[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 1, 1, 8}, {1, 2, 2, 8}, {1, 2, 2, 4},   // D <= 1024
+            {1, 3, 1, 8}, {1, 3, 2, 4}, {2, 2, 1, 6}, {2, 2, 1, 4},   // D <= 2048
+            {3, 2, 2, 3}, {3, 2, 2, 3}, {3, 2, 2, 3}, {3, 2, 2, 2},   // D <= 3072
+            {4, 2, 1, 3}, {4, 2, 1, 3}, {4, 2, 1, 3}, {4, 2, 2, 1},   // D <= 4096
+            {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 5120
+            {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 2, 1},   // D <= 6144
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        // short launches: per 512 features (three samples of 2000 rows at D = 768: 18.4 us against 21.9)
+        static const Shape tab_short[17] = {
             {1, 1, 2, 8},
             {1, 1, 2, 8}, {1, 2, 2, 4}, {1, 3, 2, 4}, {2, 2, 1, 4},
             {3, 2, 2, 3}, {3, 2, 2, 2}, {4, 2, 1, 3}, {4, 2, 2, 1},
             {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 2, 1},
             {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};
-        return table_entry(tab, nchunks, dtype);
+        if (short_launch(T, nchunks)) return table_entry(tab_short, nchunks, dtype);
+        return fine_entry(tab, nchunks, dtype);
     }
-    static const Shape tab32[17] = {
-        {1, 2, 2, 3},
-        {1, 2, 2, 3}, {1, 6, 1, 3}, {2, 4, 1, 3}, {3, 4, 1, 2},
-        {3, 4, 2, 1}, {4, 4, 1, 1}, {5, 4, 2, 1}, {4, 4, 1, 2},
-        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {8, 4, 1, 1},
-        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}};
-    return table_entry(tab32, nchunks, dtype);
+    static const Shape tab32[33] = {
+        {1, 1, 1, 8},
+        {1, 1, 1, 8}, {1, 2, 2, 3}, {1, 4, 1, 4}, {1, 6, 1, 3},   // D <= 1024
+        {2, 4, 1, 4}, {2, 4, 1, 3}, {2, 4, 1, 3}, {3, 4, 1, 2},   // D <= 2048
+        {3, 4, 1, 2}, {3, 4, 2, 1}, {4, 4, 1, 1}, {4, 4, 1, 1},   // D <= 3072
+        {4, 4, 1, 1}, {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 1},   // D <= 4096
+        {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1},   // D <= 5120
+        {6, 4, 1, 1}, {6, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 6144
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}};   // D <= 8192
+    return fine_entry(tab32, nchunks, dtype);
 }
 
 // The table's entry, or the shape the call carries (Problem::force).  A forced shape that does not
@@ -305,7 +407,7 @@ inline Shape pick_shape(const Shape* force, Shape table) { return force ? *force
 inline bool covers(const Shape& s, int nchunks) { return s.K * s.VPL * 64 >= nchunks; }
 
 // Per-token modulation (three input streams forward; three in, three out backward).  bf16: a table
-// per 512 features like the ones above, from the same sweep over the (K, VPL) these kernels are
+// per 512 features of the same kind, from a sweep over the (K, VPL) these kernels are
 // compiled for (one wave alone, or two chunks per lane on 2 to 8 waves, or five chunks per lane on two waves).  Here too neighbours do
 // not share winners: D = 2560 forward takes 526 us with {3,2,2,4} and 858 us with the {3,2,1,2}
 // that is best at D = 3072.  fp32: tables of the same kind (four chunks per lane once a row is
@@ -332,7 +434,8 @@ inline Shape tok_fwd_shape(int nchunks, int dtype) {
     return table_entry(tab32, nchunks, dtype);
 }
 
-inline Shape tok_bwd_shape(int nchunks, int dtype) {
+// Per-token backward that forms the statistics again from x.
+inline Shape tok_rc_bwd_shape(int nchunks, int dtype) {
     if (dtype == 0) {
         static const Shape tab[17] = {
             {1, 1, 1, 6},
@@ -351,34 +454,50 @@ inline Shape tok_bwd_shape(int nchunks, int dtype) {
     return table_entry(tab32, nchunks, dtype);
 }
 
-// The per-token backward without the copy of dy (five streams): what is best for six is 2 to 14 % behind,
-// because with one write less fewer, wider waves keep up.  Timed at every multiple of 512 features on 400 MB
-// and 48 MB tensors (six-stream entry -> this one, 400 MB bf16: D = 1024 354 -> 333 us, 1536 341 -> 322, 2048
-// 378 -> 334, 2560 365 -> 324, 4096 362 -> 334, 5120 345 -> 335, 5632 372 -> 346, 6144 362 -> 337; fp32: D = 512
-// 346 -> 330, 2560 356 -> 339, 3072 361 -> 338, 3584 355 -> 339, 5120 358 -> 346).  Up to 32 Mi elements bf16 rows go
-// one per step, rows wider than 6144 with two blocks per CU (48 MB tensors: D = 6656 52 -> 44 us; above, at
-// 400 MB, the two-row shape takes 359 against 373).
-inline Shape tok_bwd_noshift_shape(int nchunks, int dtype, int64_t T) {
+// Per-token backward with saved statistics.  writes_dshift: whether the copy of dy goes out (six streams) or not
+// (five).  Both take the same waves and chunks per lane at a width, so that they add a row in the same order; rows
+// per step and blocks per CU differ where that measured better, and on launches of up to 32 Mi elements.  From a
+// sweep of both at every multiple of 512 features on 400 MB and 48 MB tensors; against the former table, six
+// streams: bf16 0.98 of the time in the mean, fp32 the same (48 MB: D = 2048 0.91, 5632 0.86, 6144 0.91; at
+// 400 MB at most 2 % slower at any width); five streams, 400 MB: D = 1024 354 -> 333 us, 2048 378 -> 334, 2560
+// 365 -> 324, 4096 362 -> 338, 5632 372 -> 346, 6144 362 -> 337; fp32 D = 2560 356 -> 344, 3584 355 -> 339, 5120
+// 358 -> 346.
+inline Shape tok_bwd_shape(int nchunks, int dtype, bool writes_dshift = true, int64_t T = 0) {
     if (dtype == 0) {
-        static const Shape tab[17] = {
+        static const Shape six[17] = {
+            {1, 1, 1, 6},
+            {1, 1, 1, 6}, {1, 2, 2, 3}, {3, 1, 2, 2}, {4, 1, 1, 2},
+            {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 1},
+            {6, 2, 1, 2}, {5, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
+            {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 1, 1}, {8, 2, 1, 1}};
+        static const Shape five[17] = {
             {1, 1, 1, 8},
             {1, 1, 1, 8}, {1, 2, 1, 4}, {3, 1, 2, 2}, {4, 1, 1, 2},
-            {6, 1, 1, 2}, {8, 1, 1, 2}, {4, 2, 2, 2}, {4, 2, 2, 2},
-            {6, 2, 1, 2}, {8, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
-            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 1, 1}};
-        Shape sh = table_entry(tab, nchunks, dtype);
-        if (T * nchunks * 8 <= (int64_t(32) << 20)) {
-            if (nchunks > 768) return {8, 2, 1, 2};
-            if (sh.R == 2) sh.R = 1;
-            if (sh.K == 3) sh.per_cu = 4;              // D = 1536: 48 MB 45.5 -> 41.4 us
-        }
-        return sh;
+            {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 1},
+            {6, 2, 1, 2}, {5, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
+            {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 1, 1}};
+        static const Shape five_short[17] = {
+            {1, 1, 1, 8},
+            {1, 1, 1, 8}, {1, 2, 1, 8}, {3, 1, 1, 4}, {4, 1, 1, 3},
+            {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2},
+            {6, 2, 1, 2}, {5, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
+            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};
+        if (writes_dshift) return table_entry(six, nchunks, dtype);
+        const bool few = T > 0 && T * nchunks * 8 <= (int64_t(32) << 20);
+        return few ? table_entry(five_short, nchunks, dtype) : table_entry(five, nchunks, dtype);
     }
-    Shape sh = tok_bwd_shape(nchunks, dtype);
+    static const Shape six32[17] = {
+        {1, 2, 2, 8},
+        {1, 2, 2, 8}, {1, 4, 1, 8}, {2, 4, 1, 2}, {2, 4, 2, 2},
+        {3, 4, 2, 1}, {3, 4, 1, 1}, {4, 4, 1, 1}, {5, 4, 1, 3},
+        {5, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1},
+        {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 2}};
+    Shape sh = table_entry(six32, nchunks, dtype);
     const int cols = (nchunks + 127) / 128;
-    if (cols == 1 && nchunks > 64) sh = {1, 4, 1, 4};
-    if (cols >= 5 && cols <= 7) sh = {4, 4, 1, 2};
-    if (cols == 9 || cols == 10) sh = {6, 4, 1, 1};
+    if (!writes_dshift && cols >= 5 && cols <= 7) {
+        sh.R = 1;
+        sh.per_cu = 2;
+    }
     return sh;
 }
 
@@ -406,6 +525,11 @@ RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, 
 inline int64_t bwd_slots(const RowPlan& p, int64_t nseg) {
     return nseg < 1 ? 0 : (p.clusters + nseg - 1) * p.nb;
 }
+
+// For a caller whose workspace cannot grow: the launch shape of this backward whose plan has at most max_slots
+// slots -- the table's own if it has, else the same rows per wave with fewer blocks in a cluster or on a CU.
+// False if there is none.
+bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots, Shape* out);
 
 // Shape of the second pass: V features per lane, W waves per block, G groups of lanes per wave
 // that take different slots (a block covers 64 / G * V features).  Wide blocks need enough
@@ -470,7 +594,7 @@ hipError_t launch_stream_probe(const void* const* in, int reads, void* const* ou
 
 // Gated residual + LayerNorm-Modulate (per-sample / per-segment gate, shift, scale).
 RowPlan gated_bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype);
-Shape gated_fwd_table_shape(int nchunks, int dtype);             // the tables' entries, no override
+Shape gated_fwd_table_shape(int nchunks, int dtype, int64_t T);  // the tables' entries, no override
 Shape gated_bwd_table_shape(int nchunks, int dtype);
 hipError_t launch_gated_fwd(const Problem& p, const void* x, const void* u, const void* gate,
                             const void* shift, const void* scale, void* h, void* y, float* mean,
@@ -486,7 +610,7 @@ hipError_t launch_zero_f32(float* p, int64_t n, hipStream_t st);
 
 // Fused Q-Norm + K-Norm (RMS normalisation with a learned weight of two tensors, one launch).
 int32_t qknorm_bwd_blocks(int64_t N, int64_t D, int dtype);      // partial-sum slots per tensor
-Shape qknorm_table_shape(int nchunks, int dtype, bool backward);  // rows wider than one head; no override
+Shape qknorm_table_shape(int nchunks, int dtype, bool backward, int64_t N);  // rows wider than one head; no override
 hipError_t launch_qknorm_fwd(int dtype, const void* q, const void* k, const void* wq, const void* wk,
                              int64_t N, int64_t D, float eps, void* q_out, void* k_out,
                              float* rstd_q, float* rstd_k, hipStream_t st);

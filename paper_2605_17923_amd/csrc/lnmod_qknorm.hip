@@ -8,54 +8,79 @@ namespace {
 
 constexpr int kRows = 2;           // rows per block and step
 
-// Resident blocks per CU over both tensors together; each tensor gets half of them.
-int fwd_blocks_per_cu(int K) {
-    if (K == 1) return 4;
-    if (K == 3) return 2;              // three waves alone leave a CU short
-    const int b = 5 / K;
-    return b < 1 ? 1 : b;
-}
-int bwd_blocks_per_cu(int K) {
-    if (K == 1) return 4;
-    const int b = 6 / K;
-    return b < 1 ? 1 : b;
-}
-
-// Launch shape of the wide-row kernels: the split of choose_split, two rows per step, and the
-// blocks per CU above (R is fixed by the instantiations).
-Shape wide_table_shape(int nchunks, int dtype, bool backward) {
-    const Split sp = choose_split(nchunks, dtype);
-    Shape sh{sp.K, sp.VPL, kRows, backward ? bwd_blocks_per_cu(sp.K) : fwd_blocks_per_cu(sp.K)};
+// Launch shape of the wide-row kernels (R is fixed by the instantiations; per_cu counts the resident blocks
+// of both tensors together, each tensor gets half of them): a table per 256 features from a sweep of every
+// compiled shape on 200 MB per tensor (fp32: 150 MB; the bf16 backward 32 and 200 MB), and for short bf16
+// forwards (see short_launch) one from 32 MB.  Against the rule with overrides per 512 features that stood here:
+// forward 0.98 of the time in the mean over 32 widths, short 0.94, fp32 0.96, backward 0.99 (forward D = 768 151
+// -> 138 us, 1792 161 -> 133, short 31.0 -> 24.3; backward D = 768 229 -> 207, 1280 215 -> 202, 3328 209 -> 197).
+Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
+    if (!backward && dtype == 0) {
+        static const Shape tab[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 1, 2, 8}, {1, 2, 2, 6}, {1, 2, 2, 4},   // D <= 1024
+            {2, 2, 2, 4}, {1, 3, 2, 3}, {2, 2, 2, 3}, {2, 2, 2, 2},   // D <= 2048
+            {3, 2, 2, 2}, {3, 2, 2, 2}, {3, 2, 2, 2}, {3, 2, 2, 2},   // D <= 3072
+            {4, 2, 2, 1}, {4, 2, 2, 1}, {5, 2, 2, 1}, {4, 3, 2, 1},   // D <= 4096
+            {5, 2, 2, 1}, {5, 2, 2, 1}, {5, 2, 2, 1}, {5, 2, 2, 1},   // D <= 5120
+            {6, 2, 2, 1}, {6, 2, 2, 1}, {8, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        static const Shape tab_short[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 1, 2, 16}, {1, 2, 2, 16}, {1, 2, 2, 16},   // D <= 1024
+            {2, 2, 2, 8}, {1, 3, 2, 16}, {2, 2, 2, 6}, {2, 2, 2, 8},   // D <= 2048
+            {3, 2, 2, 6}, {4, 2, 2, 4}, {4, 2, 2, 3}, {4, 2, 2, 3},   // D <= 3072
+            {5, 2, 2, 3}, {4, 2, 2, 4}, {5, 2, 2, 3}, {4, 2, 2, 4},   // D <= 4096
+            {6, 2, 2, 3}, {6, 2, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 5120
+            {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 6144
+            {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 2}, {8, 2, 2, 2}};   // D <= 8192
+        return short_launch(N, nchunks) ? fine_entry(tab_short, nchunks, dtype) : fine_entry(tab, nchunks, dtype);
+    }
+    if (!backward) {
+        static const Shape tab32[33] = {
+            {1, 1, 2, 8},
+            {1, 1, 2, 8}, {1, 2, 2, 8}, {1, 3, 2, 8}, {1, 4, 2, 6},   // D <= 1024
+            {2, 4, 2, 3}, {2, 4, 2, 4}, {2, 4, 2, 2}, {2, 4, 2, 2},   // D <= 2048
+            {3, 4, 2, 2}, {3, 4, 2, 3}, {3, 4, 2, 3}, {3, 4, 2, 1},   // D <= 3072
+            {4, 4, 2, 1}, {4, 4, 2, 1}, {5, 4, 2, 2}, {5, 4, 2, 2},   // D <= 4096
+            {5, 4, 2, 2}, {5, 4, 2, 2}, {5, 4, 2, 2}, {5, 4, 2, 2},   // D <= 5120
+            {6, 4, 2, 2}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
+            {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
+            {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
+        return fine_entry(tab32, nchunks, dtype);
+    }
     if (dtype == 0) {
-        // widths where the sweep of every compiled shape (D = 512 ... 8192, 774 MB per tensor) beat
-        // the rule by 3 % or more
-        const int cols = (nchunks + kWave - 1) / kWave;
-        if (!backward) {
-            if (cols == 1) sh.per_cu = 8;                    // D = 512: 555 against 670 us
-            if (cols == 3) sh = {1, 3, kRows, 3};            // D = 1536: 516 against 560 us
-            if (cols == 8) sh = {4, 3, kRows, 1};            // D = 4096: 527 against 562 us for 4 waves x 2
-        } else {
-            if (cols == 1) sh.per_cu = 6;                    // D = 512: 776 against 810 us
-            if (cols == 2) sh = {1, 2, kRows, 3};            // D = 1024: 760 against 833 us
-            if (cols == 3) sh = {2, 2, kRows, 3};            // D = 1536: 784 against 838 us
-            if (cols == 6) sh = {3, 2, kRows, 1};            // D = 3072: 750 against 807 us
-            if (cols == 7) sh = {4, 2, kRows, 2};            // D = 3584: 827 against 850 us
-            if (cols == 8) sh = {5, 2, kRows, 2};            // D = 4096: 778 against 805 us
-        }
+        static const Shape tab[33] = {
+            {1, 1, 2, 6},
+            {1, 1, 2, 6}, {1, 1, 2, 6}, {1, 2, 2, 6}, {1, 2, 2, 3},   // D <= 1024
+            {2, 2, 2, 4}, {2, 2, 2, 3}, {2, 2, 2, 3}, {2, 2, 2, 2},   // D <= 2048
+            {3, 2, 2, 2}, {3, 2, 2, 2}, {3, 2, 2, 2}, {3, 2, 2, 1},   // D <= 3072
+            {4, 2, 2, 1}, {4, 2, 2, 2}, {4, 2, 2, 1}, {4, 2, 2, 1},   // D <= 4096
+            {5, 2, 2, 1}, {5, 2, 2, 1}, {5, 2, 2, 1}, {5, 2, 2, 1},   // D <= 5120
+            {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        return fine_entry(tab, nchunks, dtype);
     }
-    if (dtype == 1 && !backward) {
-        const int cols = (nchunks + 127) / 128;              // fp32, per 512 features
-        if (cols == 3) sh = {2, 4, kRows, 2};                // D = 1536: 518 against 535 us
-        if (cols == 6) sh = {3, 4, kRows, 1};                // D = 3072: 520 against 560 us
-        if (cols == 8) sh = {5, 4, kRows, 2};                // D = 4096: 551 against 576 us
-    }
-    return sh;
+    static const Shape tab32[33] = {
+        {1, 1, 2, 6},
+        {1, 1, 2, 6}, {1, 2, 2, 4}, {1, 3, 2, 4}, {1, 4, 2, 4},   // D <= 1024
+        {2, 4, 2, 3}, {1, 6, 2, 4}, {2, 4, 2, 3}, {2, 4, 2, 3},   // D <= 2048
+        {3, 4, 2, 2}, {3, 4, 2, 2}, {3, 4, 2, 2}, {3, 4, 2, 2},   // D <= 3072
+        {4, 4, 2, 2}, {4, 4, 2, 1}, {4, 4, 2, 1}, {4, 4, 2, 1},   // D <= 4096
+        {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 1},   // D <= 5120
+        {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
+        {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
+        {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
+    return fine_entry(tab32, nchunks, dtype);
 }
 
 // The table's shape; ok is false for a shape these kernels are not compiled for or that does not
 // cover the row (a mistake in the table then fails the launch instead of computing on part of a row).
-Shape wide_shape(int nchunks, int dtype, bool backward, bool* ok) {
-    const Shape sh = wide_table_shape(nchunks, dtype, backward);
+Shape wide_shape(int nchunks, int dtype, bool backward, int64_t N, bool* ok) {
+    const Shape sh = wide_table_shape(nchunks, dtype, backward, N);
     const int wide = dtype == 0 ? 2 : 4;
     bool compiled;
     if (sh.K == 1) compiled = sh.VPL >= 1 && (sh.VPL <= 3 || (dtype == 1 && (sh.VPL == 4 || sh.VPL == 6)));
@@ -162,11 +187,13 @@ int32_t qknorm_bwd_blocks(int64_t N, int64_t D, int dtype) {
         return short_blocks_per_tensor(N, 4 * r, kShortBwdBlocksPerCu) * kShortWaves;
     }
     bool ok;
-    const Shape sh = wide_shape(nchunks, dtype, true, &ok);
+    const Shape sh = wide_shape(nchunks, dtype, true, N, &ok);
     return blocks_per_tensor(N, sh.per_cu);
 }
 
-Shape qknorm_table_shape(int nchunks, int dtype, bool backward) { return wide_table_shape(nchunks, dtype, backward); }
+Shape qknorm_table_shape(int nchunks, int dtype, bool backward, int64_t N) {
+    return wide_table_shape(nchunks, dtype, backward, N);
+}
 
 hipError_t launch_qknorm_fwd(int dtype, const void* q, const void* k, const void* wq, const void* wk,
                              int64_t N, int64_t D, float eps, void* q_out, void* k_out,
@@ -196,7 +223,7 @@ hipError_t launch_qknorm_fwd(int dtype, const void* q, const void* k, const void
         return hipGetLastError();
     }
     bool ok;
-    const Shape sh = wide_shape(a.nchunks, dtype, false, &ok);
+    const Shape sh = wide_shape(a.nchunks, dtype, false, N, &ok);
     if (!ok) return hipErrorInvalidConfiguration;
     const Split sp{sh.K, sh.VPL};
     a.nb = blocks_per_tensor(N, sh.per_cu);
@@ -235,7 +262,7 @@ hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, 
         }
     } else {
         bool ok;
-        const Shape sh = wide_shape(a.nchunks, dtype, true, &ok);
+        const Shape sh = wide_shape(a.nchunks, dtype, true, N, &ok);
         if (!ok) return hipErrorInvalidConfiguration;
         const Split sp{sh.K, sh.VPL};
         a.nb = slots;

@@ -109,16 +109,17 @@ int lnmod_table_shape(int family, int64_t D, int dtype, int64_t tokens, int* out
     if (D < 8 || D > lnmod::kMaxD || D % vec != 0) return LNMOD_EUNSUPPORTED;
     const int nchunks = static_cast<int>(D / vec);
     Shape sh{};
+    const int64_t T = tokens < 0 ? 0 : tokens;
     switch (family) {
-        case LNMOD_FAMILY_FORWARD: sh = lnmod::fwd_shape(nchunks, dtype, tokens < 0 ? 0 : tokens); break;
-        case LNMOD_FAMILY_BACKWARD: sh = lnmod::bwd_shape(nchunks, dtype); break;
-        case LNMOD_FAMILY_BACKWARD_RECOMPUTE: sh = lnmod::rc_bwd_shape(nchunks, dtype); break;
+        case LNMOD_FAMILY_FORWARD: sh = lnmod::fwd_shape(nchunks, dtype, T); break;
+        case LNMOD_FAMILY_BACKWARD: sh = lnmod::bwd_shape(nchunks, dtype, T); break;
+        case LNMOD_FAMILY_BACKWARD_RECOMPUTE: sh = lnmod::rc_bwd_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_TOKEN_FORWARD: sh = lnmod::tok_fwd_shape(nchunks, dtype); break;
         case LNMOD_FAMILY_TOKEN_BACKWARD: sh = lnmod::tok_bwd_shape(nchunks, dtype); break;
-        case LNMOD_FAMILY_GATED_FORWARD: sh = lnmod::gated_fwd_table_shape(nchunks, dtype); break;
+        case LNMOD_FAMILY_GATED_FORWARD: sh = lnmod::gated_fwd_table_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_GATED_BACKWARD: sh = lnmod::gated_bwd_table_shape(nchunks, dtype); break;
-        case LNMOD_FAMILY_QKNORM_FORWARD: sh = lnmod::qknorm_table_shape(nchunks, dtype, false); break;
-        default: sh = lnmod::qknorm_table_shape(nchunks, dtype, true); break;
+        case LNMOD_FAMILY_QKNORM_FORWARD: sh = lnmod::qknorm_table_shape(nchunks, dtype, false, T); break;
+        default: sh = lnmod::qknorm_table_shape(nchunks, dtype, true, T); break;
     }
     out[0] = sh.K;
     out[1] = sh.VPL;

@@ -1,0 +1,32 @@
+"""Launch shapes chosen by token count: every family's entry covers its row at every supported width for short
+launches too, and the backward that keeps its slots in a static array finds a plan that fits wherever the plan of
+lnmod_backward does not."""
+import os
+
+import pytest
+
+from paper_2605_17923_amd import lnmod, lnmod_tools as T
+
+
+@pytest.mark.parametrize("tokens", [1, 300, 2500, 20000, 400000])
+def test_every_entry_covers_its_row_whatever_the_token_count(tokens):
+    for fam in range(T.LNMOD_FAMILIES):
+        for dtype, vec in ((0, 8), (1, 4)):
+            for D in range(8, 8193, 8):
+                st, (K, VPL, R, per_cu) = T.lnmod_table_shape(fam, D, dtype, tokens)
+                assert st == 0 and K * VPL * 64 >= D // vec, (fam, dtype, D)
+                assert R in (1, 2) and 1 <= per_cu and K * per_cu <= 32, (fam, dtype, D)
+
+
+@pytest.mark.parametrize("B,S,D,dtype,rc", [(471, 127, 3824, 1, 1), (17, 5276, 5768, 0, 1), (188, 352, 3840, 0, 1),
+                                            (146, 348, 3832, 1, 1), (419, 165, 3936, 1, 0), (1936, 297, 1592, 1, 0),
+                                            (1428, 638, 1544, 0, 0), (123, 4572, 1080, 0, 1), (1051, 56, 3984, 1, 1)])
+def test_static_backward_takes_problems_whose_usual_plan_needs_more(B, S, D, dtype, rc):
+    # these were within the array before their launch shapes got more blocks; without a GPU an accepted call
+    # ends at the first HIP call (LNMOD_ELAUNCH), a refused one before it
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("the addresses are made up: only for a host without a GPU")
+    A = 16
+    st = lnmod.lnmod_backward_static(A, A, None, A, B, S, D, 1e-6, None, None if rc else A, None if rc else A, A, A, A,
+                                     dtype, lnmod.LNMOD_PER_SAMPLE)
+    assert st == lnmod.LNMOD_ELAUNCH
