@@ -249,6 +249,11 @@ inline Shape fine_entry(const Shape (&tab)[33], int nchunks, int dtype) {
     return tab[cols < 1 ? 1 : cols > 32 ? 32 : cols];
 }
 
+// Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
+// share lines with their neighbours, and at a few widths that turns the order of the shapes around, so the
+// entries there were timed on such rows too (the unaligned_* lines below: 300 MB, unless said).
+inline bool unaligned_rows(int nchunks) { return nchunks % 8 != 0; }
+
 // A forward whose rows all find a block of their own takes one row per step: 366 rows at D = 2680 4.8 us
 // against 5.5 with two.
 inline Shape one_step(Shape sh, int64_t T) {
@@ -279,7 +284,14 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {4, 3, 2, 6}, {4, 3, 1, 3}, {4, 3, 2, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2},   // D <= 7168
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};   // D <= 8192
-        if (short_launch(T, nchunks)) return one_step(fine_entry(tab_short, nchunks, dtype), T);
+        const int col = (nchunks + 31) / 32;
+        if (short_launch(T, nchunks)) {
+            Shape sh = fine_entry(tab_short, nchunks, dtype);
+            if (unaligned_rows(nchunks) && col == 21) sh = {4, 3, 1, 2};     // D = 5272, 40 MB: 17.5 against 19.3 us
+            return one_step(sh, T);
+        }
+        if (unaligned_rows(nchunks) && col == 11) return {4, 2, 1, 3};       // D = 2760: 109 against 114
+        if (unaligned_rows(nchunks) && col == 30) return {6, 3, 1, 1};       // D = 7640: 117 against 142
         // D = 1536: four blocks per CU are 4 % faster on the 32 760 rows of the Wan-1.3B workload,
         // the two tie on 65 520 rows, three are 3 % faster on 131 040 rows and 5 % on 252 000
         if (nchunks == 192) return {1, 3, 2, T >= 98304 ? 3 : 4};
@@ -318,7 +330,7 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {1, 1, 2, 8}, {1, 1, 1, 8}, {1, 2, 2, 8}, {1, 2, 2, 3},   // D <= 1024
             {3, 1, 1, 4}, {3, 1, 1, 4}, {4, 1, 2, 3}, {4, 1, 2, 2},   // D <= 2048
             {5, 1, 2, 2}, {5, 1, 2, 2}, {3, 2, 1, 2}, {6, 1, 2, 1},   // D <= 3072
-            {8, 1, 2, 1}, {4, 2, 1, 3}, {4, 2, 2, 1}, {8, 1, 1, 1},   // D <= 4096
+            {8, 1, 2, 1}, {4, 2, 1, 3}, {4, 2, 2, 1}, {4, 2, 2, 1},   // D <= 4096
             {5, 2, 2, 1}, {5, 2, 2, 1}, {6, 2, 2, 1}, {4, 3, 2, 1},   // D <= 5120
             {8, 2, 2, 1}, {6, 2, 1, 1}, {6, 2, 1, 1}, {4, 3, 2, 1},   // D <= 6144
             {8, 2, 1, 1}, {8, 2, 1, 1}, {6, 3, 2, 1}, {6, 3, 2, 1},   // D <= 7168
@@ -326,7 +338,7 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
         static const Shape tab_short[33] = {
             {1, 1, 2, 8},
             {1, 1, 2, 8}, {1, 1, 2, 4}, {1, 2, 2, 4}, {1, 2, 2, 3},   // D <= 1024
-            {3, 1, 1, 4}, {3, 1, 2, 2}, {4, 1, 2, 2}, {4, 1, 1, 2},   // D <= 2048
+            {3, 1, 1, 4}, {3, 1, 2, 2}, {4, 1, 2, 2}, {4, 1, 2, 2},   // D <= 2048
             {5, 1, 2, 1}, {5, 1, 2, 1}, {6, 1, 2, 1}, {6, 1, 2, 1},   // D <= 3072
             {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 2, 1}, {8, 1, 1, 1},   // D <= 4096
             {6, 2, 1, 1}, {6, 2, 1, 1}, {5, 2, 2, 1}, {5, 2, 2, 1},   // D <= 5120
@@ -334,6 +346,12 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 7168
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
         if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
+        if (unaligned_rows(nchunks)) {
+            const int col = (nchunks + 31) / 32;
+            if (col == 11) return {6, 1, 2, 1};                              // D = 2760: 162 against 166 us
+            if (col == 21) return {6, 2, 1, 1};                              // D = 5272: 161 against 165
+            if (col == 23) return {4, 3, 2, 1};                              // D = 5800: 168 against 173
+        }
         if (nchunks == 192) return {3, 1, 1, 3};
         return fine_entry(tab, nchunks, dtype);
     }
@@ -482,6 +500,11 @@ inline Shape tok_bwd_shape(int nchunks, int dtype, bool writes_dshift = true, in
             {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2}, {8, 1, 1, 2},
             {6, 2, 1, 2}, {5, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};
+        const int cols = (nchunks + 63) / 64;
+        if (unaligned_rows(nchunks) && (cols == 7 || cols == 8)) {           // D = 3704, 4008, five streams,
+            if (!writes_dshift) return {4, 2, 2, 2};                         // 200 MB: 184 against 209 us
+            return {4, 2, 1, cols == 7 ? 2 : 1};
+        }
         if (writes_dshift) return table_entry(six, nchunks, dtype);
         const bool few = T > 0 && T * nchunks * 8 <= (int64_t(32) << 20);
         return few ? table_entry(five_short, nchunks, dtype) : table_entry(five, nchunks, dtype);
