@@ -166,16 +166,12 @@ struct LnModulate : public torch::autograd::Function<LnModulate> {
             mean.defined() == rstd.defined() &&
             (!mean.defined() || (plain(mean, mean.sizes(), at::kFloat, x.device()) && mean.numel() == b.T &&
                                  plain(rstd, mean.sizes(), at::kFloat, x.device())))) {
-            // With a modulation row per token the gradient of shift is dy: it is handed on as it came, as the
-            // gradient of a sum is, instead of as a copy (a sixth of that backward's traffic: 65 520 x 5120
-            // rows 726 -> 595 us).  Not while a graph of the backward is recorded: the copy has no history.
-            const bool hand_on = token && !(at::GradMode::is_enabled() && dy.requires_grad());
-            Tensor dx = at::empty_like(x), dshift = hand_on ? dy : at::empty_like(scale), dscale = at::empty_like(scale);
+            // With a modulation row per token dshift equals dy, but it is a tensor of its own: a leaf's .grad, a hook or
+            // torch.autograd.grad's caller may write to it, and whether dy's memory has another user cannot be told here
+            // (a view in front of the operator gives dy a fresh tensor over memory that is still the caller's).
+            Tensor dx = at::empty_like(x), dshift = at::empty_like(scale), dscale = at::empty_like(scale);
             int st;
-            if (hand_on) {
-                st = lnmod_backward_token(ptr(dy), ptr(x), ptr(scale), b.n, b.s_or_t, b.D, static_cast<float>(eps),
-                                          stream_of(x), f32(mean), f32(rstd), out(dx), out(dscale), code_of(x));
-            } else if (token) {
+            if (token) {
                 st = lnmod_backward(ptr(dy), ptr(x), nullptr, ptr(scale), b.n, b.s_or_t, b.D, static_cast<float>(eps),
                                     stream_of(x), f32(mean), f32(rstd), out(dx), out(dshift), out(dscale), nullptr, 0,
                                     code_of(x), LNMOD_PER_TOKEN);

@@ -101,8 +101,8 @@ def test_transforms_are_refused_as_before():
 
 
 @pytest.mark.parametrize("stats", [True, False])
-def test_per_token_shift_gradient_is_handed_on_without_sharing(stats):
-    """dshift is dy; a leaf's .grad must not share memory with a gradient that others still hold."""
+def test_per_token_shift_gradient_is_a_tensor_of_its_own(stats):
+    """dshift equals dy; a leaf's .grad must not share memory with a gradient that others still hold."""
     x, sh, sc = _leaves(torch.bfloat16, (2, 37, 264), (2, 37, 264), (2, 37, 264))
     y = F.ln_modulate(x, sh, sc, save_stats=stats)
     y.retain_grad()
@@ -122,3 +122,35 @@ def test_per_token_shift_gradient_is_handed_on_without_sharing(stats):
     # an expanded gradient
     (got,) = torch.autograd.grad(F.ln_modulate(x, sh, sc, save_stats=stats).sum(), (sh,))
     assert torch.equal(got, torch.ones_like(sh)) and got.is_contiguous()
+
+
+@pytest.mark.parametrize("stats", [True, False])
+def test_per_token_shift_gradient_shares_no_memory_behind_a_view(stats):
+    """A view of y gives the operator a fresh dy over memory that is the caller's."""
+    def leaves():
+        return _leaves(torch.bfloat16, (2, 37, 264), (2, 37, 264), (2, 37, 264))
+
+    dz = torch.randn(74, 264, device="cuda", dtype=torch.bfloat16)
+    keep = dz.clone()
+    for look in (lambda y: y.view(-1, 264), lambda y: y.flatten(0, 1), lambda y: y.reshape(74, 264)):
+        x, sh, sc = leaves()
+        look(F.ln_modulate(x, sh, sc, save_stats=stats)).backward(dz)
+        assert sh.grad.untyped_storage().data_ptr() != dz.untyped_storage().data_ptr()
+        look(F.ln_modulate(x, sh, sc, save_stats=stats)).backward(dz)         # accumulates into sh.grad
+        assert torch.equal(dz, keep) and torch.equal(sh.grad, keep.view_as(sh) * 2)
+    # two operators that receive views of one gradient: each leaf has a .grad of its own
+    (x1, s1, c1), (x2, s2, c2) = leaves(), leaves()
+    both = F.ln_modulate(x1, s1, c1, save_stats=stats).view(-1, 264) + F.ln_modulate(x2, s2, c2, save_stats=stats).view(-1, 264)
+    both.backward(dz)
+    for t in (s1, s2):
+        t.grad.mul_(0.5)
+    for t in (s1, s2):
+        assert torch.equal(t.grad, keep.view_as(t) * 0.5)
+    # the caller's own dy, refilled after the call
+    x, sh, sc = leaves()
+    dy = dz.view(2, 37, 264)
+    got = torch.autograd.grad(F.ln_modulate(x, sh, sc, save_stats=stats), (x, sh, sc), dy)
+    dy.zero_()
+    assert torch.equal(got[1], keep.view_as(sh))
+    got[1].fill_(7)
+    assert not dy.any()
