@@ -167,7 +167,9 @@ int lnmod_backward_static(const void* dy, const void* x, const void* shift, cons
  * Bytes of device workspace the backward needs for its per-block partial sums of
  * dshift/dscale (Sec. 3.3: per-feature accumulation down the sequence; the partials of the
  * blocks are combined by a second, fixed-order kernel).  0 for LNMOD_PER_TOKEN and for invalid
- * arguments.  Host-only, touches no device.
+ * arguments.  Host-only, touches no device.  For one sample (B_or_nseg == 1) the size never falls as
+ * total_tokens grows, so a workspace sized for the longest clip serves every shorter one; with several
+ * samples or segments the launch plan may need more for fewer tokens: query for each problem.
  */
 size_t lnmod_backward_workspace_bytes(int64_t B_or_nseg, int64_t total_tokens, int64_t D, int mod);
 

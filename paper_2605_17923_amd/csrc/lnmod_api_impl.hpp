@@ -33,13 +33,17 @@ inline int64_t total_tokens(int64_t B, int64_t S) {
 
 inline size_t workspace_bytes(int64_t nseg, int64_t T, int64_t D, const Shape* force = nullptr) {
     // partial-sum slots of the plan with the most of them (neither the dtype nor whether the
-    // statistics will be recomputed is an argument of the query)
+    // statistics will be recomputed is an argument of the query).  For one sample the shapes of short and
+    // long launches both count, so that the size never falls as the rows grow: a caller may size its
+    // workspace once, for its longest clip (at D = 6152 ... 6656 a short recompute launch has two blocks per
+    // CU where a long one has one).
     int64_t slots = 0;
     for (int v = 0; v < 4; ++v) {
         const int dtype = v & 1;
         if (D % (dtype == 0 ? 8 : 4) != 0) continue;
         const RowPlan pl = bwd_plan(T, nseg, D, dtype, (v & 2) != 0, force);
-        const int64_t s = bwd_slots(pl, nseg);
+        int64_t s = bwd_slots(pl, nseg);
+        if (nseg == 1 && !force) s = bwd_most_slots_one_sample(T, D, dtype, (v & 2) != 0);
         if (s > slots) slots = s;
     }
     return static_cast<size_t>(slots) * 2u * static_cast<size_t>(D) * sizeof(float);

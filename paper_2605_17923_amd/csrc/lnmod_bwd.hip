@@ -181,6 +181,18 @@ RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, 
     return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
 }
 
+int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute) {
+    if (T <= 0) return 0;
+    const int nchunks = static_cast<int>(D / (dtype == 0 ? 8 : 4));
+    int64_t most = 0;
+    for (int64_t rows = 0; rows <= 1; ++rows) {          // 0: the long table, 1: the short one
+        const Shape sh = recompute ? rc_bwd_shape(nchunks, dtype, rows) : bwd_shape(nchunks, dtype, rows);
+        const int64_t slots = bwd_slots(plan_rows(T, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R), 1);
+        if (slots > most) most = slots;
+    }
+    return most;
+}
+
 bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots, Shape* out) {
     const BwdLaunch own = plan_bwd(T, nseg, D, dtype, false, recompute, nullptr);
     *out = own.sh;

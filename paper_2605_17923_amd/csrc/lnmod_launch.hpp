@@ -549,6 +549,10 @@ inline int64_t bwd_slots(const RowPlan& p, int64_t nseg) {
     return nseg < 1 ? 0 : (p.clusters + nseg - 1) * p.nb;
 }
 
+// Slots of this backward on one sample of T rows with the shape of a short or of a long launch, whichever has more:
+// a bound on the plan's slots that does not fall as T grows.
+int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute);
+
 // For a caller whose workspace cannot grow: the launch shape of this backward whose plan has at most max_slots
 // slots -- the table's own if it has, else the same rows per wave with fewer blocks in a cluster or on a CU.
 // False if there is none.

@@ -30,3 +30,17 @@ def test_static_backward_takes_problems_whose_usual_plan_needs_more(B, S, D, dty
     st = lnmod.lnmod_backward_static(A, A, None, A, B, S, D, 1e-6, None, None if rc else A, None if rc else A, A, A, A,
                                      dtype, lnmod.LNMOD_PER_SAMPLE)
     assert st == lnmod.LNMOD_ELAUNCH
+
+
+def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
+    # a caller sizes its workspace for the longest clip and passes it for shorter ones
+    queries = (lambda T, D: lnmod.lnmod_backward_workspace_bytes(1, T, D, lnmod.LNMOD_PER_SAMPLE),
+               lambda T, D: lnmod.lnmod_gated_backward_workspace_bytes(1, T, D),
+               lambda T, D: lnmod.lnmod_qknorm_backward_workspace_bytes(T, D))
+    for D in range(8, 8193, 8):
+        rows = [1, 2, 100, 255, 256, 257, 511, 512, 513, 767, 1024, 1025, 2048, 4096, 75600, 400000]
+        rows += [72000000 // (16 * n) + k for n in (D // 8, D // 4) for k in (-1, 0, 1, 2)]    # short | long launches
+        rows = sorted(t for t in set(rows) if t > 0)
+        for q in queries:
+            sizes = [q(t, D) for t in rows]
+            assert sizes == sorted(sizes) and sizes[0] > 0, (D, rows, sizes)
