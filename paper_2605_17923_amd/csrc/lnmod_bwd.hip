@@ -144,75 +144,6 @@ hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     return hipGetLastError();
 }
 
-namespace {
-
-// Shape and row plan of a backward launch: what the launcher uses, what sizes the workspace and
-// what describe_bwd() reports.
-struct BwdLaunch {
-    Shape sh;
-    RowPlan pl;
-    int nchunks;
-};
-
-BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool per_token, bool recompute,
-                   const Shape* force, bool writes_dshift = true) {
-    BwdLaunch L;
-    const int E = dtype == 0 ? 8 : 4;
-    L.nchunks = static_cast<int>(D / E);
-    if (per_token) {
-        // (the recompute form keeps shapes of its own: 32 760 x 1536 98 us, 109 with the others)
-        L.sh = pick_shape(force, recompute ? tok_rc_bwd_shape(L.nchunks, dtype)
-                                           : tok_bwd_shape(L.nchunks, dtype, writes_dshift, T));
-        L.pl = plan_rows(T, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R);
-        return L;
-    }
-    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T) : bwd_shape(L.nchunks, dtype, T));
-    // a row moves 3 D elements (dy, x, dx), a slot 2 D floats that are written and read back
-    const double elem = dtype == 0 ? 2.0 : 4.0;
-    const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 3.0 * elem / 5.8e6;
-    L.pl = plan_rows_slots(T, nseg, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R, stream_us,
-                           16.0 / (3.0 * elem), L.sh.clusters);
-    return L;
-}
-
-}  // namespace
-
-RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, const Shape* force) {
-    return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
-}
-
-int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute) {
-    if (T <= 0) return 0;
-    const int nchunks = static_cast<int>(D / (dtype == 0 ? 8 : 4));
-    int64_t most = 0;
-    for (int64_t rows = 0; rows <= 1; ++rows) {          // 0: the long table, 1: the short one
-        const Shape sh = recompute ? rc_bwd_shape(nchunks, dtype, rows) : bwd_shape(nchunks, dtype, rows);
-        const int64_t slots = bwd_slots(plan_rows(T, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R), 1);
-        if (slots > most) most = slots;
-    }
-    return most;
-}
-
-bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots, Shape* out) {
-    const BwdLaunch own = plan_bwd(T, nseg, D, dtype, false, recompute, nullptr);
-    *out = own.sh;
-    if (bwd_slots(own.pl, nseg) <= max_slots) return true;
-    for (int per_cu = own.sh.per_cu; per_cu >= 1; --per_cu) {
-        Shape sh = own.sh;
-        sh.per_cu = per_cu;
-        const int64_t g = grid_blocks(T, static_cast<int64_t>(kNumCU) * per_cu, sh.R);
-        for (int64_t nb = own.pl.nb < g ? own.pl.nb : g; nb >= 1; nb /= 2) {
-            sh.clusters = static_cast<int>(g / nb);
-            sh.interleave = 1;
-            if (bwd_slots(plan_bwd(T, nseg, D, dtype, false, recompute, &sh).pl, nseg) <= max_slots) {
-                *out = sh;
-                return true;
-            }
-        }
-    }
-    return false;
-}
-
 hipError_t launch_bwd_seg(const Problem& p, const void* dy, const void* x, const void* scale,
                           const float* mean, const float* rstd, void* dx, void* dshift,
                           void* dscale, bool io_grads, float* ws, hipStream_t st) {

@@ -17,7 +17,8 @@ struct Shape {
     int VPL;
     int R;
     int per_cu;
-    // Only ever set by a shaped call of the measurement library (the tables leave them 0):
+    // The tables leave these 0; they are set by a shaped call of the measurement library and, clusters and interleave,
+    // by bwd_shape_within:
     int clusters = 0;      // > 0: this many clusters of blocks instead of the plan's choice
     int interleave = 0;    // 1: cluster = block index modulo the cluster count (with 8 clusters every
                            // cluster then sits on one XCD, because consecutive blocks go to the XCDs in
@@ -36,7 +37,8 @@ struct Problem {
     int64_t D;
     float eps;
     // Launch shape to use instead of the measured table's entry, or nullptr.  The operator entry
-    // points always pass nullptr; the measurement library's shaped calls pass the caller's shape,
+    // points pass nullptr, except the backward with the static workspace where the table's plan needs more
+    // slots than that holds; the measurement library's shaped calls pass the caller's shape,
     // per call, so that a sweep can time candidates without any process-wide state.
     const Shape* force = nullptr;
 };
@@ -541,22 +543,83 @@ inline int32_t cluster_split(int interleave, const RowPlan& pl) {
     return interleave ? static_cast<int32_t>(pl.clusters) : pl.nb;
 }
 
-// The backward's plan for this problem: the same function sizes the workspace, drives the main
-// kernel's grid and tells the second pass which partial-sum slots belong to a segment.
-RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, const Shape* force = nullptr);
 // Slot of (cluster c, segment m, member j) is (c + m) * nb + j with c < clusters, m < nseg.
 inline int64_t bwd_slots(const RowPlan& p, int64_t nseg) {
     return nseg < 1 ? 0 : (p.clusters + nseg - 1) * p.nb;
 }
 
+// Shape and row plan of a backward launch: what the launcher uses, what sizes the workspace and
+// what describe_bwd() reports.
+struct BwdLaunch {
+    Shape sh;
+    RowPlan pl;
+    int nchunks;
+};
+
+inline BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool per_token, bool recompute,
+                          const Shape* force, bool writes_dshift = true) {
+    BwdLaunch L;
+    const int E = dtype == 0 ? 8 : 4;
+    L.nchunks = static_cast<int>(D / E);
+    if (per_token) {
+        // (the recompute form keeps shapes of its own: 32 760 x 1536 98 us, 109 with the others)
+        L.sh = pick_shape(force, recompute ? tok_rc_bwd_shape(L.nchunks, dtype)
+                                           : tok_bwd_shape(L.nchunks, dtype, writes_dshift, T));
+        L.pl = plan_rows(T, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R);
+        return L;
+    }
+    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T) : bwd_shape(L.nchunks, dtype, T));
+    // a row moves 3 D elements (dy, x, dx), a slot 2 D floats that are written and read back
+    const double elem = dtype == 0 ? 2.0 : 4.0;
+    const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 3.0 * elem / 5.8e6;
+    L.pl = plan_rows_slots(T, nseg, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R, stream_us,
+                           16.0 / (3.0 * elem), L.sh.clusters);
+    return L;
+}
+
+// The backward's plan for this problem: the same function sizes the workspace, drives the main
+// kernel's grid and tells the second pass which partial-sum slots belong to a segment.
+inline RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, const Shape* force = nullptr) {
+    return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
+}
+
 // Slots of this backward on one sample of T rows with the shape of a short or of a long launch, whichever has more:
 // a bound on the plan's slots that does not fall as T grows.
-int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute);
+inline int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute) {
+    if (T <= 0) return 0;
+    const int nchunks = static_cast<int>(D / (dtype == 0 ? 8 : 4));
+    int64_t most = 0;
+    for (int64_t rows = 0; rows <= 1; ++rows) {          // 0: the long table, 1: the short one
+        const Shape sh = recompute ? rc_bwd_shape(nchunks, dtype, rows) : bwd_shape(nchunks, dtype, rows);
+        const int64_t slots = bwd_slots(plan_rows(T, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R), 1);
+        if (slots > most) most = slots;
+    }
+    return most;
+}
 
 // For a caller whose workspace cannot grow: the launch shape of this backward whose plan has at most max_slots
-// slots -- the table's own if it has, else the same rows per wave with fewer blocks in a cluster or on a CU.
-// False if there is none.
-bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots, Shape* out);
+// slots -- the table's own if it has, else the same rows per wave with fewer blocks in a cluster or on a CU, always in
+// clusters of every C-th block.  False if there is none.
+inline bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool recompute, int64_t max_slots,
+                             Shape* out) {
+    const BwdLaunch own = plan_bwd(T, nseg, D, dtype, false, recompute, nullptr);
+    *out = own.sh;
+    if (bwd_slots(own.pl, nseg) <= max_slots) return true;
+    for (int per_cu = own.sh.per_cu; per_cu >= 1; --per_cu) {
+        Shape sh = own.sh;
+        sh.per_cu = per_cu;
+        const int64_t g = grid_blocks(T, static_cast<int64_t>(kNumCU) * per_cu, sh.R);
+        for (int64_t nb = own.pl.nb < g ? own.pl.nb : g; nb >= 1; nb /= 2) {
+            sh.clusters = static_cast<int>(g / nb);
+            sh.interleave = 1;
+            if (bwd_slots(plan_bwd(T, nseg, D, dtype, false, recompute, &sh).pl, nseg) <= max_slots) {
+                *out = sh;
+                return true;
+            }
+        }
+    }
+    return false;
+}
 
 // Shape of the second pass: V features per lane, W waves per block, G groups of lanes per wave
 // that take different slots (a block covers 64 / G * V features).  Wide blocks need enough

@@ -69,6 +69,37 @@ int main() {
             CHECK(wide == 0 || p + 1e-12 >= cluster_penalty(C, false), "one block per CU pays less at %lld", (long long)C);
         }
     }
+    // the backward for a workspace that cannot grow: whatever shape is found, its plan (the one the launcher makes
+    // from that shape) stays within the slots asked for, covers the rows and keeps the rows per wave and step
+    int fallbacks = 0, odd = 0;
+    for (int it = 0; it < 200000; ++it) {
+        const int dtype = it & 1, E = dtype == 0 ? 8 : 4;
+        const bool rc = (it & 2) != 0;
+        const int64_t D = E * (8 / E + static_cast<int64_t>(rng() % static_cast<uint64_t>(kMaxD / E - 1)));
+        const int64_t nseg = 1 + static_cast<int64_t>(rng() % (it % 3 == 0 ? 4000 : 200));
+        const int64_t T = nseg * (1 + static_cast<int64_t>(rng() % (it % 5 == 0 ? 20000 : 600)));
+        if (T >= (int64_t(1) << 31)) continue;
+        const int64_t most = static_cast<int64_t>(kStaticWorkspaceBytes / (8 * static_cast<size_t>(D)));
+        const BwdLaunch own = plan_bwd(T, nseg, D, dtype, false, rc, nullptr);
+        Shape sh{};
+        if (!bwd_shape_within(T, nseg, D, dtype, rc, most, &sh)) {
+            CHECK(bwd_slots(own.pl, nseg) > most, "T %lld nseg %lld D %lld refused but fits", (long long)T, (long long)nseg, (long long)D);
+            // one block per CU, every block a cluster of its own: kNumCU + nseg - 1 slots
+            CHECK(nseg + kNumCU - 1 > most, "T %lld nseg %lld D %lld refused, %lld slots would do", (long long)T, (long long)nseg, (long long)D, (long long)most);
+            continue;
+        }
+        CHECK(sh.K == own.sh.K && sh.VPL == own.sh.VPL && sh.R == own.sh.R && sh.per_cu <= own.sh.per_cu, "shape T %lld D %lld", (long long)T, (long long)D);
+        if (sh.clusters == 0) continue;                     // the table's own plan
+        const BwdLaunch L = plan_bwd(T, nseg, D, dtype, false, rc, &sh);
+        check_plan("bwd_shape_within", L.pl, T, grid_blocks(T, int64_t(kNumCU) * sh.per_cu, sh.R));
+        CHECK(bwd_slots(L.pl, nseg) <= most, "T %lld nseg %lld D %lld: %lld slots, %lld fit", (long long)T, (long long)nseg, (long long)D, (long long)bwd_slots(L.pl, nseg), (long long)most);
+        const int32_t split = cluster_split(cluster_interleave(&sh, L.pl), L.pl);
+        // place_of: block b is member b / split of cluster b % split
+        CHECK((L.pl.blocks - 1) / split < L.pl.nb && split == L.pl.clusters, "T %lld: a block beyond its cluster", (long long)T);
+        ++fallbacks;
+        odd += L.pl.clusters % 2 != 0;
+    }
+    CHECK(fallbacks > 1000 && odd > 100, "%d fallbacks, %d with an odd cluster count", fallbacks, odd);
     // the plans the cost model was fitted to (D = 5120: 256 blocks, rows of 30 KB traffic)
     {
         const struct { int64_t T, nseg, clusters; } fit[] = {{152880, 24, 4}, {152880, 8, 2}, {149760, 96, 8},

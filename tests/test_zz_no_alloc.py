@@ -1,10 +1,12 @@
 """GPU test of lnmod_backward_static, the backward entry point that allocates nothing: through the
 C ABI, against lnmod_backward (same kernels and plan, so the results must be the same bits), on two
-calls in a row, the second with a smaller input; the library must not allocate device memory."""
+calls in a row, the second with a smaller input; the library must not allocate device memory.  Where
+lnmod_backward's plan needs more slots than the static array holds, a plan of fewer blocks runs instead: dx
+is still the same bits, dshift and dscale are sums in another order, checked against float64."""
 import pytest
 import torch
 
-from paper_2605_17923_amd import lnmod, synth
+from paper_2605_17923_amd import lnmod, lnmod_tools as T, synth
 from parity_util import to_device
 
 pytestmark = pytest.mark.gpu
@@ -88,3 +90,28 @@ def test_headline_workload_fits_and_too_many_slots_are_refused():
     assert lnmod.lnmod_backward_static(A, A, None, A, 3000, 40, 8192, 1e-6, st, A, A, A, A, A, lnmod.LNMOD_BF16,
                                        lnmod.LNMOD_PER_SAMPLE) == lnmod.LNMOD_EWORKSPACE
     torch.cuda.synchronize()
+
+
+# (B, S, D, dtype, recompute): lnmod_backward's plan is beyond the array; the last two get 127 clusters, an odd count
+@pytest.mark.parametrize("B,S,D,dtype,rc", [(17, 5276, 5768, "bf16", True), (188, 352, 3840, "bf16", True),
+                                            (471, 127, 3824, "f32", True), (146, 348, 3832, "f32", True),
+                                            (419, 165, 3936, "f32", False), (123, 4572, 1080, "bf16", True),
+                                            (232, 31, 7628, "f32", True), (302, 29, 6812, "f32", False)])
+def test_plan_of_fewer_blocks_where_the_usual_one_does_not_fit(B, S, D, dtype, rc):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = lnmod.LNMOD_BF16 if dtype == "bf16" else lnmod.LNMOD_F32
+    usual = T.lnmod_describe_launch(1, None, B, S, False, D, code, lnmod.LNMOD_PER_SAMPLE, rc)
+    assert int(usual.split("slots=")[1]) * 2 * D * 4 > lnmod.LNMOD_STATIC_WORKSPACE_BYTES
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B)
+    x, dy = (torch.randn(B, S, D, generator=g, device="cuda").to(dt) for _ in range(2))
+    scale = (torch.randn(B, D, generator=g, device="cuda") * 0.3).to(dt)
+    ref, got = _both(x, dy, torch.zeros_like(scale), scale, False, rc)
+    _same(ref[:1], got[:1], "fewer blocks")
+    for b0 in range(0, B, 64):                        # sums of at most 5276 fp32 products, in any order
+        xd, d = x[b0:b0 + 64].double(), dy[b0:b0 + 64].double()
+        c = xd - xd.mean(-1, keepdim=True)
+        want = (d.sum(1), (d * c * (c.square().mean(-1, keepdim=True) + 1e-6).rsqrt()).sum(1))
+        for name, a, w in zip(("dshift", "dscale"), got[1:], want):
+            err = float((a[b0:b0 + 64].double() - w).norm() / w.norm())
+            assert err <= 1e-5, "%s: relative error %.2e" % (name, err)
