@@ -56,6 +56,7 @@ int gated_backward_impl(const void* dy, const void* dh, const void* h, const voi
     if (T == 0) {
         if (B_or_nseg > 0) {                                  // empty sums are zeros
             if (!dgate || !dshift || !dscale) return LNMOD_EINVAL;
+            if (io_grads && (!aligned16(dgate) || !aligned16(dshift) || !aligned16(dscale))) return LNMOD_EALIGN;
             const auto zero = [&](void* p) {
                 return lnmod::launch_zero_f32(static_cast<float*>(p), grad_floats(B_or_nseg * D, dtype, io_grads), hs);
             };

@@ -207,6 +207,22 @@ def test_gated_rejects_bad_arguments(lib):
     assert gbwd(n=0, s=0) == E.LNMOD_OK
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_gradients_in_the_io_type_are_aligned_without_rows_too(lib, dtype):
+    # no rows: the sums are zeros, written four bytes at a time also where the elements are of two
+    E = lnmod
+    for k in range(3):
+        g = [A, A, A]
+        g[k] = A + 2
+        assert lnmod.lnmod_gated_backward_io(A, A, A, A, A, A, None, 2, 0, 64, 1e-6, None, A, A, A, A, g[0], g[1],
+                                             g[2], A, 1 << 40, dtype) == E.LNMOD_EALIGN
+    for k in range(2):
+        assert lnmod.lnmod_backward_io(A, A, A, None, 2, 0, 64, 1e-6, None, A, A, A, A + 2 * (k == 0), A + 2 * (k == 1),
+                                       A, 1 << 40, dtype) == E.LNMOD_EALIGN
+        assert lnmod.lnmod_qknorm_backward_io(A, A, A, A, A, A, 0, 64, 1e-6, None, A, A, A, A, A + 2 * (k == 0),
+                                              A + 2 * (k == 1), A, 1 << 40, dtype) == E.LNMOD_EALIGN
+
+
 def test_gated_workspace_query(lib):
     q = lnmod.lnmod_gated_backward_workspace_bytes
     assert q(-1, 10, 64) == 0 and q(1, -1, 64) == 0 and q(1, 10, 66) == 0
