@@ -88,11 +88,23 @@ def _link(target: str, objs, force: bool) -> None:
     os.replace(tmp, target)
 
 
+def _torch_stamp() -> str:
+    """File that changes when torch does: the module is only good for the torch whose headers it was built with."""
+    import torch
+    path = os.path.join(BUILD_DIR, "torch.stamp")
+    text = "%s %s %s\n" % (torch.__version__, sys.version, os.path.dirname(torch.__file__))
+    old = open(path).read() if os.path.exists(path) else None
+    if old != text:
+        with open(path, "w") as f:
+            f.write(text)
+    return path
+
+
 def _compile_torch(force: bool) -> str:
     """Object of the host-only extension module (needs torch's headers, not its build tools)."""
+    import torch
     src, obj = os.path.join(CSRC, "lnmod_torch.cpp"), os.path.join(BUILD_DIR, "lnmod_torch.o")
-    if force or _stale(obj, [src, os.path.join(INCLUDE, "lnmod.h")]):
-        import torch
+    if force or _stale(obj, [src, os.path.join(INCLUDE, "lnmod.h"), _torch_stamp()]):
         inc = os.path.join(os.path.dirname(torch.__file__), "include")
         dirs = [INCLUDE, inc, os.path.join(inc, "torch", "csrc", "api", "include"), os.path.join(ROCM, "include"),
                 sysconfig.get_paths()["include"]]

@@ -18,6 +18,7 @@
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPFunctions.h>
+#include <torch/version.h>
 
 #include "lnmod.h"
 
@@ -348,6 +349,7 @@ py::object qk_norm(const py::object& q, const py::object& k, const py::object& w
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
     m.doc() = "Host path of the lnmod operators; every function returns None for a call it leaves to the Python path.";
+    m.attr("built_for") = TORCH_VERSION;
     m.def("forward", &forward);
     m.def("ln_modulate", &ln_modulate);
     m.def("gated_ln_modulate", &gated_ln_modulate);

@@ -95,18 +95,29 @@ def library() -> ctypes.CDLL:
 
 def native():
     """The host path in C++ (_lnmod_torch.so), or None while torch.compile traces (which leaves the Python
-    path, as every call does for which one of the module's functions returns None)."""
+    path, as every call does for which one of the module's functions returns None) and where the module was
+    built for another torch: the kernels' library does not depend on torch, so those calls run too, with a
+    warning."""
     global _native
     import torch
-    if torch.compiler.is_compiling():
+    if torch.compiler.is_compiling() or _native is False:
         return None
     if _native is None:
         library()
         if not os.path.exists(TORCH_MODULE):
             raise RuntimeError("_lnmod_torch.so is not built (run `python -m paper_2605_17923_amd.build` "
                                "or __graft_entry__.build())")
-        from . import _lnmod_torch
-        _native = _lnmod_torch
+        try:
+            from . import _lnmod_torch as module
+            if module.built_for != torch.__version__.split("+")[0]:
+                raise ImportError("built for torch %s, this is %s" % (module.built_for, torch.__version__))
+        except ImportError as e:
+            import warnings
+            warnings.warn("_lnmod_torch.so is not usable (%s): calls take the slower Python host path; run "
+                          "`python -m paper_2605_17923_amd.build`" % e, RuntimeWarning)
+            _native = False
+            return None
+        _native = module
     return _native
 
 
