@@ -12,6 +12,7 @@
 // their arguments and the saved tensors with their order are the same either way.
 #include <torch/extension.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_cpp_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <torch/csrc/jit/frontend/tracer.h>
 #include <ATen/hip/impl/HIPStreamMasqueradingAsCUDA.h>
@@ -345,11 +346,39 @@ py::object qk_norm(const py::object& q, const py::object& k, const py::object& w
     });
 }
 
+// ---- what y.grad_fn shows --------------------------------------------------------------------------------------
+// The node's Python type, with the saved tensors that the Python classes' nodes show (the same ones in the same order,
+// None where nothing was saved; an error once the backward has freed them).
+template <typename Op>
+PyObject* saved_tensors(PyObject* self, void*) {
+    HANDLE_TH_ERRORS
+    auto& node = static_cast<torch::autograd::CppNode<Op>&>(*reinterpret_cast<torch::autograd::THPCppFunction*>(self)->cdata);
+    const variable_list saved = node.ctx_.get_saved_variables();
+    py::tuple t(saved.size());
+    for (size_t i = 0; i < saved.size(); ++i) t[i] = to_python(saved[i]);
+    return t.release().ptr();
+    END_HANDLE_TH_ERRORS
+}
+
+template <typename Op>
+void register_node(const char* name) {
+    using namespace torch::autograd;                   // the property macro names functions of it
+    static PyTypeObject type;
+    static PyGetSetDef properties[] = {THP_FUNCTION_DEFAULT_PROPERTIES,
+                                       {"saved_tensors", saved_tensors<Op>, nullptr, nullptr, nullptr},
+                                       {nullptr, nullptr, nullptr, nullptr, nullptr}};
+    if (!_initFunctionPyTypeObject(type, name, properties, nullptr)) throw py::error_already_set();
+    registerCppFunction(typeid(CppNode<Op>), &type);
+}
+
 }  // namespace
 
 PYBIND11_MODULE(TORCH_EXTENSION_NAME, m) {
     m.doc() = "Host path of the lnmod operators; every function returns None for a call it leaves to the Python path.";
     m.attr("built_for") = TORCH_VERSION;
+    register_node<LnModulate>("LnModulateBackward");
+    register_node<GatedLnModulate>("GatedLnModulateBackward");
+    register_node<QkNorm>("QkNormBackward");
     m.def("forward", &forward);
     m.def("ln_modulate", &ln_modulate);
     m.def("gated_ln_modulate", &gated_ln_modulate);

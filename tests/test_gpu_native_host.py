@@ -63,6 +63,34 @@ def test_same_results_as_the_python_path(op, dtype):
         assert not (out[0] if isinstance(out, tuple) else out).requires_grad
 
 
+@pytest.mark.parametrize("op", ["sample", "token", "recompute", "packed", "gated", "gated packed", "qk"])
+def test_nodes_show_the_saved_tensors(op):
+    """y.grad_fn.saved_tensors: what the Python path's node shows, also through hooks; gone after the backward."""
+    native, python, ts = _case(op, torch.bfloat16)
+
+    def node(call):
+        out = call(*ts)
+        return (out[0] if isinstance(out, tuple) else out).grad_fn, out
+
+    (a, out), (b, ref) = node(native), node(python)
+    assert type(a) is not type(b) and len(a.next_functions) == len(b.next_functions) and a.name()
+    assert len(a.saved_tensors) == len(b.saved_tensors) >= 5
+    for u, v in zip(a.saved_tensors, b.saved_tensors):
+        assert (u is None) == (v is None)
+        assert u is None or (u.shape == v.shape and torch.equal(u, v))
+    with torch.autograd.graph.save_on_cpu():
+        held, kept = node(native)
+    for u, v in zip(held.saved_tensors, b.saved_tensors):
+        assert u is None or torch.equal(u, v)
+    del ref, kept                                      # (a node without its output has nothing saved any more)
+    seen = []
+    a.register_hook(lambda *g: seen.append(len(g)))
+    sum(o.float().sum() for o in (out if isinstance(out, tuple) else (out,))).backward()
+    assert seen == [2]
+    with pytest.raises(RuntimeError):
+        a.saved_tensors
+
+
 def test_plain_forward_matches_the_python_path():
     x, sh, sc = (t.detach() for t in _leaves(torch.bfloat16, (2, 37, 264), (2, 264), (2, 264)))
     for u, v in zip(lnmod.forward(x, sh, sc), lnmod.forward(x, sh, sc, stream=torch.cuda.current_stream())):
