@@ -30,6 +30,13 @@ void go_seg(const BwdArgs& a, int R, int64_t blocks, hipStream_t st) {
     }
 }
 
+// The per-token form with saved statistics.
+template <typename Tag, int VPL, int K>
+void go_saved(const BwdArgs& a, int R, int64_t blocks, hipStream_t st) {
+    if (R == 1) go_seg_rc<Tag, VPL, K, 1, true, false>(a, blocks, st);
+    else go_seg_rc<Tag, VPL, K, 2, true, false>(a, blocks, st);
+}
+
 // Every (VPL, K) the shape table, the fp32 rule and the per-token rule can ask for.
 template <typename Tag, bool TOK>
 bool dispatch_seg(const BwdArgs& a, int VPL, int K, int R, int64_t blocks, hipStream_t st) {
@@ -50,13 +57,13 @@ bool dispatch_seg(const BwdArgs& a, int VPL, int K, int R, int64_t blocks, hipSt
             default: break;
         }
     }
-    if constexpr (IO<Tag>::E == 8 && TOK) {              // without the copy of dy
+    if constexpr (IO<Tag>::E == 8 && TOK) {              // per token, with saved statistics only
+        if (a.mean == nullptr) return false;
         switch (VPL * 100 + K) {
-            case 103: go_seg<Tag, 1, 3, TOK>(a, R, blocks, st); return true;
-            case 104: go_seg<Tag, 1, 4, TOK>(a, R, blocks, st); return true;
-            case 106: go_seg<Tag, 1, 6, TOK>(a, R, blocks, st); return true;
-            case 108: go_seg<Tag, 1, 8, TOK>(a, R, blocks, st); return true;
-            case 304: go_seg<Tag, 3, 4, TOK>(a, R, blocks, st); return true;
+            case 103: go_saved<Tag, 1, 3>(a, R, blocks, st); return true;
+            case 104: go_saved<Tag, 1, 4>(a, R, blocks, st); return true;
+            case 108: go_saved<Tag, 1, 8>(a, R, blocks, st); return true;
+            case 304: go_saved<Tag, 3, 4>(a, R, blocks, st); return true;
             default: break;
         }
     }
@@ -191,8 +198,10 @@ hipError_t launch_bwd_tok(const Problem& p, const void* dy, const void* x, const
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
     a.split = cluster_split(0, pl);
-    const bool ok = p.dtype == 0 ? dispatch_seg<bf16_io, true>(a, sh.VPL, sh.K, sh.R, pl.blocks, st)
-                                 : dispatch_seg<f32_io, true>(a, sh.VPL, sh.K, sh.R, pl.blocks, st);
+    const auto run = [&](auto tag) { return dispatch_seg<decltype(tag), true>(a, sh.VPL, sh.K, sh.R, pl.blocks, st); };
+    bool ok;
+    if (dshift != nullptr) ok = p.dtype == 0 ? run(bf16_io{}) : run(f32_io{});
+    else ok = p.dtype == 0 ? run(bf16_io_no_dshift{}) : run(f32_io_no_dshift{});
     return ok ? hipGetLastError() : hipErrorInvalidConfiguration;
 }
 
