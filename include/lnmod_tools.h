@@ -88,11 +88,13 @@ typedef enum {
     LNMOD_FAMILY_BACKWARD = 1,            /* lnmod_backward / _varlen with saved statistics          */
     LNMOD_FAMILY_BACKWARD_RECOMPUTE = 2,  /* the same without saved statistics                       */
     LNMOD_FAMILY_TOKEN_FORWARD = 3,       /* LNMOD_PER_TOKEN forward                                 */
-    LNMOD_FAMILY_TOKEN_BACKWARD = 4,      /* LNMOD_PER_TOKEN backward                                */
+    LNMOD_FAMILY_TOKEN_BACKWARD = 4,      /* LNMOD_PER_TOKEN backward with saved statistics          */
     LNMOD_FAMILY_GATED_FORWARD = 5,       /* lnmod_gated_forward                                     */
     LNMOD_FAMILY_GATED_BACKWARD = 6,      /* lnmod_gated_backward                                    */
     LNMOD_FAMILY_QKNORM_FORWARD = 7,      /* lnmod_qknorm_forward, rows wider than one head          */
-    LNMOD_FAMILY_QKNORM_BACKWARD = 8      /* lnmod_qknorm_backward, rows wider than one head         */
+    LNMOD_FAMILY_QKNORM_BACKWARD = 8,     /* lnmod_qknorm_backward, rows wider than one head         */
+    LNMOD_FAMILY_TOKEN_BACKWARD_RECOMPUTE = 9,   /* LNMOD_PER_TOKEN backward without saved statistics */
+    LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT = 10   /* lnmod_backward_token with saved statistics        */
 } lnmod_family;
 
 /* The shape a family's measured table gives for rows of D elements of `dtype` and (where the entry

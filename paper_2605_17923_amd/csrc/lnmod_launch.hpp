@@ -503,12 +503,15 @@ inline Shape tok_bwd_shape(int nchunks, int dtype, bool writes_dshift = true, in
             {6, 2, 1, 2}, {5, 2, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};
         const int cols = (nchunks + 63) / 64;
-        if (unaligned_rows(nchunks) && (cols == 7 || cols == 8)) {           // D = 3704, 4008, five streams,
-            if (!writes_dshift) return {4, 2, 2, 2};                         // 200 MB: 184 against 209 us
+        const bool few = T > 0 && T * nchunks * 8 <= (int64_t(32) << 20);
+        // D = 3336 ... 4088 beyond short launches (110 and 250 MB): 0.86 to 1.0 of the time with five streams, at six
+        // 2 % faster to 8 % slower, but the same waves and chunks as five.  On 10 and 48 MB it lost 0 to 13 % at
+        // every width from 3088 on, and below 3336 1 to 5 % at any size.
+        if (unaligned_rows(nchunks) && !few && nchunks > 416 && nchunks <= 512) {
+            if (!writes_dshift) return {4, 2, 2, 2};
             return {4, 2, 1, cols == 7 ? 2 : 1};
         }
         if (writes_dshift) return table_entry(six, nchunks, dtype);
-        const bool few = T > 0 && T * nchunks * 8 <= (int64_t(32) << 20);
         return few ? table_entry(five_short, nchunks, dtype) : table_entry(five, nchunks, dtype);
     }
     static const Shape six32[17] = {

@@ -103,7 +103,7 @@ int lnmod_gate_residual(const void* x, const void* u, const void* gate, int64_t 
 }
 
 int lnmod_table_shape(int family, int64_t D, int dtype, int64_t tokens, int* out) {
-    if (family < LNMOD_FAMILY_FORWARD || family > LNMOD_FAMILY_QKNORM_BACKWARD || !out) return LNMOD_EINVAL;
+    if (family < LNMOD_FAMILY_FORWARD || family > LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT || !out) return LNMOD_EINVAL;
     if (dtype != LNMOD_BF16 && dtype != LNMOD_F32) return LNMOD_EINVAL;
     const int64_t vec = dtype == LNMOD_BF16 ? 8 : 4;
     if (D < 8 || D > lnmod::kMaxD || D % vec != 0) return LNMOD_EUNSUPPORTED;
@@ -115,7 +115,9 @@ int lnmod_table_shape(int family, int64_t D, int dtype, int64_t tokens, int* out
         case LNMOD_FAMILY_BACKWARD: sh = lnmod::bwd_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_BACKWARD_RECOMPUTE: sh = lnmod::rc_bwd_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_TOKEN_FORWARD: sh = lnmod::tok_fwd_shape(nchunks, dtype); break;
-        case LNMOD_FAMILY_TOKEN_BACKWARD: sh = lnmod::tok_bwd_shape(nchunks, dtype); break;
+        case LNMOD_FAMILY_TOKEN_BACKWARD: sh = lnmod::tok_bwd_shape(nchunks, dtype, true, T); break;
+        case LNMOD_FAMILY_TOKEN_BACKWARD_RECOMPUTE: sh = lnmod::tok_rc_bwd_shape(nchunks, dtype); break;
+        case LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT: sh = lnmod::tok_bwd_shape(nchunks, dtype, false, T); break;
         case LNMOD_FAMILY_GATED_FORWARD: sh = lnmod::gated_fwd_table_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_GATED_BACKWARD: sh = lnmod::gated_bwd_table_shape(nchunks, dtype); break;
         case LNMOD_FAMILY_QKNORM_FORWARD: sh = lnmod::qknorm_table_shape(nchunks, dtype, false, T); break;

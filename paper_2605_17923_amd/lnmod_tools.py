@@ -20,8 +20,9 @@ EXPORTS = ("lnmod_copy", "lnmod_stream_probe", "lnmod_unfused_forward", "lnmod_g
 # lnmod_family of include/lnmod_tools.h
 (LNMOD_FAMILY_FORWARD, LNMOD_FAMILY_BACKWARD, LNMOD_FAMILY_BACKWARD_RECOMPUTE,
  LNMOD_FAMILY_TOKEN_FORWARD, LNMOD_FAMILY_TOKEN_BACKWARD, LNMOD_FAMILY_GATED_FORWARD,
- LNMOD_FAMILY_GATED_BACKWARD, LNMOD_FAMILY_QKNORM_FORWARD, LNMOD_FAMILY_QKNORM_BACKWARD) = range(9)
-LNMOD_FAMILIES = 9
+ LNMOD_FAMILY_GATED_BACKWARD, LNMOD_FAMILY_QKNORM_FORWARD, LNMOD_FAMILY_QKNORM_BACKWARD,
+ LNMOD_FAMILY_TOKEN_BACKWARD_RECOMPUTE, LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT) = range(11)
+LNMOD_FAMILIES = 11
 
 # read/write mixtures lnmod_stream_probe is compiled for
 PROBE_MIXTURES = ((1, 0), (0, 1), (1, 1), (2, 1), (2, 2), (3, 1), (3, 3), (4, 2))

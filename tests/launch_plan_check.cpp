@@ -37,7 +37,13 @@ int main() {
             check_shape("bwd", dtype, D, n, bwd_shape(n, dtype));
             check_shape("rc_bwd", dtype, D, n, rc_bwd_shape(n, dtype));
             check_shape("tok_fwd", dtype, D, n, tok_fwd_shape(n, dtype));
-            check_shape("tok_bwd", dtype, D, n, tok_bwd_shape(n, dtype));
+            check_shape("tok_rc_bwd", dtype, D, n, tok_rc_bwd_shape(n, dtype));
+            for (const int64_t T : {int64_t(0), int64_t(1), int64_t(300), int64_t(20000), int64_t(1000000)}) {
+                const Shape six = tok_bwd_shape(n, dtype, true, T), five = tok_bwd_shape(n, dtype, false, T);
+                check_shape("tok_bwd", dtype, D, n, six);
+                check_shape("tok_bwd without dshift", dtype, D, n, five);
+                CHECK(six.K == five.K && six.VPL == five.VPL, "dtype %d D %d T %lld: the two add a row in another order", dtype, D, (long long)T);
+            }
         }
     }
     std::mt19937_64 rng(7);

@@ -44,3 +44,17 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
         for q in queries:
             sizes = [q(t, D) for t in rows]
             assert sizes == sorted(sizes) and sizes[0] > 0, (D, rows, sizes)
+
+
+# (family, D, dtype, rows, (waves, chunks per lane, rows per step, blocks per CU)): both sides of the lines where a width
+# below the one that its table entry was timed at, another alignment or another size wants another shape
+@pytest.mark.parametrize("family,D,dtype,rows,shape", [
+    # per token: rows that are not whole lines, beyond short launches, from D = 3336 on
+    (T.LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT, 3704, 0, 40000, (4, 2, 2, 2)),
+    (T.LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT, 3704, 0, 5000, (8, 1, 1, 2)),
+    (T.LNMOD_FAMILY_TOKEN_BACKWARD, 4008, 0, 5000, (8, 1, 1, 1)),
+    (T.LNMOD_FAMILY_TOKEN_BACKWARD, 3208, 0, 40000, (8, 1, 1, 2)),
+    (T.LNMOD_FAMILY_TOKEN_BACKWARD, 3400, 0, 40000, (4, 2, 1, 2)),
+])
+def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
+    assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
