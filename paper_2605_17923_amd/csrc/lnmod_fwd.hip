@@ -106,6 +106,10 @@ bool dispatch(const FwdArgs& a, int VPL, int K, int R, int64_t blocks, hipStream
 // Segments of at most 1024 rows in the mean: most steps of a block of a flat launch then change segment.
 bool many_short(const Problem& p) { return p.nseg > 1 && p.T <= 1024 * p.nseg; }
 
+// x beyond 200 MB: between the short tables' line (72 MB) and here a flat launch on short segments still gains from
+// the short tables' blocks, beyond it the windows of the long tables' blocks count for more.
+bool large_launch(const Problem& p, int nchunks) { return p.T * nchunks * 16 > 200000000; }
+
 // Whether a forward with one modulation row per sample / segment runs one loop over all rows of a
 // block's region (kModFlat) or one loop per segment (kModSegment).  With several segments the flat
 // loop wins wherever few blocks share a CU, because a block that drains its pipeline at a segment's
@@ -130,9 +134,12 @@ bool fwd_flat(const Problem& p) {
 // block at most 32 segments (D = 5120: 2, 4, 8 clusters best on 24, 96, 480 segments of 150 000 rows), or
 // at most 8 where three or more blocks share a CU and either the launch is short or most steps change segment
 // (96 segments, 52 000 rows: D = 1536 67.5 -> 61.8 us together with the blocks of the short table, 3072
-// 129 -> 123; 200 segments of 490 rows at D = 3072 233 -> 226).
+// 129 -> 123; 200 segments of 490 rows at D = 3072 233 -> 226).  Large launches at D = 1536 keep 32 (segments of 500
+// and 900 rows, 360 and 480 MB: 1 to 7 % slower with 8).
 int64_t flat_clusters(const Problem& p, int per_cu) {
-    const bool few = per_cu > 2 && (many_short(p) || short_launch(p.T, static_cast<int>(p.D / (p.dtype == 0 ? 8 : 4))));
+    const int nchunks = static_cast<int>(p.D / (p.dtype == 0 ? 8 : 4));
+    const bool few = per_cu > 2 && (short_launch(p.T, nchunks) ||
+                                    (many_short(p) && !(nchunks == 192 && large_launch(p, nchunks))));
     int64_t c = 2;
     while (c < 32 && p.nseg > (few ? 8 : 32) * c) c *= 2;
     return c;
@@ -145,6 +152,25 @@ struct FwdLaunch {
     int nchunks;
 };
 
+// Shape of a flat bf16 launch on many short segments, rows of one wave (D <= 1536); tab is the one for its token
+// count.  The reload of one block hides behind the others of its CU, so as many, smaller blocks as a short launch has,
+// where that measured better than tab.  From 17 widths, 85 to 480 MB, segments of 100 to 900 rows in the mean, as a
+// share of the time with the loop per segment (D = 1536: flat, tab) that stood here before either rule:
+//   D <= 768   the entry with its two rows per step: 0.41 ... 1.00 (one row: up to 1.07 at D = 512)
+//   D <= 1024  the entry with one row: 0.58 ... 0.98, but 1.02 ... 1.07 on large launches with segments of 500 rows and
+//              more, where tab takes 0.96 ... 1.03
+//   D <= 1280  tab: 0.87 ... 1.00 (the entry: up to 1.06), except on segments of 100 rows: 0.74 against 0.70
+//   D <  1536  the entry with one row: 0.74 ... 1.04 (tab: up to 1.22)
+//   D = 1536   the entry with one row: 0.85 ... 1.02; tab on large launches (the entry there: up to 1.07)
+Shape many_short_shape(const Problem& p, int nchunks, Shape tab) {
+    Shape sh = fwd_short_entry(nchunks);
+    if (nchunks <= 96) return one_step(sh, p.T);
+    sh.R = 1;
+    if (nchunks <= 128) return large_launch(p, nchunks) && p.T > 384 * p.nseg ? tab : sh;
+    if (nchunks <= 160) return p.T > 192 * p.nseg ? tab : sh;
+    return nchunks == 192 && large_launch(p, nchunks) ? tab : sh;
+}
+
 FwdLaunch plan_fwd(const Problem& p, int mode) {
     FwdLaunch L;
     const int E = p.dtype == 0 ? 8 : 4;
@@ -156,9 +182,12 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
         // D = 1536, flat: four blocks per CU at every token count (24 mixed segments, 152 880 rows:
         // 159 us against 182 with three)
         if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0 && !short_launch(p.T, L.nchunks)) tab.per_cu = 4;
-        // rows of one wave whose segments change at most steps: the reload of one block hides behind the
-        // others of the CU, so as many as a short launch has (200 segments of 490 rows at D = 1536 117.3 -> 115.5)
-        if (mode == kModFlat && L.nchunks <= 192 && many_short(p)) tab = fwd_shape(L.nchunks, p.dtype, 1);
+        if (mode == kModFlat && L.nchunks <= 192 && p.dtype == 0 && many_short(p)) tab = many_short_shape(p, L.nchunks, tab);
+        // short launches at D = 5184 ... 5376, aligned: on one to six segments the entry (see fwd_short_entry), on more of
+        // them six blocks per CU (20 segments, 30 MB: 16.4 us against 19.2; 3 segments, 64 MB 29.1 against 26.8)
+        if (mode == kModFlat && p.dtype == 0 && p.nseg >= 8 && L.nchunks > 640 && L.nchunks <= 672 &&
+            !unaligned_rows(L.nchunks) && short_launch(p.T, L.nchunks))
+            tab = {4, 3, 2, 6};
         sh = pick_shape(p.force, tab);
     }
     if ((mode == kLnOnly || mode == kModOnly) && p.dtype == 0) {

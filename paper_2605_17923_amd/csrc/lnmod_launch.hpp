@@ -263,6 +263,22 @@ inline Shape one_step(Shape sh, int64_t T) {
     return sh;
 }
 
+// bf16 forward, short launches: the table's entry as it stands, before one_step.  (D = 5128 ... 5376: two blocks of one
+// row, 0.81 to 1.0 of the time of six blocks of two rows on one sample of 8 to 65 MB.)
+inline Shape fwd_short_entry(int nchunks) {
+    static const Shape tab_short[33] = {
+        {1, 1, 2, 16},
+        {1, 1, 2, 16}, {1, 1, 2, 16}, {1, 2, 2, 16}, {1, 2, 2, 12},   // D <= 1024
+        {1, 3, 1, 12}, {1, 3, 2, 8}, {2, 2, 2, 8}, {2, 2, 1, 8},   // D <= 2048
+        {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 12},   // D <= 3072
+        {4, 2, 1, 4}, {4, 2, 1, 3}, {4, 2, 2, 3}, {4, 2, 2, 2},   // D <= 4096
+        {4, 3, 2, 3}, {4, 3, 1, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 5120
+        {4, 3, 1, 2}, {4, 3, 1, 3}, {4, 3, 2, 2}, {4, 3, 1, 2},   // D <= 6144
+        {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2},   // D <= 7168
+        {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};   // D <= 8192
+    return fine_entry(tab_short, nchunks, 0);
+}
+
 // T: the token count if known (0: not known, a long launch).
 inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
     if (dtype == 0) {
@@ -276,22 +292,8 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 2, 2}, {5, 3, 1, 1}, {5, 3, 1, 1},   // D <= 7168
             {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
-        static const Shape tab_short[33] = {
-            {1, 1, 2, 16},
-            {1, 1, 2, 16}, {1, 1, 2, 16}, {1, 2, 2, 16}, {1, 2, 2, 12},   // D <= 1024
-            {1, 3, 1, 12}, {1, 3, 2, 8}, {2, 2, 2, 8}, {2, 2, 1, 8},   // D <= 2048
-            {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 6}, {2, 3, 2, 12},   // D <= 3072
-            {4, 2, 1, 4}, {4, 2, 1, 3}, {4, 2, 2, 3}, {4, 2, 2, 2},   // D <= 4096
-            {4, 3, 2, 3}, {4, 3, 1, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 5120
-            {4, 3, 2, 6}, {4, 3, 1, 3}, {4, 3, 2, 2}, {4, 3, 1, 2},   // D <= 6144
-            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2},   // D <= 7168
-            {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 1, 2}};   // D <= 8192
         const int col = (nchunks + 31) / 32;
-        if (short_launch(T, nchunks)) {
-            Shape sh = fine_entry(tab_short, nchunks, dtype);
-            if (unaligned_rows(nchunks) && col == 21) sh = {4, 3, 1, 2};     // D = 5272, 40 MB: 17.5 against 19.3 us
-            return one_step(sh, T);
-        }
+        if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
         if (unaligned_rows(nchunks) && col == 11) return {4, 2, 1, 3};       // D = 2760: 109 against 114
         if (unaligned_rows(nchunks) && col == 30) return {6, 3, 1, 1};       // D = 7640: 117 against 142
         // D = 1536: four blocks per CU are 4 % faster on the 32 760 rows of the Wan-1.3B workload,

@@ -55,6 +55,27 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
     (T.LNMOD_FAMILY_TOKEN_BACKWARD, 4008, 0, 5000, (8, 1, 1, 1)),
     (T.LNMOD_FAMILY_TOKEN_BACKWARD, 3208, 0, 40000, (8, 1, 1, 2)),
     (T.LNMOD_FAMILY_TOKEN_BACKWARD, 3400, 0, 40000, (4, 2, 1, 2)),
+    # short forward, D = 5128 ... 5376: two blocks of one row whatever the alignment
+    (T.LNMOD_FAMILY_FORWARD, 5376, 0, 3044, (4, 3, 1, 2)),
+    (T.LNMOD_FAMILY_FORWARD, 5272, 0, 3044, (4, 3, 1, 2)),
 ])
 def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
+
+
+@pytest.mark.parametrize("D,rows,segments,kernel,blocks", [
+    (512, 150000, 300, "1, 1, 2", 4096),          # the short table's entry with its two rows per step
+    (768, 150000, 300, "2, 1, 2", 4096),
+    (1024, 60000, 300, "2, 1, 1", 3072),          # one row per step ...
+    (1024, 150000, 300, "2, 1, 2", 1024),         # ... but the long table's on large launches of longer segments
+    (1024, 150000, 600, "2, 1, 1", 3072),
+    (1280, 60000, 300, "3, 1, 1", 2048),          # the long table's, except on very short segments
+    (1280, 60000, 600, "3, 1, 1", 3072),
+    (1408, 60000, 120, "3, 1, 1", 2048),
+    (1536, 52000, 96, "3, 1, 1", 2048),
+    (1536, 120000, 150, "3, 1, 2", 1024),         # the long table's on large launches
+    (5376, 2843, 20, "3, 4, 2", 1422)])           # (1422 steps for six blocks per CU)
+def test_forward_on_many_short_segments_takes_the_shape_of_its_size(D, rows, segments, kernel, blocks):
+    text = T.lnmod_describe_launch(0, None, segments, rows, True, D, 0, lnmod.LNMOD_PER_SAMPLE)
+    assert text.startswith("fwd_split_kernel<bf16_io, %s, " % kernel) and ", 4, true>" in text, text
+    assert abs(int(text.split("grid=")[1].split()[0]) - blocks) <= 32, text
