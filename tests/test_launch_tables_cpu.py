@@ -58,6 +58,13 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
     # short forward, D = 5128 ... 5376: two blocks of one row whatever the alignment
     (T.LNMOD_FAMILY_FORWARD, 5376, 0, 3044, (4, 3, 1, 2)),
     (T.LNMOD_FAMILY_FORWARD, 5272, 0, 3044, (4, 3, 1, 2)),
+    # backward, D = 264 ... 504, and its fp32 form at D = 3076 ... 3328
+    (T.LNMOD_FAMILY_BACKWARD, 264, 0, 200000, (1, 1, 2, 8)),
+    (T.LNMOD_FAMILY_BACKWARD, 504, 0, 60000, (1, 1, 2, 8)),
+    (T.LNMOD_FAMILY_BACKWARD, 440, 0, 30000, (1, 1, 2, 4)),
+    (T.LNMOD_FAMILY_BACKWARD, 512, 0, 200000, (1, 1, 1, 8)),
+    (T.LNMOD_FAMILY_BACKWARD_RECOMPUTE, 312, 0, 400000, (1, 1, 2, 8)),
+    (T.LNMOD_FAMILY_BACKWARD, 3116, 1, 15000, (5, 4, 2, 1)),
 ])
 def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
