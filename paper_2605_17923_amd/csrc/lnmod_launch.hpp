@@ -294,8 +294,15 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
         const int col = (nchunks + 31) / 32;
         if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
-        if (unaligned_rows(nchunks) && col == 11) return {4, 2, 1, 3};       // D = 2760: 109 against 114
-        if (unaligned_rows(nchunks) && col == 30) return {6, 3, 1, 1};       // D = 7640: 117 against 142
+        // D = 2632 ... 2808: 100 MB 1 to 3 % slower, 300 MB 1 to 5 % faster; narrower (2568, 2616) 2 to 5 % slower at both
+        if (unaligned_rows(nchunks) && col == 11 && nchunks > 328) return {4, 2, 1, 3};
+        // D = 7432 ... 7672, 100 and 300 MB: 0.81 to 0.89 of the time
+        if (unaligned_rows(nchunks) && col == 30) return {6, 3, 1, 1};
+        // D = 1288 ... 1528: the entry was timed at D = 1536.  Aligned rows 0.84 to 1.01 of its time at 79, 119 and 300
+        // MB; unaligned ones up to D = 1344 0.89 to 0.99 at 79 and 119 MB, beyond either 1 to 8 % slower
+        if (col == 6 && nchunks != 192 &&
+            (!unaligned_rows(nchunks) || (nchunks <= 168 && T * nchunks * 16 <= 150000000 && T > 0)))
+            return {1, 3, 1, 8};
         // D = 1536: four blocks per CU are 4 % faster on the 32 760 rows of the Wan-1.3B workload,
         // the two tie on 65 520 rows, three are 3 % faster on 131 040 rows and 5 % on 252 000
         if (nchunks == 192) return {1, 3, 2, T >= 98304 ? 3 : 4};

@@ -65,6 +65,13 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
     (T.LNMOD_FAMILY_BACKWARD, 512, 0, 200000, (1, 1, 1, 8)),
     (T.LNMOD_FAMILY_BACKWARD_RECOMPUTE, 312, 0, 400000, (1, 1, 2, 8)),
     (T.LNMOD_FAMILY_BACKWARD, 3116, 1, 15000, (5, 4, 2, 1)),
+    # forward, D = 1288 ... 1528 and 2568 ... 2808
+    (T.LNMOD_FAMILY_FORWARD, 1408, 0, 60000, (1, 3, 1, 8)),
+    (T.LNMOD_FAMILY_FORWARD, 1400, 0, 60000, (1, 3, 2, 4)),
+    (T.LNMOD_FAMILY_FORWARD, 1288, 0, 40000, (1, 3, 1, 8)),
+    (T.LNMOD_FAMILY_FORWARD, 1288, 0, 100000, (1, 3, 2, 4)),
+    (T.LNMOD_FAMILY_FORWARD, 2568, 0, 40000, (2, 3, 1, 4)),
+    (T.LNMOD_FAMILY_FORWARD, 2680, 0, 40000, (4, 2, 1, 3)),
 ])
 def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
