@@ -39,11 +39,17 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
             {3, 2, 1, 4}, {3, 2, 1, 2}, {4, 2, 1, 3}, {4, 2, 1, 3},   // D <= 3072
             {4, 2, 1, 2}, {4, 2, 2, 2}, {4, 2, 1, 2}, {5, 2, 1, 2},   // D <= 4096
             {4, 3, 1, 2}, {4, 3, 2, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 5120
-            {4, 3, 1, 1}, {4, 3, 1, 4}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
+            {4, 3, 1, 1}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 1, 1},   // D <= 7168
-            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 2}};   // D <= 8192
-        if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
-        if (unaligned_rows(nchunks) && (nchunks + 31) / 32 == 5) return {2, 2, 1, 3};    // D = 1144: 161 against 170 us
+            {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 2}};   // D <= 8192
+        // D = 4360 ... 6656: two tensors are read, and at 71 MB the short entries lost 3 to 8 % (5048 52.5 -> 56.4 us);
+        // elsewhere they win up to 72 MB at most widths (2568 56.2 against 60.3 us, 7096 44.9 against 47.2)
+        if (short_launch(T, nchunks) && (nchunks <= 544 || nchunks > 832 || T * nchunks * 16 <= 48000000))
+            return fine_entry(tab_short, nchunks, dtype);
+        // D = 1160 ... 1272: 0.88 to 0.97 of the time at 85 and 200 MB; narrower (1032 ... 1144) 0.95 to 1.03 at 200 MB
+        // and 8 to 14 % slower at 85
+        if (unaligned_rows(nchunks) && (nchunks + 31) / 32 == 5 && (nchunks > 144 || T == 0 || T * nchunks * 16 > 128000000))
+            return {2, 2, 1, 3};
         return fine_entry(tab, nchunks, dtype);
     }
     if (ln) {
@@ -52,14 +58,26 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
             {1, 1, 1, 8}, {1, 2, 2, 4}, {1, 3, 2, 4}, {1, 4, 1, 4},   // D <= 1024
             {2, 4, 1, 3}, {2, 4, 1, 2}, {2, 4, 1, 3}, {2, 4, 1, 3},   // D <= 2048
             {3, 4, 1, 2}, {3, 4, 2, 2}, {4, 4, 1, 2}, {3, 4, 1, 2},   // D <= 3072
-            {5, 4, 1, 1}, {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},   // D <= 4096
+            {4, 4, 2, 1}, {4, 4, 1, 2}, {4, 4, 1, 2}, {4, 4, 1, 2},   // D <= 4096
             {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 2}, {5, 4, 1, 1},   // D <= 5120
             {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 6144
             {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 2}, {8, 4, 1, 2},   // D <= 7168
             {8, 4, 1, 1}, {8, 4, 1, 2}, {8, 4, 1, 2}, {8, 4, 1, 2}};   // D <= 8192
         Shape sh = fine_entry(tab32, nchunks, dtype);
-        // few rows for each of 256 blocks: two per step (976 x 5120: 15.7 us against 18.4)
-        if (sh.per_cu == 1 && short_launch(T, nchunks)) sh.R = 2;
+        if (short_launch(T, nchunks)) {
+            // few rows for each of 256 blocks: two per step (976 x 5120: 15.7 us against 18.4)
+            if (sh.per_cu == 1) sh.R = 2;
+            // four waves per CU and at most four steps of one row: two per step (2441 x 1024: 9.3 us against 10.2,
+            // 1775 x 1408 10.7 against 12.1)
+            if (sh.K * sh.per_cu == 4 && T <= 1024 * sh.per_cu) sh.R = 2;
+            // five waves, less than three steps of two rows: one block per CU (1354 x 4612: 21.8 against 24.2)
+            if (sh.K == 5 && T < 1536) sh.per_cu = 1;
+            // eight waves: a row for every block, or two rows per step in one or two blocks per CU (488 x 7168: 11.3 us
+            // against 14.6 with one row and two blocks, 903 x 6916 19.8 against 21.7; 244 x 8192 one row 9.1 against 10.3)
+            if (sh.K == 8 && T <= kNumCU) sh = {8, 4, 1, 1};
+            else if (sh.K == 8 && nchunks > 1920) sh = {8, 4, 2, 2};
+            else if (sh.K == 8 && T <= 1024) sh = {8, 4, 2, 1};
+        }
         return sh;
     }
     const Split sp = choose_split(nchunks, dtype);
@@ -157,7 +175,9 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
                                           pick_clusters(stream_us, p.nseg));
     a.rows_per_cluster = pl.rows_per_cluster;
     a.nb = pl.nb;
-    a.interleave = cluster_interleave(nullptr, pl);
+    // two and four clusters on all XCDs (2 to 12 samples, 20 and 200 MB: 0.98 and 0.985 of the time in the mean over 13
+    // widths, 2 x 24 800 x 2528 194 -> 184 us), eight and more with an XCD each (40 segments, 20 and 60 MB: 0.97)
+    a.interleave = pl.clusters >= 8 ? 1 : 0;
     a.split = cluster_split(a.interleave, pl);
     const bool ok = p.dtype == 0 ? dispatch<bf16_io, LN>(a, sh, pl.blocks, st)
                                  : dispatch<f32_io, LN>(a, sh, pl.blocks, st);

@@ -72,6 +72,18 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
     (T.LNMOD_FAMILY_FORWARD, 1288, 0, 100000, (1, 3, 2, 4)),
     (T.LNMOD_FAMILY_FORWARD, 2568, 0, 40000, (2, 3, 1, 4)),
     (T.LNMOD_FAMILY_FORWARD, 2680, 0, 40000, (4, 2, 1, 3)),
+    # gated forward
+    (T.LNMOD_FAMILY_GATED_FORWARD, 5632, 0, 700, (4, 3, 1, 2)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 5048, 0, 7131, (4, 3, 1, 1)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 2568, 0, 14000, (4, 2, 1, 3)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 1144, 0, 37000, (2, 2, 1, 4)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 1144, 0, 90000, (2, 2, 1, 3)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 3116, 1, 15000, (4, 4, 2, 1)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 7168, 1, 488, (8, 4, 2, 1)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 7168, 1, 256, (8, 4, 1, 1)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 8192, 1, 1983, (8, 4, 2, 2)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 1024, 1, 2441, (1, 4, 2, 4)),
+    (T.LNMOD_FAMILY_GATED_FORWARD, 4612, 1, 1354, (5, 4, 2, 1)),
 ])
 def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
