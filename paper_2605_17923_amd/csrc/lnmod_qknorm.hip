@@ -35,8 +35,11 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 2, 2, 3}, {6, 2, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 5120
             {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 6144
             {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
-            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 2}, {8, 2, 2, 2}};   // D <= 8192
-        return short_launch(N, nchunks) ? fine_entry(tab_short, nchunks, dtype) : fine_entry(tab, nchunks, dtype);
+            {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        // two tensors are read: beyond D = 3840 the short entries lost 3 to 8 % at 62 MB (D = 5128 44.4 -> 48.1 us),
+        // below it they still win there at most widths (1808 53.1 -> 47.0, 3136 48.7 -> 43.5)
+        const bool few = short_launch(N, nchunks) && (nchunks <= 480 || N * nchunks * 16 <= 36000000);
+        return few ? fine_entry(tab_short, nchunks, dtype) : fine_entry(tab, nchunks, dtype);
     }
     if (!backward) {
         static const Shape tab32[33] = {
@@ -62,6 +65,10 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        // D = 1800 ... 1984: the entry was timed at 2048 (1920, 62, 95 and 173 MB: 67.7, 99.1, 176 us against 70.1, 103, 186)
+        if (nchunks > 224 && nchunks <= 248) return {2, 2, 2, 3};
+        // D = 3080 ... 3320 from 62 MB on: 0.94 to 0.985 of the time (3160 190 against 203 us); aligned rows 4 to 6 % slower
+        if (unaligned_rows(nchunks) && (nchunks + 31) / 32 == 13 && (N == 0 || N * nchunks * 16 > 40000000)) return {4, 2, 2, 2};
         return fine_entry(tab, nchunks, dtype);
     }
     static const Shape tab32[33] = {

@@ -84,6 +84,14 @@ def test_one_samples_workspace_never_shrinks_as_its_rows_grow():
     (T.LNMOD_FAMILY_GATED_FORWARD, 8192, 1, 1983, (8, 4, 2, 2)),
     (T.LNMOD_FAMILY_GATED_FORWARD, 1024, 1, 2441, (1, 4, 2, 4)),
     (T.LNMOD_FAMILY_GATED_FORWARD, 4612, 1, 1354, (5, 4, 2, 1)),
+    # query / key normalisation
+    (T.LNMOD_FAMILY_QKNORM_FORWARD, 5128, 0, 6142, (6, 2, 2, 1)),
+    (T.LNMOD_FAMILY_QKNORM_FORWARD, 3136, 0, 9885, (5, 2, 2, 3)),
+    (T.LNMOD_FAMILY_QKNORM_FORWARD, 8192, 0, 1100, (8, 2, 2, 1)),
+    (T.LNMOD_FAMILY_QKNORM_BACKWARD, 1920, 0, 45000, (2, 2, 2, 3)),
+    (T.LNMOD_FAMILY_QKNORM_BACKWARD, 2048, 0, 45000, (2, 2, 2, 2)),
+    (T.LNMOD_FAMILY_QKNORM_BACKWARD, 3160, 0, 27000, (4, 2, 2, 2)),
+    (T.LNMOD_FAMILY_QKNORM_BACKWARD, 3200, 0, 27000, (4, 2, 2, 1)),
 ])
 def test_shapes_on_both_sides_of_a_line(family, D, dtype, rows, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows) == (0, shape)
