@@ -75,6 +75,21 @@ int main() {
             CHECK(wide == 0 || p + 1e-12 >= cluster_penalty(C, false), "one block per CU pays less at %lld", (long long)C);
         }
     }
+    // one sample: the bound that sizes its workspace holds its plan's slots and does not fall as its rows grow
+    for (int dtype = 0; dtype < 2; ++dtype) {
+        const int E = dtype == 0 ? 8 : 4;
+        for (int D = 8; D <= kMaxD; D += E) {
+            for (int rc = 0; rc < 2; ++rc) {
+                int64_t before = 0;
+                for (int64_t T = 1; T < 1000000; T = T * 5 / 4 + 1) {
+                    const int64_t most = bwd_most_slots_one_sample(T, D, dtype, rc != 0);
+                    const int64_t own = bwd_slots(bwd_plan(T, 1, D, dtype, rc != 0), 1);
+                    CHECK(own <= most && most >= before, "D %d T %lld rc %d: %lld slots, bound %lld, before %lld", D, (long long)T, rc, (long long)own, (long long)most, (long long)before);
+                    before = most;
+                }
+            }
+        }
+    }
     // the backward for a workspace that cannot grow: whatever shape is found, its plan (the one the launcher makes
     // from that shape) stays within the slots asked for, covers the rows and keeps the rows per wave and step
     int fallbacks = 0, odd = 0;
