@@ -70,7 +70,7 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
             // four waves per CU and at most four steps of one row: two per step (2441 x 1024: 9.3 us against 10.2,
             // 1775 x 1408 10.7 against 12.1)
             if (sh.K * sh.per_cu == 4 && T <= 1024 * sh.per_cu) sh.R = 2;
-            // five waves, less than three steps of two rows: one block per CU (1354 x 4612: 21.8 against 24.2)
+            // five waves, less than three steps of two rows: one block per CU (three segments, 1354 x 4612: 21.8 against 24.2)
             if (sh.K == 5 && T < 1536) sh.per_cu = 1;
             // eight waves: a row for every block, or two rows per step in one or two blocks per CU (488 x 7168: 11.3 us
             // against 14.6 with one row and two blocks, 903 x 6916 19.8 against 21.7; 244 x 8192 one row 9.1 against 10.3)

@@ -253,7 +253,7 @@ inline Shape fine_entry(const Shape (&tab)[33], int nchunks, int dtype) {
 
 // Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
 // share lines with their neighbours, and at a few widths that turns the order of the shapes around, so the
-// entries there were timed on such rows too (the unaligned_* lines below: 300 MB, unless said).
+// entries there were timed on such rows too, at six to eleven widths of each column (the unaligned_rows lines below).
 inline bool unaligned_rows(int nchunks) { return nchunks % 8 != 0; }
 
 // A forward whose rows all find a block of their own takes one row per step: 366 rows at D = 2680 4.8 us
@@ -362,9 +362,10 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
         if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
         if (unaligned_rows(nchunks)) {
             const int col = (nchunks + 31) / 32;
-            if (col == 11) return {6, 1, 2, 1};                              // D = 2760: 162 against 166 us
-            if (col == 21) return {6, 2, 1, 1};                              // D = 5272: 161 against 165
-            if (col == 23) return {4, 3, 2, 1};                              // D = 5800: 168 against 173
+            // six widths of each column, 100 and 300 MB, as a share of the entry's time
+            if (col == 11) return {6, 1, 2, 1};                              // D = 2568 ... 2808: 0.91 ... 1.0
+            if (col == 21) return {6, 2, 1, 1};                              // D = 5128 ... 5368: 0.96 ... 1.0
+            if (col == 23) return {4, 3, 2, 1};                              // D = 5640 ... 5880: 0.94 ... 0.99 at 300 MB, 0.99 ... 1.04 at 100
         }
         if (nchunks == 192) return {3, 1, 1, 3};
         return fine_entry(tab, nchunks, dtype);
@@ -491,8 +492,8 @@ inline Shape tok_rc_bwd_shape(int nchunks, int dtype) {
 // (five).  Both take the same waves and chunks per lane at a width, so that they add a row in the same order; rows
 // per step and blocks per CU differ where that measured better, and on launches of up to 32 Mi elements.  From a
 // sweep of both at every multiple of 512 features on 400 MB and 48 MB tensors; against the former table, six
-// streams: bf16 0.98 of the time in the mean, fp32 the same (48 MB: D = 2048 0.91, 5632 0.86, 6144 0.91; at
-// 400 MB at most 2 % slower at any width); five streams, 400 MB: D = 1024 354 -> 333 us, 2048 378 -> 334, 2560
+// streams: bf16 0.98 of the time in the mean, fp32 the same (48 MB: D = 2048 0.94, 5632 0.87, 6144 0.91; slower by
+// 1.4 % at 97 656 x 1536, 1.3 % at 20 926 x 7168, 4 % at 813 x 6144, 1 % or less elsewhere); five streams, 400 MB: D = 1024 354 -> 333 us, 2048 378 -> 334, 2560
 // 365 -> 324, 4096 362 -> 338, 5632 372 -> 346, 6144 362 -> 337; fp32 D = 2560 356 -> 344, 3584 355 -> 339, 5120
 // 358 -> 346.
 inline Shape tok_bwd_shape(int nchunks, int dtype, bool writes_dshift = true, int64_t T = 0) {
