@@ -113,8 +113,8 @@ def _every_operator(i, aligned, dtype, nbytes):
         _close("dw" + name, dw, (dd * that).sum(0), 1e-5)
 
 
-@pytest.mark.parametrize("megabytes", [3, 100, 210])
-@pytest.mark.parametrize("D", [256, 440, 712, 768, 1000, 1024, 1232, 1280, 1400, 1408, 1536])
+@pytest.mark.parametrize("megabytes", [3, 30, 100, 210])
+@pytest.mark.parametrize("D", [256, 440, 712, 768, 1000, 1024, 1232, 1280, 1400, 1408, 1536, 2560, 5312])
 def test_forward_on_many_short_segments(D, megabytes):
     g = torch.Generator(device="cuda")
     g.manual_seed(D + megabytes)
