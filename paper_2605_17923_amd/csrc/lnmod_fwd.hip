@@ -183,8 +183,8 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
         // 159 us against 182 with three)
         if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0 && !short_launch(p.T, L.nchunks)) tab.per_cu = 4;
         if (mode == kModFlat && L.nchunks <= 192 && p.dtype == 0 && many_short(p)) tab = many_short_shape(p, L.nchunks, tab);
-        // short launches at D = 5184 ... 5376, aligned: on one to six segments the entry (see fwd_short_entry), on more of
-        // them six blocks per CU (20 segments, 30 MB: 16.4 us against 19.2; 3 segments, 64 MB 29.1 against 26.8)
+        // short launches at D = 5184 ... 5376, aligned: on fewer than eight segments the entry (see fwd_short_entry), from
+        // eight on six blocks per CU (20 segments, 30 MB: 16.4 us against 19.2; 3 segments, 64 MB 29.1 against 26.8)
         if (mode == kModFlat && p.dtype == 0 && p.nseg >= 8 && L.nchunks > 640 && L.nchunks <= 672 &&
             !unaligned_rows(L.nchunks) && short_launch(p.T, L.nchunks))
             tab = {4, 3, 2, 6};
