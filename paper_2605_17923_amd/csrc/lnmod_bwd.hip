@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void zero_f32_kernel(float* p, int64_t n) {
 
 }  // namespace
 
-// Grid of the second pass: (sum, feature block) by segment, at most kReduceMaxGrid blocks and 65 535 of
+// Grid of the second pass: feature block, sum, segment; at most kReduceMaxGrid blocks and 65 535 of
 // them along the segments; beyond that the blocks walk the segments with a stride of the grid.
 constexpr int64_t kReduceMaxGrid = int64_t(1) << 20;
 
@@ -137,12 +137,14 @@ hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     const ReduceShape sh = reduce_shape(r.seg.nseg, r.nsum, r.D, clusters, r.nb);
     const int V = sh.V, W = sh.W, G = sh.G;
     const int per_block = kWave / G * V;
-    r.dblocks = static_cast<int32_t>((r.D + per_block - 1) / per_block);
-    const int64_t gx = static_cast<int64_t>(r.nsum) * r.dblocks;
-    int64_t gy = kReduceMaxGrid / gx;
-    if (gy > 65535) gy = 65535;
-    if (gy > r.seg.nseg) gy = r.seg.nseg;
-    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(gy)), block(W * kWave);
+    const int64_t gx = (r.D + per_block - 1) / per_block;
+    int64_t gz = kReduceMaxGrid / (gx * r.nsum);
+    if (gz > 65535) gz = 65535;
+    if (gz > r.seg.nseg) gz = r.seg.nseg;
+    r.waves = W;
+    r.grid_segs = static_cast<int32_t>(gz);
+    r.cluster_of = Divider(static_cast<uint32_t>(r.rows_per_cluster));
+    const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(r.nsum), static_cast<unsigned>(gz)), block(W * kWave);
     if (G == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 4>), grid, block, 0, st, r);
     else if (G == 2) hipLaunchKernelGGL((bwd_reduce_kernel<4, 2>), grid, block, 0, st, r);
     else if (V == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 1>), grid, block, 0, st, r);

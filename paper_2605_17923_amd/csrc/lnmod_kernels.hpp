@@ -32,6 +32,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lnmod_launch.hpp"
+
 #ifndef LNMOD_NT_LOAD
 #define LNMOD_NT_LOAD 1
 #endif
@@ -944,21 +946,24 @@ void bwd_seg_kernel(const BwdArgs a) {
 }
 
 // Second pass: out[k][m, d] = sum of the partial slots of segment m, k < nsum (dshift, dscale
-// and, for the gated operator, dgate).  A block takes 64 * V consecutive features of one sum of
-// one segment; its W = blockDim.x / 64 waves split the slots in ascending order (wave w takes
-// slots w, w + W, ...), and the W wave sums are then added in wave order.  V and W are chosen
+// and, for the gated operator, dgate).  A block takes 64 / G * V consecutive features of one sum of
+// one segment; its parts = waves * G groups of 64 / G lanes split the slots (part p takes slots p, p + parts, ...,
+// in ascending order), and the part sums are then added in a fixed order.  V, G and the waves are chosen
 // from the shapes alone, so results repeat bit for bit.
 struct ReduceArgs {
     const float* ws;         // [nslots][nsum][D]
     void* out[3];            // [nseg, D] each, float32 or bf16
-    int32_t out_bf16;        // 1: the sums are rounded once, here, to bf16
     Segments seg;
     int64_t T;
     int64_t rows_per_cluster;
     int32_t nb;              // blocks per cluster = partial slots per (cluster, segment)
     int32_t D;
-    int32_t dblocks;         // ceil(D / (64 * V))
     int32_t nsum;            // 2 or 3
+    int32_t out_bf16;        // 1: the sums are rounded once, here, to bf16
+    // set by launch_reduce:
+    int32_t waves;           // of a block
+    int32_t grid_segs;       // blocks along the segments
+    Divider cluster_of;      // row -> cluster
 };
 
 // Stores V consecutive sums.  A caller that keeps the gradients in the tensors' own type used to
@@ -985,69 +990,94 @@ constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 
 template <int V> struct FVec { typedef float type __attribute__((ext_vector_type(V))); };
 template <> struct FVec<1> { typedef float type; };
 
-// blockIdx.x is (which sum, block of 64 * V features); the segments are blockIdx.y, blockIdx.y + gridDim.y,
-// ..., so that any segment count the interface admits stays inside the launch limits.
+// blockIdx.x is the block of features, blockIdx.y the sum; the segments are blockIdx.z, blockIdx.z + grid_segs, ...,
+// so that any segment count the interface admits stays inside the launch limits.
+//
+// The kernel reads 1 to 40 MB that the main kernel has just written, in 4 to 5 us of which most is neither bytes nor
+// additions: it is instructions that every launch fetches anew (130 more of them in front of the loads cost 2 us) and a
+// chain of dependent round trips (arguments, segment table, slots, LDS).  So its code is kept short: no division
+// (Divider, and the grid has the sums and the segments as dimensions of their own), 32-bit offsets from a uniform base, a
+// slot beyond the last is read as the last one and not added, one LDS stage for waves and lane groups together.  With
+// 64-bit slot numbers and addresses, two divisions and a branch per load it took 4.5 us on 512 x 1536 fp32 rows, now 3.7;
+// on 32 760 x 1536 6.0, now 5.3; on 6449 x 2048 in ten samples 5.0, now 4.4.
 template <int V, int G = 1>
 __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const ReduceArgs a) {
     using vec = typename FVec<V>::type;
-    constexpr int kReduceBatch = kReduceFloats / V;
-    constexpr int FL = kWave / G;                 // lanes along the features; G groups of them take different slots
-    __shared__ vec red[kReduceWaves][FL];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
-    const int W = blockDim.x >> 6;
-    const int fl = lane % FL, grp = lane / FL;
-    const uint32_t which = blockIdx.x / static_cast<uint32_t>(a.dblocks);
-    const int d = (static_cast<int>(blockIdx.x - which * static_cast<uint32_t>(a.dblocks)) * FL + fl) * V;
-    for (int64_t m = blockIdx.y; m < a.seg.nseg; m += gridDim.y) {
-        int64_t n0 = seg_begin(a.seg, m), n1 = seg_begin(a.seg, m + 1);
-        if (n0 < 0) n0 = 0;                       // a malformed table must not lead outside ws
-        if (n1 > a.T) n1 = a.T;
+    constexpr uint32_t kReduceBatch = kReduceFloats / V;
+    constexpr uint32_t FL = kWave / G;            // lanes along the features; G groups of them take different slots
+    __shared__ vec red[kReduceWaves * kWave];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t W = static_cast<uint32_t>(a.waves);
+    const uint32_t parts = W * G, part = tid / FL;
+    const uint32_t d = (blockIdx.x * FL + tid % FL) * V;
+    const uint32_t which = blockIdx.y;
+    const bool dead = d >= static_cast<uint32_t>(a.D);
+    const uint32_t d_off = dead ? 0u : d * 4u;    // lanes beyond the row read its start
+    const uint32_t pitch = static_cast<uint32_t>(a.nsum * a.D) * 4u, nb = static_cast<uint32_t>(a.nb);
+    for (int64_t m = blockIdx.z; m < a.seg.nseg; m += a.grid_segs) {
+        int32_t n0, n1;
+        if (a.seg.cu) {
+            n0 = table_at(a.seg.cu, m);
+            n1 = table_at(a.seg.cu, m + 1);
+            if (n0 < 0) n0 = 0;                   // a malformed table must not lead outside ws
+            if (n1 > static_cast<int32_t>(a.T)) n1 = static_cast<int32_t>(a.T);
+        } else {
+            n0 = static_cast<int32_t>(m) * static_cast<int32_t>(a.seg.S);
+            n1 = n0 + static_cast<int32_t>(a.seg.S);
+        }
         vec acc = vec(0.0f);
-        if (n1 > n0 && d < a.D) {
+        if (n1 > n0) {
             // clusters c_lo..c_hi touch this segment; (cluster c, segment m) owns slots (c+m)*nb ..
-            const uint32_t rpc = static_cast<uint32_t>(a.rows_per_cluster);
-            const int64_t c_lo = static_cast<uint32_t>(n0) / rpc, c_hi = static_cast<uint32_t>(n1 - 1) / rpc;
-            const int64_t s_lo = (c_lo + m) * a.nb, s_hi = (c_hi + m + 1) * a.nb;
-            const float* base = a.ws + static_cast<int64_t>(which) * a.D + d;
-            const int64_t pitch = static_cast<int64_t>(a.nsum) * a.D;
-            const int64_t stride = static_cast<int64_t>(W) * G;
-            // kReduceBatch slots requested before the first is added (the chain of dependent round
-            // trips, not the bytes, is what this kernel's time consists of); the additions keep slot order
-            for (int64_t sl = s_lo + wave * G + grp; sl < s_hi; sl += kReduceBatch * stride) {
+            const uint32_t c_lo = a.cluster_of(static_cast<uint32_t>(n0)), c_hi = a.cluster_of(static_cast<uint32_t>(n1 - 1));
+            const uint32_t count = (c_hi - c_lo + 1) * nb;           // at most the blocks of the launch
+            const char* base = reinterpret_cast<const char*>(a.ws) + (c_lo + m) * nb * static_cast<int64_t>(pitch) +
+                               which * static_cast<uint32_t>(a.D) * 4u;
+            // kReduceBatch slots requested before the first is added; the additions keep slot order
+            for (uint32_t s0 = part; s0 - part < count; s0 += kReduceBatch * parts) {
                 vec v[kReduceBatch];
 #pragma unroll
-                for (int u = 0; u < kReduceBatch; ++u) {
-                    const int64_t su = sl + static_cast<int64_t>(u) * stride;
-                    v[u] = su < s_hi ? *reinterpret_cast<const vec*>(base + su * pitch) : vec(0.0f);
+                for (uint32_t u = 0; u < kReduceBatch; ++u) {
+                    const uint32_t su = s0 + u * parts;
+                    v[u] = *reinterpret_cast<const vec*>(base + ((su < count ? su : count - 1) * pitch + d_off));
                 }
 #pragma unroll
-                for (int u = 0; u < kReduceBatch; ++u) acc += v[u];
-            }
-        }
-        if constexpr (G > 1) {
-            // the G groups of the wave, in a fixed order
-#pragma unroll
-            for (int off = FL; off < kWave; off <<= 1) {
-                if constexpr (V == 1) {
-                    acc += __shfl_xor(acc, off);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off);
-                }
+                for (uint32_t u = 0; u < kReduceBatch; ++u) acc += s0 + u * parts < count ? v[u] : vec(0.0f);
             }
         }
         if (W > 1) {
-            if (grp == 0) red[wave][fl] = acc;
+            red[tid] = acc;
             __syncthreads();
-            if (wave == 0 && grp == 0) {
-                acc = red[0][fl];
-                for (int w = 1; w < W; ++w) acc += red[w][fl];
+            if (tid < kWave) {                    // the waves' sums in wave order: W is 2 or a multiple of 4
+                if (W == 2) {
+                    acc += red[kWave + tid];
+                } else {
+                    acc = vec(0.0f);
+                    for (uint32_t w0 = 0; w0 < W; w0 += 4) {
+                        vec v[4];
+#pragma unroll
+                        for (uint32_t k = 0; k < 4; ++k) v[k] = red[(w0 + k) * kWave + tid];
+#pragma unroll
+                        for (uint32_t k = 0; k < 4; ++k) acc += v[k];
+                    }
+                }
             }
-            __syncthreads();                      // red is written again in the next round
+            if (m + a.grid_segs < a.seg.nseg) __syncthreads();       // red is written again in the next round
         }
-        if (wave == 0 && grp == 0 && d < a.D)
-            store_sums<V>(a.out[which], m * a.D + d, acc, a.out_bf16 != 0);
+        if (tid < kWave) {
+            if constexpr (G > 1) {
+                // the G groups of lanes, in a fixed order
+#pragma unroll
+                for (int off = FL; off < kWave; off <<= 1) {
+                    if constexpr (V == 1) {
+                        acc += __shfl_xor(acc, off);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off);
+                    }
+                }
+            }
+            if (part == 0 && !dead) store_sums<V>(a.out[which], m * a.D + d, acc, a.out_bf16 != 0);
+        }
     }
 }
 

@@ -10,6 +10,27 @@ namespace lnmod {
 constexpr int kNumCU = 256;            // MI355X: 8 XCDs x 32 CUs
 constexpr int64_t kMaxD = 8192;
 
+// n / d for 0 <= n < 2^31 and a d >= 1 that every division of a launch shares: the high half of one multiplication and a
+// shift.  d a power of two: n >> sh.  Else, with 2^sh < d < 2^(sh+1), mul = floor(2^(32+sh) / d) + 1 is below 2^32 and
+// exceeds 2^(32+sh) / d by e / d with e <= d, so the quotient's error is at most n e / (d 2^(32+sh)) <= n / 2^(32+sh) < 1 / d.
+struct Divider {
+    uint32_t mul = 0, keep = ~uint32_t(0), sh = 0;
+    Divider() = default;
+    explicit Divider(uint32_t d) {
+        while (sh < 31 && d >> (sh + 1) != 0) ++sh;
+        if ((d & (d - 1)) != 0) {
+            mul = static_cast<uint32_t>((uint64_t{1} << (32 + sh)) / d) + 1;
+            keep = 0;
+        }
+    }
+#ifdef __HIPCC__
+    __host__ __device__
+#endif
+    uint32_t operator()(uint32_t n) const {
+        return (static_cast<uint32_t>((static_cast<uint64_t>(n) * mul) >> 32) + (n & keep)) >> sh;
+    }
+};
+
 // Launch shape of a row kernel: K waves per row, VPL 16-byte chunks per lane, R rows per block and
 // step, per_cu resident blocks per compute unit that the grid is sized for.
 struct Shape {
