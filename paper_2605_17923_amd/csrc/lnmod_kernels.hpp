@@ -32,6 +32,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lnmod_launch.hpp"
 
 #ifndef LNMOD_NT_LOAD
@@ -972,7 +974,9 @@ struct ReduceArgs {
 template <int V, typename VEC>
 __device__ inline void store_sums(void* out, int64_t at, const VEC& v, bool bf16) {
     if (!bf16) {
-        *reinterpret_cast<VEC*>(static_cast<float*>(out) + at) = v;
+        // the weight gradients of the query/key normalisation may be at any float's address
+        typedef VEC loose __attribute__((aligned(4)));
+        *reinterpret_cast<loose*>(static_cast<float*>(out) + at) = v;
         return;
     }
     __bf16* p = static_cast<__bf16*>(out) + at;
@@ -1014,14 +1018,16 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
     const bool dead = d >= static_cast<uint32_t>(a.D);
     const uint32_t d_off = dead ? 0u : d * 4u;    // lanes beyond the row read its start
     const uint32_t pitch = static_cast<uint32_t>(a.nsum * a.D) * 4u, nb = static_cast<uint32_t>(a.nb);
-    for (int64_t m = blockIdx.z; m < a.seg.nseg; m += a.grid_segs) {
-        int32_t n0, n1;
+    void* const out = which == 0 ? a.out[0] : which == 1 ? a.out[1] : a.out[2];
+    int64_t m = blockIdx.z;
+    do {                                          // the grid has no more blocks along the segments than there are
+        int32_t n0 = 0, n1 = static_cast<int32_t>(a.T);
         if (a.seg.cu) {
             n0 = table_at(a.seg.cu, m);
             n1 = table_at(a.seg.cu, m + 1);
             if (n0 < 0) n0 = 0;                   // a malformed table must not lead outside ws
             if (n1 > static_cast<int32_t>(a.T)) n1 = static_cast<int32_t>(a.T);
-        } else {
+        } else if (a.seg.nseg > 1) {
             n0 = static_cast<int32_t>(m) * static_cast<int32_t>(a.seg.S);
             n1 = n0 + static_cast<int32_t>(a.seg.S);
         }
@@ -1047,18 +1053,21 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
         if (W > 1) {
             red[tid] = acc;
             __syncthreads();
-            if (tid < kWave) {                    // the waves' sums in wave order: W is 2 or a multiple of 4
-                if (W == 2) {
-                    acc += red[kWave + tid];
+            if (tid < kWave) {                    // the waves' sums in wave order: W is a power of two
+                vec v[kReduceWaves];
+                const auto add = [&](auto first, auto last) {
+#pragma unroll
+                    for (uint32_t k = first; k < last; ++k) v[k] = red[k * kWave + tid];
+#pragma unroll
+                    for (uint32_t k = first; k < last; ++k) acc += v[k];
+                };
+                using std::integral_constant;
+                if (W == 16) {
+                    add(integral_constant<uint32_t, 1>{}, integral_constant<uint32_t, 16>{});
                 } else {
-                    acc = vec(0.0f);
-                    for (uint32_t w0 = 0; w0 < W; w0 += 4) {
-                        vec v[4];
-#pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k) v[k] = red[(w0 + k) * kWave + tid];
-#pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k) acc += v[k];
-                    }
+                    add(integral_constant<uint32_t, 1>{}, integral_constant<uint32_t, 2>{});
+                    if (W >= 4) add(integral_constant<uint32_t, 2>{}, integral_constant<uint32_t, 4>{});
+                    if (W >= 8) add(integral_constant<uint32_t, 4>{}, integral_constant<uint32_t, 8>{});
                 }
             }
             if (m + a.grid_segs < a.seg.nseg) __syncthreads();       // red is written again in the next round
@@ -1076,9 +1085,10 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
                     }
                 }
             }
-            if (part == 0 && !dead) store_sums<V>(a.out[which], m * a.D + d, acc, a.out_bf16 != 0);
+            if (part == 0 && !dead) store_sums<V>(out, m * a.D + d, acc, a.out_bf16 != 0);
         }
-    }
+        m += a.grid_segs;
+    } while (m < a.seg.nseg);
 }
 
 // =============================================================================================

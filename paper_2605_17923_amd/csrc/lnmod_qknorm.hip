@@ -189,9 +189,9 @@ int32_t short_blocks_per_tensor(int64_t N, int rows_per_piece, int per_cu) {
 int32_t qknorm_bwd_blocks(int64_t N, int64_t D, int dtype) {
     const int E = dtype == 0 ? 8 : 4;
     const int nchunks = static_cast<int>(D / E);
-    if (nchunks <= kShortMaxChunks) {                // one slot per wave
+    if (nchunks <= kShortMaxChunks) {
         const int r = nchunks <= 16 ? short_bwd_r<1>() : short_bwd_r<2>();
-        return short_blocks_per_tensor(N, 4 * r, kShortBwdBlocksPerCu) * kShortWaves;
+        return short_blocks_per_tensor(N, 4 * r, kShortBwdBlocksPerCu);
     }
     bool ok;
     const Shape sh = wide_shape(nchunks, dtype, true, N, &ok);
@@ -258,7 +258,7 @@ hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, 
     int32_t slots = qknorm_bwd_blocks(N, D, dtype);              // per tensor
     if (a.nchunks <= kShortMaxChunks) {
         const bool one = a.nchunks <= 16;
-        a.nb = slots / kShortWaves;
+        a.nb = slots;
         const dim3 grid(static_cast<unsigned>(2 * a.nb)), block(kShortWaves * kWave);
         if (dtype == 0) {
             if (one) hipLaunchKernelGGL((qknorm_short_bwd_kernel<bf16_io, 1, short_bwd_r<1>()>), grid, block, 0, st, a);
@@ -279,17 +279,18 @@ hipError_t launch_qknorm_bwd(int dtype, const void* dq_out, const void* dk_out, 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
 
-    QkReduceArgs r;
+    ReduceArgs r{};
     r.ws = ws;
-    r.dw[0] = dwq;
-    r.dw[1] = dwk;
+    r.out[0] = dwq;
+    r.out[1] = dwk;
     r.out_bf16 = io_grads && dtype == 0;
-    r.nb = slots;
+    r.seg = Segments{nullptr, N, 1};
+    r.T = N;
+    r.rows_per_cluster = N;
+    r.nb = a.nb;
     r.D = a.D;
-    r.dblocks = static_cast<int32_t>((D + kWave - 1) / kWave);
-    hipLaunchKernelGGL(qknorm_reduce_kernel<0>, dim3(static_cast<unsigned>(2 * r.dblocks)),
-                       dim3(kReduceWaves * kWave), 0, st, r);
-    return hipGetLastError();
+    r.nsum = 2;
+    return launch_reduce(r, 1, st);
 }
 
 }  // namespace lnmod

@@ -161,7 +161,7 @@ struct QkBwdArgs {
     const void* w[2];
     const float* rstd[2];
     void* dx[2];
-    float* ws;               // [2][nb][D] fp32 partial dw sums
+    float* ws;               // [nb][2][D] fp32 partial dw sums
     int64_t N;
     int32_t nb;
     int32_t D;
@@ -313,7 +313,7 @@ void qknorm_bwd_kernel(const QkBwdArgs a) {
     }
 
     // this block's partial dw (zeros if it had no row)
-    float* slot = a.ws + (static_cast<int64_t>(t) * a.nb + member) * a.D;
+    float* slot = a.ws + (member * 2 + t) * a.D;
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         if (ok[i]) {
@@ -429,7 +429,8 @@ void qknorm_short_fwd_kernel(const QkFwdArgs a) {
     }
 }
 
-// One partial-sum slot per wave: slot (t*nb + member)*kShortWaves + wave of a.ws.
+// One partial-sum slot per block, as in the kernel above: the waves' sums are added in LDS first (a slot per wave made the
+// second pass read four times as much with the few blocks that short rows give it).
 template <typename Tag, int VPL, int R>
 __global__ __launch_bounds__(kShortWaves* kWave)
 void qknorm_short_bwd_kernel(const QkBwdArgs a) {
@@ -535,9 +536,8 @@ void qknorm_short_bwd_kernel(const QkBwdArgs a) {
         }
     }
 
-    // add the four groups of the wave (lanes l, l+16, l+32, l+48 hold the same features), then
-    // the first group writes the wave's slot
-    float* slot = a.ws + ((static_cast<int64_t>(t) * a.nb + member) * kShortWaves + wave) * a.D;
+    // add the four groups of each wave (lanes l, l+16, l+32, l+48 hold the same features), then the waves
+    __shared__ f32x4 part[kShortWaves][VPL][E / 4][16];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
 #pragma unroll
@@ -547,57 +547,23 @@ void qknorm_short_bwd_kernel(const QkBwdArgs a) {
             v += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(((lane ^ 32) << 2), __builtin_bit_cast(int, v)));
             acc[i][e] = v;
         }
-        if (ok[i] && group == 0) {
-            f32x4* ps = reinterpret_cast<f32x4*>(slot + (i * 16 + gl) * E);
+        if (group == 0) {
 #pragma unroll
             for (int q = 0; q < E / 4; ++q)
-                ps[q] = f32x4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+                part[wave][i][q][gl] = f32x4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
         }
     }
-}
-
-// Second pass: dw[t][d] = sum of the nb slots of tensor t, slots in ascending order split over 16
-// waves, the 16 wave sums then added in wave order.  grid.x = 2 * dblocks.
-struct QkReduceArgs {
-    const float* ws;
-    void* dw[2];             // float32 or bf16
-    int32_t out_bf16;        // see ReduceArgs
-    int32_t nb;
-    int32_t D;
-    int32_t dblocks;
-};
-
-template <int kUnused = 0>
-__global__ __launch_bounds__(kReduceWaves* kWave) void qknorm_reduce_kernel(const QkReduceArgs a) {
-    __shared__ float red[kReduceWaves][kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x >> 6;
-    const int d = static_cast<int>(blockIdx.x % a.dblocks) * kWave + lane;
-    const int t = static_cast<int>(blockIdx.x / a.dblocks);
-    float acc = 0.0f;
-    if (d < a.D) {
-        // eight slots requested before the first is added (a wave may have 64 of them: short rows
-        // give one slot per wave of the main kernel); the additions keep slot order
-        const float* base = a.ws + static_cast<int64_t>(t) * a.nb * a.D + d;
-        for (int64_t sl = wave; sl < a.nb; sl += 8 * kReduceWaves) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t su = sl + static_cast<int64_t>(u) * kReduceWaves;
-                v[u] = su < a.nb ? base[su * a.D] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-    }
-    red[wave][lane] = acc;
     __syncthreads();
-    if (wave == 0 && d < a.D) {
-        float s = 0.0f;
+    float* slot = a.ws + (member * 2 + t) * a.D;
+    for (int v = threadIdx.x; v < VPL * 16 * (E / 4); v += kShortWaves * kWave) {
+        const int i = v / (16 * (E / 4)), q = v / 16 % (E / 4), chunk = i * 16 + v % 16;
+        f32x4 sum = part[0][i][q][v % 16];
 #pragma unroll
-        for (int w = 0; w < kReduceWaves; ++w) s += red[w][lane];
-        store_sums<1>(t ? a.dw[1] : a.dw[0], d, s, a.out_bf16 != 0);
+        for (int w = 1; w < kShortWaves; ++w) sum += part[w][i][q][v % 16];
+        if (chunk < a.nchunks) *reinterpret_cast<f32x4*>(slot + chunk * E + q * 4) = sum;
     }
 }
+
+// The second pass is bwd_reduce_kernel on one segment with two sums per slot, dwq and dwk.
 
 }  // namespace lnmod
