@@ -272,6 +272,18 @@ inline Shape fine_entry(const Shape (&tab)[33], int nchunks, int dtype) {
     return tab[cols < 1 ? 1 : cols > 32 ? 32 : cols];
 }
 
+// Between the short launches and the 770 MB the long tables were timed at the winners are others again at some widths, and
+// at the widths between two multiples of 256 an entry timed at the multiple can be far off.  The rules below come from
+// 1200 random bf16 and 380 fp32 problems with x of 4 to 300 MB (widths of models and any others, one sample, several and
+// packed), on each of which every compiled shape was timed; a rule stands where one shape took at least 2 % less time in the
+// mean of its class, and gives the shares of the former entry's time (mean, worst).  Most end at 300 MB, where the long
+// tables were timed; those without an upper end were timed on one sample of 400 and 800 MB too, at three or four widths.
+constexpr int64_t kAnyMB = int64_t(1) << 40;
+inline bool launch_mb(int64_t T, int nchunks, int64_t lo, int64_t hi) {      // x of more than lo and at most hi MB
+    const int64_t bytes = T * nchunks * 16;
+    return bytes > lo * 1000000 && bytes <= hi * 1000000;
+}
+
 // Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
 // share lines with their neighbours, and at a few widths that turns the order of the shapes around, so the
 // entries there were timed on such rows too, at six to eleven widths of each column (the unaligned_rows lines below).
@@ -314,6 +326,29 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {8, 2, 1, 2}, {8, 2, 2, 2}, {5, 3, 1, 1}, {5, 3, 1, 1},   // D <= 7168
             {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
         const int col = (nchunks + 31) / 32;
+        if (launch_mb(T, nchunks, 20, 72)) {
+            if (col == 6) return {1, 3, 2, 12};                              // D = 1288 ... 1536: 0.935, 0.99
+            if (col == 12) return {2, 3, 2, 6};                              // D = 2824 ... 3072: 0.93, 1.03
+            if (nchunks == 512 && launch_mb(T, nchunks, 24, 72)) return {4, 2, 1, 3};     // D = 4096: 0.975, 1.005
+        }
+        if (short_launch(T, nchunks) && T > 0) {
+            if (col == 12 && launch_mb(T, nchunks, 12, 20)) return {2, 3, 1, 6};  // D = 2824 ... 3072: 0.90, 0.97
+            if (nchunks == 448 && launch_mb(T, nchunks, 12, 72)) return {4, 2, 1, 4};     // D = 3584: 0.965, 1.01
+            if (col == 24 && nchunks < 768) return one_step({4, 3, 2, 3}, T);     // D = 5896 ... 6136: 0.94, 0.99
+        }
+        if (launch_mb(T, nchunks, 72, 150)) {
+            if (col == 4 && nchunks <= 112) return {1, 2, 1, 12};            // D = 776 ... 896: 0.935, 1.0
+            if (col == 7 && nchunks < 224) return {2, 2, 2, 4};              // D = 1544 ... 1784: 0.97, 0.995
+            if (col == 18 && nchunks < 576) return {4, 3, 2, 2};             // D = 4360 ... 4600: 0.96, 1.03
+            if (nchunks == 512) return {4, 2, 1, 3};                         // D = 4096: 0.94, 0.98
+            if (nchunks == 640) return {5, 2, 1, 2};                         // D = 5120: 0.93, 0.96
+        }
+        if (launch_mb(T, nchunks, 72, 300)) {
+            if (col == 12) return {2, 3, 1, 4};                              // D = 2824 ... 3072: 0.955, 0.995
+            if (col == 16 && nchunks < 512) return {4, 2, 1, 3};             // D = 3848 ... 4088: 0.80, 0.80
+        }
+        // D = 4872 ... 5112: 0.71, 0.77; 400 MB 0.70, 800 MB 0.72 (4976: 386 -> 271 us)
+        if (launch_mb(T, nchunks, 72, kAnyMB) && col == 20 && nchunks < 640) return {4, 3, 1, 2};
         if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
         // D = 2632 ... 2808: 100 MB 1 to 3 % slower, 300 MB 1 to 5 % faster; narrower (2568, 2616) 2 to 5 % slower at both
         if (unaligned_rows(nchunks) && col == 11 && nchunks > 328) return {4, 2, 1, 3};
@@ -351,11 +386,16 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
         {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2},   // D <= 6144
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 2}, {8, 4, 2, 2}};   // D <= 8192
+    if (short_launch(T, nchunks) && T > 0) {
+        if (nchunks > 576 && nchunks <= 640) return one_step({3, 4, 2, 3}, T);       // D = 2308 ... 2560: 0.91, 1.01
+        if (nchunks == 1536 && launch_mb(T, nchunks, 20, 72)) return {6, 4, 2, 1};   // D = 6144: 0.92, 0.94
+    }
     if (short_launch(T, nchunks)) return one_step(fine_entry(tab32_short, nchunks, dtype), T);
     return fine_entry(tab32, nchunks, dtype);
 }
 
-inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
+// nseg: samples or segments if known (0: not known, or one).
+inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) {
     if (dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 2, 8},
@@ -380,9 +420,30 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
         // D = 264 ... 504 from 40 MB on: the entries were timed at D = 512, where every lane has a chunk (89 and 250 MB:
         // D = 264 80.5 us against 94.5, 190 against 236; 440 153 against 167; 28 MB 32.6 against 30.4)
         if (nchunks > 32 && nchunks < 64 && (T == 0 || T * nchunks * 16 > 40000000)) return {1, 1, 2, 8};
+        const int col = (nchunks + 31) / 32;
+        if (T > 0 && launch_mb(T, nchunks, 0, 20)) {
+            if (col == 5 && nchunks > 130 && nchunks < 160) return {3, 1, 2, 2};     // D = 1048 ... 1272: 0.90, 1.01
+            if (col == 20) return {8, 2, 1, 1};                              // D = 4872 ... 5120: 0.96, 0.99
+        }
+        if (launch_mb(T, nchunks, 20, 72)) {
+            if (col == 4 && nchunks < 128) return {1, 2, 2, 4};              // D = 776 ... 1016: 0.94, 1.04
+            if (col == 9 && nchunks < 288) return {5, 1, 2, 2};              // D = 2056 ... 2296: 0.95, 0.99
+        }
+        if (launch_mb(T, nchunks, 72, 300)) {
+            if (col == 4 && nchunks < 128 && launch_mb(T, nchunks, 72, 150)) return {1, 2, 2, 6};     // D = 776 ... 1016: 0.85, 1.0
+            // D = 3584: 0.93, 1.0; on segments of fewer than 512 rows in the mean up to 1.09
+            if (nchunks == 448 && T >= 512 * nseg) return {8, 1, 2, 1};
+            if (nchunks == 640) return {5, 2, 2, 1};                         // D = 5120: 0.98, 1.0
+        }
+        if (launch_mb(T, nchunks, 72, kAnyMB)) {
+            if (col == 4 && nchunks < 128) return {1, 2, 2, 4};              // D = 776 ... 1016: 0.87, 0.92; 800 MB 0.80
+            if (col == 6 && nchunks < 192) return {3, 1, 2, 3};              // D = 1288 ... 1528: 0.95, 1.05; 800 MB 0.91
+            if (col == 14 && nchunks < 448 && T >= 512 * nseg) return {8, 1, 2, 1};     // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
+            if (col == 20 && nchunks < 640) return {6, 2, 2, 1};             // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
+            if (nchunks == 768) return {8, 2, 1, 1};                         // D = 6144: 0.975, 0.99; 800 MB 0.98
+        }
         if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
         if (unaligned_rows(nchunks)) {
-            const int col = (nchunks + 31) / 32;
             // six widths of each column, 100 and 300 MB, as a share of the entry's time
             if (col == 11) return {6, 1, 2, 1};                              // D = 2568 ... 2808: 0.91 ... 1.0
             if (col == 21) return {6, 2, 1, 1};                              // D = 5128 ... 5368: 0.96 ... 1.0
@@ -413,6 +474,8 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0) {
         {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 2, 1},   // D <= 6144
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 2, 1}};   // D <= 8192
+    // D = 516 ... 764: 0.90, 0.95 up to 150 MB, the same within 1 % of the best beyond
+    if (launch_mb(T, nchunks, 72, 300) && nchunks > 128 && nchunks < 192) return {1, 3, 2, 4};
     return short_launch(T, nchunks) ? fine_entry(tab32_short, nchunks, dtype) : fine_entry(tab32, nchunks, dtype);
 }
 
@@ -606,7 +669,8 @@ inline BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool pe
         L.pl = plan_rows(T, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R);
         return L;
     }
-    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T) : bwd_shape(L.nchunks, dtype, T));
+    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T)
+                                              : bwd_shape(L.nchunks, dtype, T, nseg));
     // a row moves 3 D elements (dy, x, dx), a slot 2 D floats that are written and read back
     const double elem = dtype == 0 ? 2.0 : 4.0;
     const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 3.0 * elem / 5.8e6;
@@ -621,13 +685,15 @@ inline RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool reco
     return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
 }
 
-// Slots of this backward on one sample of T rows with the shape of a short or of a long launch, whichever has more:
+// Slots of this backward on one sample of T rows with the shape of the size class that has most of them:
 // a bound on the plan's slots that does not fall as T grows.
 inline int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute) {
     if (T <= 0) return 0;
     const int nchunks = static_cast<int>(D / (dtype == 0 ? 8 : 4));
     int64_t most = 0;
-    for (int64_t rows = 0; rows <= 1; ++rows) {          // 0: the long table, 1: the short one
+    // one launch of each size class the shapes tell apart (see launch_mb), and an unknown, long one
+    for (const int64_t mb : {10, 30, 100, 200, 400, 0}) {
+        const int64_t rows = mb * 1000000 / (nchunks * 16);
         const Shape sh = recompute ? rc_bwd_shape(nchunks, dtype, rows) : bwd_shape(nchunks, dtype, rows);
         const int64_t slots = bwd_slots(plan_rows(T, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R), 1);
         if (slots > most) most = slots;

@@ -1,0 +1,51 @@
+"""Launch shapes by size class (x of 12, 20, 72, 150, 300 MB): the entries on both sides of each line, and that a sample's
+workspace holds the slots of its own plan in every class."""
+import pytest
+
+from paper_2605_17923_amd import lnmod, lnmod_tools as T
+
+F, B, RC = T.LNMOD_FAMILY_FORWARD, T.LNMOD_FAMILY_BACKWARD, T.LNMOD_FAMILY_BACKWARD_RECOMPUTE
+
+
+def rows_of(mb, D, dtype):
+    return int(mb * 1e6) // (D * (2, 4)[dtype])
+
+
+@pytest.mark.parametrize("family,D,dtype,mb,shape", [
+    # forward
+    (F, 1536, 0, 19, (1, 3, 2, 8)), (F, 1536, 0, 21, (1, 3, 2, 12)), (F, 1288, 0, 70, (1, 3, 2, 12)), (F, 1288, 0, 80, (1, 3, 1, 8)),
+    (F, 3072, 0, 13, (2, 3, 1, 6)), (F, 3072, 0, 70, (2, 3, 2, 6)), (F, 2824, 0, 290, (2, 3, 1, 4)), (F, 3072, 0, 310, (4, 2, 1, 3)),
+    (F, 4096, 0, 23, (4, 2, 2, 2)), (F, 4096, 0, 25, (4, 2, 1, 3)), (F, 4096, 0, 149, (4, 2, 1, 3)), (F, 4096, 0, 151, (4, 2, 2, 1)),
+    (F, 3584, 0, 11, (4, 2, 1, 3)), (F, 3584, 0, 71, (4, 2, 1, 4)), (F, 3584, 0, 73, (4, 2, 1, 3)), (F, 5904, 0, 71, (4, 3, 2, 3)), (F, 6144, 0, 71, (4, 3, 1, 2)),
+    (F, 784, 0, 100, (1, 2, 1, 12)), (F, 904, 0, 100, (1, 2, 2, 4)), (F, 1640, 0, 140, (2, 2, 2, 4)), (F, 1792, 0, 140, (2, 2, 1, 6)),
+    (F, 5120, 0, 140, (5, 2, 1, 2)), (F, 5120, 0, 160, (5, 2, 2, 1)), (F, 5112, 0, 160, (4, 3, 1, 2)), (F, 4872, 0, 900, (4, 3, 1, 2)),
+    (F, 4088, 0, 290, (4, 2, 1, 3)), (F, 4088, 0, 310, (4, 2, 2, 1)), (F, 4400, 0, 149, (4, 3, 2, 2)), (F, 4400, 0, 151, (4, 3, 1, 2)),
+    (F, 2560, 1, 40, (3, 4, 2, 3)), (F, 2304, 1, 40, (3, 4, 2, 4)), (F, 6144, 1, 40, (6, 4, 2, 1)), (F, 6144, 1, 19, (6, 4, 1, 2)),
+    # backward
+    (B, 1040, 0, 19, (3, 1, 1, 4)), (B, 1152, 0, 19, (3, 1, 2, 2)), (B, 1152, 0, 21, (3, 1, 1, 4)), (B, 5120, 0, 19, (8, 2, 1, 1)), (B, 5120, 0, 21, (5, 2, 2, 1)),
+    (B, 5120, 0, 299, (5, 2, 2, 1)), (B, 5120, 0, 301, (4, 3, 2, 1)), (B, 4872, 0, 900, (6, 2, 2, 1)), (B, 4864, 0, 900, (6, 2, 2, 1)),
+    (B, 1000, 0, 21, (1, 2, 2, 4)), (B, 1000, 0, 149, (1, 2, 2, 6)), (B, 1000, 0, 151, (1, 2, 2, 4)), (B, 1024, 0, 160, (1, 2, 2, 3)),
+    (B, 2264, 0, 21, (5, 1, 2, 2)), (B, 2264, 0, 19, (5, 1, 2, 1)), (B, 1400, 0, 80, (3, 1, 2, 3)), (B, 1536, 0, 80, (3, 1, 1, 3)),
+    (B, 3584, 0, 290, (8, 1, 2, 1)), (B, 3584, 0, 310, (4, 2, 1, 3)), (B, 3400, 0, 900, (8, 1, 2, 1)), (B, 6144, 0, 80, (8, 2, 1, 1)),
+    (B, 640, 1, 80, (1, 3, 2, 4)), (B, 640, 1, 70, (1, 3, 2, 3)),
+])
+def test_entry_on_both_sides_of_a_size(family, D, dtype, mb, shape):
+    assert T.lnmod_table_shape(family, D, dtype, rows_of(mb, D, dtype)) == (0, shape)
+
+
+def test_backward_of_many_short_segments_keeps_the_other_shape():
+    d = T.lnmod_describe_launch
+    T_ = rows_of(120, 3584, 0)
+    assert d(True, None, T_ // 512, T_, True, 3584, 0, 0).startswith("bwd_seg_kernel<bf16_io, 1, 8, 2,")
+    assert d(True, None, T_ // 500, T_, True, 3584, 0, 0).startswith("bwd_seg_kernel<bf16_io, 2, 4, 1,")
+
+
+@pytest.mark.parametrize("D", [776, 1152, 1400, 1536, 2048, 2264, 2560, 3400, 3584, 4096, 4872, 5120, 6144])
+def test_one_samples_workspace_holds_its_plan_in_every_class(D):
+    for mb in (1, 11, 13, 19, 21, 71, 73, 149, 151, 299, 301, 700):
+        for dtype in (0, 1):
+            rows = rows_of(mb, D, dtype)
+            for recompute in (False, True):
+                text = T.lnmod_describe_launch(True, None, 1, rows, False, D, dtype, 0, recompute)
+                slots = int(text.split("slots=")[1])
+                assert slots * 2 * D * 4 <= lnmod.lnmod_backward_workspace_bytes(1, rows, D, lnmod.LNMOD_PER_SAMPLE), (mb, dtype)
