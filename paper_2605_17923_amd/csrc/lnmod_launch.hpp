@@ -502,6 +502,28 @@ inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {3, 2, 2, 3}, {3, 2, 2, 2}, {4, 2, 1, 3}, {4, 2, 2, 1},
             {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 2, 1},
             {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};
+        // Shares of the former entry's time from 470 random problems as at launch_mb above.  Up to 20 MB a block has one to four
+        // steps: one chunk per lane and one block per CU halve the slots and shorten the chain of the first row.
+        const int col = (nchunks + 31) / 32;
+        if (T > 0 && launch_mb(T, nchunks, 0, 20)) {
+            if (col == 6) return {3, 1, 2, 2};                               // D = 1288 ... 1536: 0.87, 1.0
+            if (nchunks == 256) return {4, 1, 2, 1};                         // D = 2048: 0.75, 0.80
+            if (col == 7 || col == 8) return {4, 1, 2, 2};                   // D = 1544 ... 2040: 0.82, 0.87
+            if (nchunks == 320) return {5, 1, 1, 1};                         // D = 2560: 0.83, 0.95
+            if (col == 9 || col == 10) return {5, 1, 1, 2};                  // D = 2056 ... 2552: 0.90, 0.97
+            if (col == 11 || col == 12) return {6, 1, 2, 1};                 // D = 2568 ... 3072: 0.89, 1.07
+            if (col == 14) return {8, 1, 2, 1};                              // D = 3336 ... 3584: 0.82, 0.97
+            if (nchunks > 512 && nchunks < 768) return {4, 3, 1, 1};         // D = 4104 ... 6136: 0.90, 0.97
+        }
+        if (launch_mb(T, nchunks, 20, 72)) {
+            if (col == 3 && launch_mb(T, nchunks, 36, 72)) return {1, 2, 2, 8};      // D = 520 ... 768: 0.95, 1.02 (27 MB 1.07)
+            if (col == 7 || col == 8) return {4, 1, 2, 2};                   // D = 1544 ... 2048: 0.905, 0.97
+        }
+        if (launch_mb(T, nchunks, 72, 150) && nchunks == 256) return {4, 1, 2, 2};       // D = 2048: 0.95, 0.97
+        if (launch_mb(T, nchunks, 72, 300)) {
+            if (col == 4 && nchunks < 128) return {1, 2, 1, 8};              // D = 776 ... 1016: 0.935, 0.965
+            if (col == 16 && nchunks < 512) return {4, 2, 1, 2};             // D = 3848 ... 4088: 0.93, 0.95
+        }
         if (short_launch(T, nchunks)) return table_entry(tab_short, nchunks, dtype);
         if (nchunks > 32 && nchunks < 64) return {1, 1, 2, 8};       // D = 264 ... 504: 0.97 in the mean, 264 258 against 281 us
         return fine_entry(tab, nchunks, dtype);

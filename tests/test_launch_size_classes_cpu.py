@@ -28,6 +28,13 @@ def rows_of(mb, D, dtype):
     (B, 2264, 0, 21, (5, 1, 2, 2)), (B, 2264, 0, 19, (5, 1, 2, 1)), (B, 1400, 0, 80, (3, 1, 2, 3)), (B, 1536, 0, 80, (3, 1, 1, 3)),
     (B, 3584, 0, 290, (8, 1, 2, 1)), (B, 3584, 0, 310, (4, 2, 1, 3)), (B, 3400, 0, 900, (8, 1, 2, 1)), (B, 6144, 0, 80, (8, 2, 1, 1)),
     (B, 640, 1, 80, (1, 3, 2, 4)), (B, 640, 1, 70, (1, 3, 2, 3)),
+    # backward without saved statistics
+    (RC, 1536, 0, 19, (3, 1, 2, 2)), (RC, 1536, 0, 21, (1, 3, 2, 4)), (RC, 2048, 0, 19, (4, 1, 2, 1)), (RC, 2048, 0, 149, (4, 1, 2, 2)),
+    (RC, 2048, 0, 151, (2, 2, 1, 4)), (RC, 1544, 0, 71, (4, 1, 2, 2)), (RC, 1544, 0, 73, (2, 2, 1, 6)), (RC, 2560, 0, 19, (5, 1, 1, 1)),
+    (RC, 2552, 0, 19, (5, 1, 1, 2)), (RC, 2560, 0, 21, (3, 2, 2, 3)), (RC, 2568, 0, 19, (6, 1, 2, 1)), (RC, 3072, 0, 19, (6, 1, 2, 1)),
+    (RC, 3080, 0, 19, (4, 2, 1, 3)), (RC, 3584, 0, 19, (8, 1, 2, 1)), (RC, 4096, 0, 19, (4, 2, 2, 1)), (RC, 4104, 0, 19, (4, 3, 1, 1)),
+    (RC, 6136, 0, 19, (4, 3, 1, 1)), (RC, 6144, 0, 19, (4, 3, 2, 1)), (RC, 640, 0, 35, (1, 2, 2, 4)), (RC, 640, 0, 37, (1, 2, 2, 8)),
+    (RC, 1000, 0, 290, (1, 2, 1, 8)), (RC, 1000, 0, 310, (1, 2, 2, 4)), (RC, 4088, 0, 290, (4, 2, 1, 2)), (RC, 4088, 0, 310, (4, 2, 2, 1)),
 ])
 def test_entry_on_both_sides_of_a_size(family, D, dtype, mb, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows_of(mb, D, dtype)) == (0, shape)
