@@ -36,6 +36,13 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 6144
             {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        // size classes (see launch_mb): 510 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+        if (N > 0 && launch_mb(N, nchunks, 0, 20)) {
+            if (nchunks > 128 && nchunks < 160) return {1, 3, 2, 16};        // D = 1032 ... 1272: 0.945, 0.985
+            if (nchunks == 320) return {3, 2, 2, 8};                         // D = 2560: 0.945, 1.01
+            if (nchunks == 384) return {3, 2, 2, 6};                         // D = 3072: 0.96, 1.0
+        }
+        if (nchunks == 512 && launch_mb(N, nchunks, 20, 72)) return {4, 2, 2, 3};       // D = 4096: 0.965, 0.995
         // two tensors are read: beyond D = 3840 the short entries lost 3 to 8 % at 62 MB (D = 5128 44.4 -> 48.1 us),
         // below it they still win there at most widths (1808 53.1 -> 47.0, 3136 48.7 -> 43.5)
         const bool few = short_launch(N, nchunks) && (nchunks <= 480 || N * nchunks * 16 <= 36000000);
@@ -52,6 +59,15 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 4, 2, 2}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
+        // the table was timed at 150 MB; 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+        const int col = (nchunks + 63) / 64;
+        if (N > 0 && launch_mb(N, nchunks, 0, 72)) {
+            if (col == 5) return {1, 6, 2, 6};                               // D = 1028 ... 1280: 0.92, 0.98
+            if (col == 7 || col == 8) return {2, 4, 2, launch_mb(N, nchunks, 0, 20) ? 4 : 6};    // D = 1540 ... 2048: 0.90, 0.98
+            if (col == 9 || nchunks == 768) return {3, 4, 2, 3};             // D = 2052 ... 2304: 0.935, 0.98; 3072: 0.88, 0.95
+            if (nchunks == 1536 && launch_mb(N, nchunks, 20, 72)) return {8, 4, 2, 2};       // D = 6144: 0.92, 0.97
+        }
+        if (N > 0 && col == 14 && launch_mb(N, nchunks, 0, 300)) return {4, 4, 2, 2};        // D = 3332 ... 3584: 0.90, 0.95
         return fine_entry(tab32, nchunks, dtype);
     }
     if (dtype == 0) {
@@ -65,6 +81,8 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
+        // D = 3336 ... 3584 up to 20 MB: 0.92, 0.98 of the time
+        if (N > 0 && nchunks > 416 && nchunks <= 448 && launch_mb(N, nchunks, 0, 20)) return {4, 2, 2, 1};
         // D = 1800 ... 1984: the entry was timed at 2048 (1920, 62, 95 and 173 MB: 67.7, 99.1, 176 us against 70.1, 103, 186)
         if (nchunks > 224 && nchunks <= 248) return {2, 2, 2, 3};
         // D = 3080 ... 3320 from 62 MB on: 0.94 to 0.985 of the time (3160 190 against 203 us); aligned rows 4 to 6 % slower
@@ -81,6 +99,9 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
         {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
+    // 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+    if (nchunks > 320 && nchunks <= 384) return {2, 4, 2, 3};                        // D = 1284 ... 1536: 0.955, 1.01
+    if (nchunks > 832 && nchunks <= 896 && (N == 0 || launch_mb(N, nchunks, 20, kAnyMB))) return {4, 4, 2, 2};   // D = 3332 ... 3584: 0.96, 0.985
     return fine_entry(tab32, nchunks, dtype);
 }
 
