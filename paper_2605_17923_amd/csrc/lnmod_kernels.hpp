@@ -1075,13 +1075,16 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
         if (tid < kWave) {
             if constexpr (G > 1) {
                 // the G groups of lanes, in a fixed order
+                const auto from = [](float v, uint32_t at) {
+                    return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(static_cast<int>(at * 4u), __builtin_bit_cast(int, v)));
+                };
 #pragma unroll
-                for (int off = FL; off < kWave; off <<= 1) {
+                for (uint32_t off = FL; off < kWave; off <<= 1) {
                     if constexpr (V == 1) {
-                        acc += __shfl_xor(acc, off);
+                        acc += from(acc, tid ^ off);
                     } else {
 #pragma unroll
-                        for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off);
+                        for (int e = 0; e < V; ++e) acc[e] += from(acc[e], tid ^ off);
                     }
                 }
             }

@@ -100,7 +100,8 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
     // 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
-    if (nchunks > 320 && nchunks <= 384) return {2, 4, 2, 3};                        // D = 1284 ... 1536: 0.955, 1.01
+    // D = 1284 ... 1536: 0.95, 0.985 (two blocks up to 20 MB: 2008 rows 20.1 us, with three 21.2)
+    if (nchunks > 320 && nchunks <= 384) return {2, 4, 2, N > 0 && launch_mb(N, nchunks, 0, 20) ? 2 : 3};
     if (nchunks > 832 && nchunks <= 896 && (N == 0 || launch_mb(N, nchunks, 20, kAnyMB))) return {4, 4, 2, 2};   // D = 3332 ... 3584: 0.96, 0.985
     return fine_entry(tab32, nchunks, dtype);
 }
