@@ -135,7 +135,8 @@ constexpr int64_t kReduceMaxGrid = int64_t(1) << 20;
 
 hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     const ReduceShape sh = reduce_shape(r.seg.nseg, r.nsum, r.D, clusters, r.nb);
-    const int V = sh.V, W = sh.W, G = sh.G;
+    const int W = sh.W, G = sh.G;
+    constexpr int V = ReduceShape::V;
     const int per_block = kWave / G * V;
     const int64_t gx = (r.D + per_block - 1) / per_block;
     int64_t gz = kReduceMaxGrid / (gx * r.nsum);
@@ -145,11 +146,9 @@ hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     r.grid_segs = static_cast<int32_t>(gz);
     r.cluster_of = Divider(static_cast<uint32_t>(r.rows_per_cluster));
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(r.nsum), static_cast<unsigned>(gz)), block(W * kWave);
-    if (G == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 4>), grid, block, 0, st, r);
-    else if (G == 2) hipLaunchKernelGGL((bwd_reduce_kernel<4, 2>), grid, block, 0, st, r);
-    else if (V == 4) hipLaunchKernelGGL((bwd_reduce_kernel<4, 1>), grid, block, 0, st, r);
-    else if (V == 2) hipLaunchKernelGGL((bwd_reduce_kernel<2, 1>), grid, block, 0, st, r);
-    else hipLaunchKernelGGL((bwd_reduce_kernel<1, 1>), grid, block, 0, st, r);
+    if (G == 4) hipLaunchKernelGGL((bwd_reduce_kernel<V, 4>), grid, block, 0, st, r);
+    else if (G == 2) hipLaunchKernelGGL((bwd_reduce_kernel<V, 2>), grid, block, 0, st, r);
+    else hipLaunchKernelGGL((bwd_reduce_kernel<V, 1>), grid, block, 0, st, r);
     return hipGetLastError();
 }
 

@@ -948,9 +948,9 @@ void bwd_seg_kernel(const BwdArgs a) {
 }
 
 // Second pass: out[k][m, d] = sum of the partial slots of segment m, k < nsum (dshift, dscale
-// and, for the gated operator, dgate).  A block takes 64 / G * V consecutive features of one sum of
-// one segment; its parts = waves * G groups of 64 / G lanes split the slots (part p takes slots p, p + parts, ...,
-// in ascending order), and the part sums are then added in a fixed order.  V, G and the waves are chosen
+// and, for the gated operator, dgate).  A block takes 64 / G * V consecutive features (V = 4: D is a multiple of 4) of
+// one sum of one segment; its parts = waves * G groups of 64 / G lanes split the slots (part p takes slots p, p + parts,
+// ..., in ascending order), and the part sums are then added in a fixed order.  G and the waves are chosen
 // from the shapes alone, so results repeat bit for bit.
 struct ReduceArgs {
     const float* ws;         // [nslots][nsum][D]
@@ -968,31 +968,25 @@ struct ReduceArgs {
     Divider cluster_of;      // row -> cluster
 };
 
+template <int V> using floats = float __attribute__((ext_vector_type(V)));
+
 // Stores V consecutive sums.  A caller that keeps the gradients in the tensors' own type used to
 // cast the float32 sums with a kernel per gradient (4.4 us each on top of a 5 us second pass); the
 // rounding to nearest even is the same one.
-template <int V, typename VEC>
-__device__ inline void store_sums(void* out, int64_t at, const VEC& v, bool bf16) {
+template <int V>
+__device__ inline void store_sums(void* out, int64_t at, const floats<V>& v, bool bf16) {
     if (!bf16) {
         // the weight gradients of the query/key normalisation may be at any float's address
-        typedef VEC loose __attribute__((aligned(4)));
+        typedef floats<V> loose __attribute__((aligned(4)));
         *reinterpret_cast<loose*>(static_cast<float*>(out) + at) = v;
         return;
     }
-    __bf16* p = static_cast<__bf16*>(out) + at;
-    if constexpr (V == 1) {
-        *p = static_cast<__bf16>(v);
-    } else {
-        typedef __bf16 half_vec __attribute__((ext_vector_type(V)));
-        *reinterpret_cast<half_vec*>(p) = __builtin_convertvector(v, half_vec);
-    }
+    typedef __bf16 half_vec __attribute__((ext_vector_type(V)));
+    *reinterpret_cast<half_vec*>(static_cast<__bf16*>(out) + at) = __builtin_convertvector(v, half_vec);
 }
 
 constexpr int kReduceWaves = 16;     // most waves a reduce block may have
 constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 16 / V slot loads
-
-template <int V> struct FVec { typedef float type __attribute__((ext_vector_type(V))); };
-template <> struct FVec<1> { typedef float type; };
 
 // blockIdx.x is the block of features, blockIdx.y the sum; the segments are blockIdx.z, blockIdx.z + grid_segs, ...,
 // so that any segment count the interface admits stays inside the launch limits.
@@ -1004,9 +998,9 @@ template <> struct FVec<1> { typedef float type; };
 // slot beyond the last is read as the last one and not added, one LDS stage for waves and lane groups together.  With
 // 64-bit slot numbers and addresses, two divisions and a branch per load it took 4.5 us on 512 x 1536 fp32 rows, now 3.7;
 // on 32 760 x 1536 6.0, now 5.3; on 6449 x 2048 in ten samples 5.0, now 4.4.
-template <int V, int G = 1>
+template <int V, int G>
 __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const ReduceArgs a) {
-    using vec = typename FVec<V>::type;
+    using vec = floats<V>;
     constexpr uint32_t kReduceBatch = kReduceFloats / V;
     constexpr uint32_t FL = kWave / G;            // lanes along the features; G groups of them take different slots
     __shared__ vec red[kReduceWaves * kWave];
@@ -1080,12 +1074,8 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
                 };
 #pragma unroll
                 for (uint32_t off = FL; off < kWave; off <<= 1) {
-                    if constexpr (V == 1) {
-                        acc += from(acc, tid ^ off);
-                    } else {
 #pragma unroll
-                        for (int e = 0; e < V; ++e) acc[e] += from(acc[e], tid ^ off);
-                    }
+                    for (int e = 0; e < V; ++e) acc[e] += from(acc[e], tid ^ off);
                 }
             }
             if (part == 0 && !dead) store_sums<V>(out, m * a.D + d, acc, a.out_bf16 != 0);

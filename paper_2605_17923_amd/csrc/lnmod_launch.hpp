@@ -747,33 +747,25 @@ inline bool bwd_shape_within(int64_t T, int64_t nseg, int64_t D, int dtype, bool
     return false;
 }
 
-// Shape of the second pass: V features per lane, W waves per block, G groups of lanes per wave
-// that take different slots (a block covers 64 / G * V features).  Wide blocks need enough
-// (segment, sum, feature-block) triples to fill the chip; a wave should have about four slots
-// to add, and a block never more than 16 waves.
+// Shape of the second pass: W waves per block, G groups of lanes per wave that take different slots; a lane adds
+// V features (16 bytes of a slot; D is a multiple of 4), so a block covers 64 / G * V of them.  Wide blocks need enough
+// (segment, sum, feature-block) triples to fill the chip; with fewer of them a block is narrower and its waves cover
+// several slots per load (second pass of 75 600 x 5120: 6.1 -> 4.9 us with 16 bytes per lane instead of 4, of 32 760 x
+// 1536: 8.9 -> 6.4, of 2 x 32 760 x 5120: 9.9 -> 7.8; eight groups of 32 features or sixteen of 16 were slower again).
+// A group should have about one batch of slots to add, and a block never more than 16 waves.
 struct ReduceShape {
-    int V;
-    int W;
-    int G = 1;      // groups of lanes of a wave that take different slots (then V = 4)
+    static constexpr int V = 4;
+    int W = 1;
+    int G = 1;
 };
 
 inline ReduceShape reduce_shape(int64_t nseg, int nsum, int64_t D, int64_t clusters, int64_t nb) {
-    ReduceShape sh{1, 1};
+    ReduceShape sh;
     const int64_t triples = nseg * nsum;
-    if (triples * ((D + 255) / 256) >= 256) sh.V = 4;
-    else if (triples * ((D + 127) / 128) >= 256) sh.V = 2;
+    if (triples * ((D + 255) / 256) < 256) sh.G = triples * ((D + 127) / 128) >= 256 ? 2 : 4;
     const int64_t slots = nb * (1 + (clusters - 1) / nseg);   // typical slots of one segment
-    // Narrow blocks keep their width but read 16 bytes per lane: the lanes form 4 / V groups that take
-    // different slots, so a wave covers several slots per load (second pass of 75 600 x 5120:
-    // 6.1 -> 4.9 us, of 32 760 x 1536: 8.9 -> 6.4, of 2 x 32 760 x 5120: 9.9 -> 7.8; eight groups of
-    // 32 features or sixteen of 16 were slower again)
-    if (sh.V < 4 && D % 4 == 0) {
-        sh.G = 4 / sh.V;
-        sh.V = 4;
-        while (sh.W < 16 && sh.W * 2 * sh.G <= slots) sh.W *= 2;
-        return sh;
-    }
-    while (sh.W < 16 && sh.W * 2 * 4 <= slots) sh.W *= 2;
+    const int64_t each = sh.G == 1 ? 4 : sh.G;
+    while (sh.W < 16 && sh.W * 2 * each <= slots) sh.W *= 2;
     return sh;
 }
 
