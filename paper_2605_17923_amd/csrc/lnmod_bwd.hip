@@ -146,9 +146,19 @@ hipError_t launch_reduce(ReduceArgs r, int64_t clusters, hipStream_t st) {
     r.grid_segs = static_cast<int32_t>(gz);
     r.cluster_of = Divider(static_cast<uint32_t>(r.rows_per_cluster));
     const dim3 grid(static_cast<unsigned>(gx), static_cast<unsigned>(r.nsum), static_cast<unsigned>(gz)), block(W * kWave);
-    if (G == 4) hipLaunchKernelGGL((bwd_reduce_kernel<V, 4>), grid, block, 0, st, r);
-    else if (G == 2) hipLaunchKernelGGL((bwd_reduce_kernel<V, 2>), grid, block, 0, st, r);
-    else hipLaunchKernelGGL((bwd_reduce_kernel<V, 1>), grid, block, 0, st, r);
+    using Many = void (*)(ReduceArgs);
+    using One = void (*)(OneSegmentReduceArgs);
+    // one sample: up to 96 blocks of 256 features, so always the narrow blocks
+    if (G == 4 && r.seg.nseg == 1 && r.seg.cu == nullptr) {
+        const OneSegmentReduceArgs one{r.ws, {r.out[0], r.out[1], r.out[2]}, static_cast<int32_t>(clusters * r.nb), r.D, r.nsum, r.out_bf16, W};
+        hipLaunchKernelGGL(static_cast<One>(bwd_reduce_kernel<V, 4>), grid, block, 0, st, one);
+    } else if (G == 4) {
+        hipLaunchKernelGGL(static_cast<Many>(bwd_reduce_kernel<V, 4>), grid, block, 0, st, r);
+    } else if (G == 2) {
+        hipLaunchKernelGGL(static_cast<Many>(bwd_reduce_kernel<V, 2>), grid, block, 0, st, r);
+    } else {
+        hipLaunchKernelGGL(static_cast<Many>(bwd_reduce_kernel<V, 1>), grid, block, 0, st, r);
+    }
     return hipGetLastError();
 }
 

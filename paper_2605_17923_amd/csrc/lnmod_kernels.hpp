@@ -968,6 +968,13 @@ struct ReduceArgs {
     Divider cluster_of;      // row -> cluster
 };
 
+// The same for one segment that is no table's: all `count` slots are its own.
+struct OneSegmentReduceArgs {
+    const float* ws;
+    void* out[3];
+    int32_t count, D, nsum, out_bf16, waves;
+};
+
 template <int V> using floats = float __attribute__((ext_vector_type(V)));
 
 // Stores V consecutive sums.  A caller that keeps the gradients in the tensors' own type used to
@@ -998,8 +1005,15 @@ constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 
 // slot beyond the last is read as the last one and not added, one LDS stage for waves and lane groups together.  With
 // 64-bit slot numbers and addresses, two divisions and a branch per load it took 4.5 us on 512 x 1536 fp32 rows, now 3.7;
 // on 32 760 x 1536 6.0, now 5.3; on 6449 x 2048 in ten samples 5.0, now 4.4.
-template <int V, int G>
-__global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const ReduceArgs a) {
+//
+// One segment (a single sample, and the weight gradients of the query/key normalisation) has an instantiation without
+// table, clusters and loop.  While it shared the code for many, the query/key backward on rows of more than one head took
+// 0.3 to 0.5 us more than with a kernel of its own (90 problems of 0.5 to 12 MB: 1.025 of the time in the mean, now 1.004);
+// the backward of one sample takes 0.98 of its time (60 problems of 0.5 to 30 MB).  The same code with the slot count as an
+// argument that skips the table at run time took 0.992.
+template <int V, int G, typename Args>
+__device__ inline void reduce_slots(const Args& a) {
+    constexpr bool kOne = std::is_same<Args, OneSegmentReduceArgs>::value;
     using vec = floats<V>;
     constexpr uint32_t kReduceBatch = kReduceFloats / V;
     constexpr uint32_t FL = kWave / G;            // lanes along the features; G groups of them take different slots
@@ -1011,49 +1025,34 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
     const uint32_t which = blockIdx.y;
     const bool dead = d >= static_cast<uint32_t>(a.D);
     const uint32_t d_off = dead ? 0u : d * 4u;    // lanes beyond the row read its start
-    const uint32_t pitch = static_cast<uint32_t>(a.nsum * a.D) * 4u, nb = static_cast<uint32_t>(a.nb);
+    const uint32_t pitch = static_cast<uint32_t>(a.nsum * a.D) * 4u;
     void* const out = which == 0 ? a.out[0] : which == 1 ? a.out[1] : a.out[2];
-    int64_t m = blockIdx.z;
-    do {                                          // the grid has no more blocks along the segments than there are
-        int32_t n0 = 0, n1 = static_cast<int32_t>(a.T);
-        if (a.seg.cu) {
-            n0 = table_at(a.seg.cu, m);
-            n1 = table_at(a.seg.cu, m + 1);
-            if (n0 < 0) n0 = 0;                   // a malformed table must not lead outside ws
-            if (n1 > static_cast<int32_t>(a.T)) n1 = static_cast<int32_t>(a.T);
-        } else if (a.seg.nseg > 1) {
-            n0 = static_cast<int32_t>(m) * static_cast<int32_t>(a.seg.S);
-            n1 = n0 + static_cast<int32_t>(a.seg.S);
-        }
+
+    // the sum of the `count` slots from byte `first` on, to row m of the output; again: the block has another one after it
+    const auto reduce = [&](int64_t first, uint32_t count, int64_t m, bool again) {
+        const char* base = reinterpret_cast<const char*>(a.ws) + first + which * static_cast<uint32_t>(a.D) * 4u;
         vec acc = vec(0.0f);
-        if (n1 > n0) {
-            // clusters c_lo..c_hi touch this segment; (cluster c, segment m) owns slots (c+m)*nb ..
-            const uint32_t c_lo = a.cluster_of(static_cast<uint32_t>(n0)), c_hi = a.cluster_of(static_cast<uint32_t>(n1 - 1));
-            const uint32_t count = (c_hi - c_lo + 1) * nb;           // at most the blocks of the launch
-            const char* base = reinterpret_cast<const char*>(a.ws) + (c_lo + m) * nb * static_cast<int64_t>(pitch) +
-                               which * static_cast<uint32_t>(a.D) * 4u;
-            // kReduceBatch slots requested before the first is added; the additions keep slot order
-            for (uint32_t s0 = part; s0 - part < count; s0 += kReduceBatch * parts) {
-                vec v[kReduceBatch];
+        // kReduceBatch slots requested before the first is added; the additions keep slot order
+        for (uint32_t s0 = part; s0 - part < count; s0 += kReduceBatch * parts) {
+            vec v[kReduceBatch];
 #pragma unroll
-                for (uint32_t u = 0; u < kReduceBatch; ++u) {
-                    const uint32_t su = s0 + u * parts;
-                    v[u] = *reinterpret_cast<const vec*>(base + ((su < count ? su : count - 1) * pitch + d_off));
-                }
-#pragma unroll
-                for (uint32_t u = 0; u < kReduceBatch; ++u) acc += s0 + u * parts < count ? v[u] : vec(0.0f);
+            for (uint32_t u = 0; u < kReduceBatch; ++u) {
+                const uint32_t su = s0 + u * parts;
+                v[u] = *reinterpret_cast<const vec*>(base + ((su < count ? su : count - 1) * pitch + d_off));
             }
+#pragma unroll
+            for (uint32_t u = 0; u < kReduceBatch; ++u) acc += s0 + u * parts < count ? v[u] : vec(0.0f);
         }
         if (W > 1) {
             red[tid] = acc;
             __syncthreads();
             if (tid < kWave) {                    // the waves' sums in wave order: W is a power of two
                 vec v[kReduceWaves];
-                const auto add = [&](auto first, auto last) {
+                const auto add = [&](auto from, auto to) {
 #pragma unroll
-                    for (uint32_t k = first; k < last; ++k) v[k] = red[k * kWave + tid];
+                    for (uint32_t k = from; k < to; ++k) v[k] = red[k * kWave + tid];
 #pragma unroll
-                    for (uint32_t k = first; k < last; ++k) acc += v[k];
+                    for (uint32_t k = from; k < to; ++k) acc += v[k];
                 };
                 using std::integral_constant;
                 if (W == 16) {
@@ -1064,7 +1063,7 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
                     if (W >= 8) add(integral_constant<uint32_t, 4>{}, integral_constant<uint32_t, 8>{});
                 }
             }
-            if (m + a.grid_segs < a.seg.nseg) __syncthreads();       // red is written again in the next round
+            if (again) __syncthreads();           // red is written again in the next round
         }
         if (tid < kWave) {
             if constexpr (G > 1) {
@@ -1080,9 +1079,42 @@ __global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const R
             }
             if (part == 0 && !dead) store_sums<V>(out, m * a.D + d, acc, a.out_bf16 != 0);
         }
-        m += a.grid_segs;
-    } while (m < a.seg.nseg);
+    };
+
+    if constexpr (kOne) {
+        reduce(0, static_cast<uint32_t>(a.count), 0, false);
+    } else {
+        const uint32_t nb = static_cast<uint32_t>(a.nb);
+        int64_t m = blockIdx.z;
+        do {                                      // the grid has no more blocks along the segments than there are
+            int32_t n0, n1;
+            if (a.seg.cu) {
+                n0 = table_at(a.seg.cu, m);
+                n1 = table_at(a.seg.cu, m + 1);
+                if (n0 < 0) n0 = 0;               // a malformed table must not lead outside ws
+                if (n1 > static_cast<int32_t>(a.T)) n1 = static_cast<int32_t>(a.T);
+            } else {
+                n0 = static_cast<int32_t>(m) * static_cast<int32_t>(a.seg.S);
+                n1 = n0 + static_cast<int32_t>(a.seg.S);
+            }
+            int64_t first = 0;
+            uint32_t count = 0;
+            if (n1 > n0) {
+                // clusters c_lo..c_hi touch this segment; (cluster c, segment m) owns slots (c+m)*nb ..
+                const uint32_t c_lo = a.cluster_of(static_cast<uint32_t>(n0)), c_hi = a.cluster_of(static_cast<uint32_t>(n1 - 1));
+                count = (c_hi - c_lo + 1) * nb;   // at most the blocks of the launch
+                first = (c_lo + m) * nb * static_cast<int64_t>(pitch);
+            }
+            reduce(first, count, m, m + a.grid_segs < a.seg.nseg);
+            m += a.grid_segs;
+        } while (m < a.seg.nseg);
+    }
 }
+
+template <int V, int G>
+__global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const ReduceArgs a) { reduce_slots<V, G>(a); }
+template <int V, int G>
+__global__ __launch_bounds__(kReduceWaves* kWave) void bwd_reduce_kernel(const OneSegmentReduceArgs a) { reduce_slots<V, G>(a); }
 
 // =============================================================================================
 // Bandwidth reference (not part of the fused path)
