@@ -33,10 +33,9 @@ inline int64_t total_tokens(int64_t B, int64_t S) {
 
 inline size_t workspace_bytes(int64_t nseg, int64_t T, int64_t D, const Shape* force = nullptr) {
     // partial-sum slots of the plan with the most of them (neither the dtype nor whether the
-    // statistics will be recomputed is an argument of the query).  For one sample the shapes of short and
-    // long launches both count, so that the size never falls as the rows grow: a caller may size its
-    // workspace once, for its longest clip (at D = 6152 ... 6656 a short recompute launch has two blocks per
-    // CU where a long one has one).
+    // statistics will be recomputed is an argument of the query).  For one sample the shapes of every size class
+    // count, so that the size never falls as the rows grow: a caller may size its workspace once, for its longest
+    // clip (at D = 6152 ... 6656 a short recompute launch has two blocks per CU where a long one has one).
     int64_t slots = 0;
     for (int v = 0; v < 4; ++v) {
         const int dtype = v & 1;

@@ -42,15 +42,16 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
             {4, 3, 1, 1}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 1, 1},   // D <= 7168
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 2}};   // D <= 8192
-        // size classes and widths between two multiples of 256 (see launch_mb): 480 random problems of 4 to 300 MB, every
+        // size classes and widths between two multiples of 256 (see SizeRule): 480 random problems of 4 to 300 MB, every
         // compiled shape, the shares of the entry's time (mean, worst)
-        const int col = (nchunks + 31) / 32;
-        if (T > 0 && col == 3 && nchunks < 96 && launch_mb(T, nchunks, 0, 20)) return {1, 2, 2, 12};   // D = 520 ... 760: 0.93, 0.98
-        if (col == 3 && nchunks < 96 && launch_mb(T, nchunks, 20, 150)) return {1, 2, 2, 8};     // the same: 0.94, 0.99
-        if (col == 4 && nchunks < 128 && launch_mb(T, nchunks, 72, 300)) return {1, 2, 2, 4};    // D = 776 ... 1016: 0.965, 0.985
-        if (col == 8 && nchunks < 256 && launch_mb(T, nchunks, 72, 150)) return {2, 2, 1, 4};    // D = 1800 ... 2040: 0.95, 0.965
-        if (T > 0 && col == 10 && launch_mb(T, nchunks, 0, 20)) return {4, 2, 1, 3};             // D = 2312 ... 2560: 0.955, 0.995
-        if (nchunks == 448 && launch_mb(T, nchunks, 20, 72)) return {4, 2, 1, 3};                // D = 3584: 0.97, 0.995
+        static const SizeRule rules[] = {
+            {65, 95, 0, 20, {1, 2, 2, 12}},          // D = 520 ... 760: 0.93, 0.98
+            {65, 95, 20, 150, {1, 2, 2, 8}},         // the same: 0.94, 0.99
+            {97, 127, 72, 300, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.965, 0.985
+            {225, 255, 72, 150, {2, 2, 1, 4}},       // D = 1800 ... 2040: 0.95, 0.965
+            {289, 320, 0, 20, {4, 2, 1, 3}},         // D = 2312 ... 2560: 0.955, 0.995
+            {448, 448, 20, 72, {4, 2, 1, 3}}};       // D = 3584: 0.97, 0.995
+        if (const Shape* sh = size_rule(rules, nchunks, T)) return *sh;
         // D = 4360 ... 6656: two tensors are read, and at 71 MB the short entries lost 3 to 8 % (5048 52.5 -> 56.4 us);
         // elsewhere they win up to 72 MB at most widths (2568 56.2 against 60.3 us, 7096 44.9 against 47.2)
         if (short_launch(T, nchunks) && (nchunks <= 544 || nchunks > 832 || T * nchunks * 16 <= 48000000))

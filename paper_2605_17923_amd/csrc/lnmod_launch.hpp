@@ -273,15 +273,28 @@ inline Shape fine_entry(const Shape (&tab)[33], int nchunks, int dtype) {
 }
 
 // Between the short launches and the 770 MB the long tables were timed at the winners are others again at some widths, and
-// at the widths between two multiples of 256 an entry timed at the multiple can be far off.  The rules below come from
-// 1200 random bf16 and 380 fp32 problems with x of 4 to 300 MB (widths of models and any others, one sample, several and
-// packed), on each of which every compiled shape was timed; a rule stands where one shape took at least 2 % less time in the
-// mean of its class, and gives the shares of the former entry's time (mean, worst).  Most end at 300 MB, where the long
-// tables were timed; those without an upper end were timed on one sample of 400 and 800 MB too, at three or four widths.
-constexpr int64_t kAnyMB = int64_t(1) << 40;
+// at the widths between two multiples of 256 an entry timed at the multiple can be far off.  A size rule names the shape for a
+// range of widths and sizes; the first one that holds goes before the tables.
+constexpr int32_t kAnyMB = 2000000000;
 inline bool launch_mb(int64_t T, int nchunks, int64_t lo, int64_t hi) {      // x of more than lo and at most hi MB
     const int64_t bytes = T * nchunks * 16;
     return bytes > lo * 1000000 && bytes <= hi * 1000000;
+}
+
+struct SizeRule {
+    int first, last;               // chunks of a row
+    int32_t over, to;              // x of more than `over` and at most `to` MB
+    Shape sh;
+    int rows_per_seg = 0;          // only where samples or segments have at least that many rows in the mean
+};
+
+// The shape of the first rule that holds, or nullptr.  T: the token count if known (0: not known, no rule holds).
+template <int N>
+inline const Shape* size_rule(const SizeRule (&rules)[N], int nchunks, int64_t T, int64_t nseg = 0) {
+    if (T <= 0) return nullptr;
+    for (const SizeRule& r : rules)
+        if (nchunks >= r.first && nchunks <= r.last && launch_mb(T, nchunks, r.over, r.to) && T >= r.rows_per_seg * nseg) return &r.sh;
+    return nullptr;
 }
 
 // Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
@@ -325,30 +338,24 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 2, 2}, {5, 3, 1, 1}, {5, 3, 1, 1},   // D <= 7168
             {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
+        static const SizeRule rules[] = {
+            {161, 192, 20, 72, {1, 3, 2, 12}},       // D = 1288 ... 1536: 0.935, 0.99
+            {353, 384, 20, 72, {2, 3, 2, 6}},        // D = 2824 ... 3072: 0.93, 1.03
+            {512, 512, 24, 72, {4, 2, 1, 3}},        // D = 4096: 0.975, 1.005
+            {353, 384, 12, 20, {2, 3, 1, 6}},        // D = 2824 ... 3072: 0.90, 0.97
+            {448, 448, 12, 72, {4, 2, 1, 4}},        // D = 3584: 0.965, 1.01
+            {737, 767, 0, 72, {4, 3, 2, 3}},         // D = 5896 ... 6136: 0.94, 0.99
+            {97, 112, 72, 150, {1, 2, 1, 12}},       // D = 776 ... 896: 0.935, 1.0
+            {193, 223, 72, 150, {2, 2, 2, 4}},       // D = 1544 ... 1784: 0.97, 0.995
+            {545, 575, 72, 150, {4, 3, 2, 2}},       // D = 4360 ... 4600: 0.96, 1.03
+            {512, 512, 72, 150, {4, 2, 1, 3}},       // D = 4096: 0.94, 0.98
+            {640, 640, 72, 150, {5, 2, 1, 2}},       // D = 5120: 0.93, 0.96
+            {353, 384, 72, 300, {2, 3, 1, 4}},       // D = 2824 ... 3072: 0.955, 0.995
+            {481, 511, 72, 300, {4, 2, 1, 3}},       // D = 3848 ... 4088: 0.80, 0.80
+            // D = 4872 ... 5112: 0.71, 0.77; 400 MB 0.70, 800 MB 0.72 (4976: 386 -> 271 us)
+            {609, 639, 72, kAnyMB, {4, 3, 1, 2}}};
+        if (const Shape* sh = size_rule(rules, nchunks, T)) return one_step(*sh, T);
         const int col = (nchunks + 31) / 32;
-        if (launch_mb(T, nchunks, 20, 72)) {
-            if (col == 6) return {1, 3, 2, 12};                              // D = 1288 ... 1536: 0.935, 0.99
-            if (col == 12) return {2, 3, 2, 6};                              // D = 2824 ... 3072: 0.93, 1.03
-            if (nchunks == 512 && launch_mb(T, nchunks, 24, 72)) return {4, 2, 1, 3};     // D = 4096: 0.975, 1.005
-        }
-        if (short_launch(T, nchunks) && T > 0) {
-            if (col == 12 && launch_mb(T, nchunks, 12, 20)) return {2, 3, 1, 6};  // D = 2824 ... 3072: 0.90, 0.97
-            if (nchunks == 448 && launch_mb(T, nchunks, 12, 72)) return {4, 2, 1, 4};     // D = 3584: 0.965, 1.01
-            if (col == 24 && nchunks < 768) return one_step({4, 3, 2, 3}, T);     // D = 5896 ... 6136: 0.94, 0.99
-        }
-        if (launch_mb(T, nchunks, 72, 150)) {
-            if (col == 4 && nchunks <= 112) return {1, 2, 1, 12};            // D = 776 ... 896: 0.935, 1.0
-            if (col == 7 && nchunks < 224) return {2, 2, 2, 4};              // D = 1544 ... 1784: 0.97, 0.995
-            if (col == 18 && nchunks < 576) return {4, 3, 2, 2};             // D = 4360 ... 4600: 0.96, 1.03
-            if (nchunks == 512) return {4, 2, 1, 3};                         // D = 4096: 0.94, 0.98
-            if (nchunks == 640) return {5, 2, 1, 2};                         // D = 5120: 0.93, 0.96
-        }
-        if (launch_mb(T, nchunks, 72, 300)) {
-            if (col == 12) return {2, 3, 1, 4};                              // D = 2824 ... 3072: 0.955, 0.995
-            if (col == 16 && nchunks < 512) return {4, 2, 1, 3};             // D = 3848 ... 4088: 0.80, 0.80
-        }
-        // D = 4872 ... 5112: 0.71, 0.77; 400 MB 0.70, 800 MB 0.72 (4976: 386 -> 271 us)
-        if (launch_mb(T, nchunks, 72, kAnyMB) && col == 20 && nchunks < 640) return {4, 3, 1, 2};
         if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
         // D = 2632 ... 2808: 100 MB 1 to 3 % slower, 300 MB 1 to 5 % faster; narrower (2568, 2616) 2 to 5 % slower at both
         if (unaligned_rows(nchunks) && col == 11 && nchunks > 328) return {4, 2, 1, 3};
@@ -386,16 +393,52 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
         {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2}, {6, 4, 1, 2},   // D <= 6144
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 2}, {8, 4, 2, 2}};   // D <= 8192
-    if (short_launch(T, nchunks) && T > 0) {
-        if (nchunks > 576 && nchunks <= 640) return one_step({3, 4, 2, 3}, T);       // D = 2308 ... 2560: 0.91, 1.01
-        if (nchunks == 1536 && launch_mb(T, nchunks, 20, 72)) return {6, 4, 2, 1};   // D = 6144: 0.92, 0.94
-    }
+    static const SizeRule rules32[] = {
+        {577, 640, 0, 72, {3, 4, 2, 3}},             // D = 2308 ... 2560: 0.91, 1.01
+        {1536, 1536, 20, 72, {6, 4, 2, 1}}};         // D = 6144: 0.92, 0.94
+    if (const Shape* sh = size_rule(rules32, nchunks, T)) return one_step(*sh, T);
     if (short_launch(T, nchunks)) return one_step(fine_entry(tab32_short, nchunks, dtype), T);
     return fine_entry(tab32, nchunks, dtype);
 }
 
-// nseg: samples or segments if known (0: not known, or one).
-inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) {
+constexpr int64_t kNarrowBwdBytes = 40000000;        // the line of the backward at D = 264 ... 504, below
+
+// Size rules of the backwards.  Their shapes all count in bwd_most_slots_one_sample.
+constexpr SizeRule kBwdRules[] = {
+    {131, 159, 0, 20, {3, 1, 2, 2}},             // D = 1048 ... 1272: 0.90, 1.01
+    {609, 640, 0, 20, {8, 2, 1, 1}},             // D = 4872 ... 5120: 0.96, 0.99
+    {97, 127, 20, 72, {1, 2, 2, 4}},             // D = 776 ... 1016: 0.94, 1.04
+    {257, 287, 20, 72, {5, 1, 2, 2}},            // D = 2056 ... 2296: 0.95, 0.99
+    {97, 127, 72, 150, {1, 2, 2, 6}},            // D = 776 ... 1016: 0.85, 1.0
+    // D = 3584: 0.93, 1.0; on segments of fewer than 512 rows in the mean up to 1.09
+    {448, 448, 72, 300, {8, 1, 2, 1}, 512},
+    {640, 640, 72, 300, {5, 2, 2, 1}},           // D = 5120: 0.98, 1.0
+    {97, 127, 150, kAnyMB, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.87, 0.92; 800 MB 0.80
+    {161, 191, 72, kAnyMB, {3, 1, 2, 3}},        // D = 1288 ... 1528: 0.95, 1.05; 800 MB 0.91
+    {417, 447, 72, kAnyMB, {8, 1, 2, 1}, 512},   // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
+    {609, 639, 72, kAnyMB, {6, 2, 2, 1}},        // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
+    {768, 768, 72, kAnyMB, {8, 2, 1, 1}}};       // D = 6144: 0.975, 0.99; 800 MB 0.98
+// D = 516 ... 764: 0.90, 0.95 up to 150 MB, the same within 1 % of the best beyond
+constexpr SizeRule kBwdRules32[] = {{129, 191, 72, 300, {1, 3, 2, 4}}};
+// Without saved statistics.  Up to 20 MB a block has one to four steps: one chunk per lane and one block per CU halve the
+// slots and shorten the chain of the first row.
+constexpr SizeRule kRcBwdRules[] = {
+    {161, 192, 0, 20, {3, 1, 2, 2}},             // D = 1288 ... 1536: 0.87, 1.0
+    {256, 256, 0, 20, {4, 1, 2, 1}},             // D = 2048: 0.75, 0.80
+    {193, 255, 0, 20, {4, 1, 2, 2}},             // D = 1544 ... 2040: 0.82, 0.87
+    {320, 320, 0, 20, {5, 1, 1, 1}},             // D = 2560: 0.83, 0.95
+    {257, 319, 0, 20, {5, 1, 1, 2}},             // D = 2056 ... 2552: 0.90, 0.97
+    {321, 384, 0, 20, {6, 1, 2, 1}},             // D = 2568 ... 3072: 0.89, 1.07
+    {417, 448, 0, 20, {8, 1, 2, 1}},             // D = 3336 ... 3584: 0.82, 0.97
+    {513, 767, 0, 20, {4, 3, 1, 1}},             // D = 4104 ... 6136: 0.90, 0.97
+    {65, 96, 36, 72, {1, 2, 2, 8}},              // D = 520 ... 768: 0.95, 1.02 (27 MB 1.07)
+    {193, 256, 20, 72, {4, 1, 2, 2}},            // D = 1544 ... 2048: 0.905, 0.97
+    {256, 256, 72, 150, {4, 1, 2, 2}},           // D = 2048: 0.95, 0.97
+    {97, 127, 72, 300, {1, 2, 1, 8}},            // D = 776 ... 1016: 0.935, 0.965
+    {481, 511, 72, 300, {4, 2, 1, 2}}};          // D = 3848 ... 4088: 0.93, 0.95
+
+// The tables, without the size rules.
+inline Shape bwd_table(int nchunks, int dtype, int64_t T) {
     if (dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 2, 8},
@@ -419,31 +462,10 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) 
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
         // D = 264 ... 504 from 40 MB on: the entries were timed at D = 512, where every lane has a chunk (89 and 250 MB:
         // D = 264 80.5 us against 94.5, 190 against 236; 440 153 against 167; 28 MB 32.6 against 30.4)
-        if (nchunks > 32 && nchunks < 64 && (T == 0 || T * nchunks * 16 > 40000000)) return {1, 1, 2, 8};
-        const int col = (nchunks + 31) / 32;
-        if (T > 0 && launch_mb(T, nchunks, 0, 20)) {
-            if (col == 5 && nchunks > 130 && nchunks < 160) return {3, 1, 2, 2};     // D = 1048 ... 1272: 0.90, 1.01
-            if (col == 20) return {8, 2, 1, 1};                              // D = 4872 ... 5120: 0.96, 0.99
-        }
-        if (launch_mb(T, nchunks, 20, 72)) {
-            if (col == 4 && nchunks < 128) return {1, 2, 2, 4};              // D = 776 ... 1016: 0.94, 1.04
-            if (col == 9 && nchunks < 288) return {5, 1, 2, 2};              // D = 2056 ... 2296: 0.95, 0.99
-        }
-        if (launch_mb(T, nchunks, 72, 300)) {
-            if (col == 4 && nchunks < 128 && launch_mb(T, nchunks, 72, 150)) return {1, 2, 2, 6};     // D = 776 ... 1016: 0.85, 1.0
-            // D = 3584: 0.93, 1.0; on segments of fewer than 512 rows in the mean up to 1.09
-            if (nchunks == 448 && T >= 512 * nseg) return {8, 1, 2, 1};
-            if (nchunks == 640) return {5, 2, 2, 1};                         // D = 5120: 0.98, 1.0
-        }
-        if (launch_mb(T, nchunks, 72, kAnyMB)) {
-            if (col == 4 && nchunks < 128) return {1, 2, 2, 4};              // D = 776 ... 1016: 0.87, 0.92; 800 MB 0.80
-            if (col == 6 && nchunks < 192) return {3, 1, 2, 3};              // D = 1288 ... 1528: 0.95, 1.05; 800 MB 0.91
-            if (col == 14 && nchunks < 448 && T >= 512 * nseg) return {8, 1, 2, 1};     // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
-            if (col == 20 && nchunks < 640) return {6, 2, 2, 1};             // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
-            if (nchunks == 768) return {8, 2, 1, 1};                         // D = 6144: 0.975, 0.99; 800 MB 0.98
-        }
+        if (nchunks > 32 && nchunks < 64 && (T == 0 || T * nchunks * 16 > kNarrowBwdBytes)) return {1, 1, 2, 8};
         if (short_launch(T, nchunks)) return fine_entry(tab_short, nchunks, dtype);
         if (unaligned_rows(nchunks)) {
+            const int col = (nchunks + 31) / 32;
             // six widths of each column, 100 and 300 MB, as a share of the entry's time
             if (col == 11) return {6, 1, 2, 1};                              // D = 2568 ... 2808: 0.91 ... 1.0
             if (col == 21) return {6, 2, 1, 1};                              // D = 5128 ... 5368: 0.96 ... 1.0
@@ -474,16 +496,20 @@ inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) 
         {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 1, 1}, {6, 4, 2, 1},   // D <= 6144
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 2, 1}};   // D <= 8192
-    // D = 516 ... 764: 0.90, 0.95 up to 150 MB, the same within 1 % of the best beyond
-    if (launch_mb(T, nchunks, 72, 300) && nchunks > 128 && nchunks < 192) return {1, 3, 2, 4};
     return short_launch(T, nchunks) ? fine_entry(tab32_short, nchunks, dtype) : fine_entry(tab32, nchunks, dtype);
+}
+
+// nseg: samples or segments if known (0: not known, or one).
+inline Shape bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) {
+    const Shape* sh = dtype == 0 ? size_rule(kBwdRules, nchunks, T, nseg) : size_rule(kBwdRules32, nchunks, T, nseg);
+    return sh ? *sh : bwd_table(nchunks, dtype, T);
 }
 
 // Backward that forms the statistics again from x.  It has one more dependent chain per step
 // (per-wave mean, four wave sums, the merge with a division and a square root), which fewer waves per
 // row with more chunks each, or two blocks per CU, hide better than the shapes above; it runs 2 to 20 %
 // behind the backward that reads the saved statistics (D = 5120: 14 %).
-inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0) {
+inline Shape rc_bwd_table(int nchunks, int dtype, int64_t T) {
     if (dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 2, 8},
@@ -502,28 +528,6 @@ inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {3, 2, 2, 3}, {3, 2, 2, 2}, {4, 2, 1, 3}, {4, 2, 2, 1},
             {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 2, 1},
             {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};
-        // Shares of the former entry's time from 470 random problems as at launch_mb above.  Up to 20 MB a block has one to four
-        // steps: one chunk per lane and one block per CU halve the slots and shorten the chain of the first row.
-        const int col = (nchunks + 31) / 32;
-        if (T > 0 && launch_mb(T, nchunks, 0, 20)) {
-            if (col == 6) return {3, 1, 2, 2};                               // D = 1288 ... 1536: 0.87, 1.0
-            if (nchunks == 256) return {4, 1, 2, 1};                         // D = 2048: 0.75, 0.80
-            if (col == 7 || col == 8) return {4, 1, 2, 2};                   // D = 1544 ... 2040: 0.82, 0.87
-            if (nchunks == 320) return {5, 1, 1, 1};                         // D = 2560: 0.83, 0.95
-            if (col == 9 || col == 10) return {5, 1, 1, 2};                  // D = 2056 ... 2552: 0.90, 0.97
-            if (col == 11 || col == 12) return {6, 1, 2, 1};                 // D = 2568 ... 3072: 0.89, 1.07
-            if (col == 14) return {8, 1, 2, 1};                              // D = 3336 ... 3584: 0.82, 0.97
-            if (nchunks > 512 && nchunks < 768) return {4, 3, 1, 1};         // D = 4104 ... 6136: 0.90, 0.97
-        }
-        if (launch_mb(T, nchunks, 20, 72)) {
-            if (col == 3 && launch_mb(T, nchunks, 36, 72)) return {1, 2, 2, 8};      // D = 520 ... 768: 0.95, 1.02 (27 MB 1.07)
-            if (col == 7 || col == 8) return {4, 1, 2, 2};                   // D = 1544 ... 2048: 0.905, 0.97
-        }
-        if (launch_mb(T, nchunks, 72, 150) && nchunks == 256) return {4, 1, 2, 2};       // D = 2048: 0.95, 0.97
-        if (launch_mb(T, nchunks, 72, 300)) {
-            if (col == 4 && nchunks < 128) return {1, 2, 1, 8};              // D = 776 ... 1016: 0.935, 0.965
-            if (col == 16 && nchunks < 512) return {4, 2, 1, 2};             // D = 3848 ... 4088: 0.93, 0.95
-        }
         if (short_launch(T, nchunks)) return table_entry(tab_short, nchunks, dtype);
         if (nchunks > 32 && nchunks < 64) return {1, 1, 2, 8};       // D = 264 ... 504: 0.97 in the mean, 264 258 against 281 us
         return fine_entry(tab, nchunks, dtype);
@@ -539,6 +543,11 @@ inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0) {
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}, {8, 4, 1, 1}};   // D <= 8192
     return fine_entry(tab32, nchunks, dtype);
+}
+
+inline Shape rc_bwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) {
+    const Shape* sh = dtype == 0 ? size_rule(kRcBwdRules, nchunks, T, nseg) : nullptr;
+    return sh ? *sh : rc_bwd_table(nchunks, dtype, T);
 }
 
 // The table's entry, or the shape the call carries (Problem::force).  A forced shape that does not
@@ -691,8 +700,8 @@ inline BwdLaunch plan_bwd(int64_t T, int64_t nseg, int64_t D, int dtype, bool pe
         L.pl = plan_rows(T, static_cast<int64_t>(kNumCU) * L.sh.per_cu, L.sh.R);
         return L;
     }
-    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T)
-                                              : bwd_shape(L.nchunks, dtype, T, nseg));
+    L.sh = pick_shape(force, recompute ? rc_bwd_shape(L.nchunks, dtype, T, nseg)
+                                       : bwd_shape(L.nchunks, dtype, T, nseg));
     // a row moves 3 D elements (dy, x, dx), a slot 2 D floats that are written and read back
     const double elem = dtype == 0 ? 2.0 : 4.0;
     const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 3.0 * elem / 5.8e6;
@@ -707,19 +716,26 @@ inline RowPlan bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype, bool reco
     return plan_bwd(T, nseg, D, dtype, false, recompute, force).pl;
 }
 
-// Slots of this backward on one sample of T rows with the shape of the size class that has most of them:
-// a bound on the plan's slots that does not fall as T grows.
+// Slots of this backward on one sample of T rows with the shape that has most of them at this width, whatever the size:
+// a bound on the plan's slots that does not fall as T grows.  These are all the shapes a width can get: the tables' for
+// short and long launches and between them for one beyond kNarrowBwdBytes, and those of its size rules.
 inline int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool recompute) {
     if (T <= 0) return 0;
     const int nchunks = static_cast<int>(D / (dtype == 0 ? 8 : 4));
     int64_t most = 0;
-    // one launch of each size class the shapes tell apart (see launch_mb), and an unknown, long one
-    for (const int64_t mb : {10, 30, 100, 200, 400, 0}) {
-        const int64_t rows = mb * 1000000 / (nchunks * 16);
-        const Shape sh = recompute ? rc_bwd_shape(nchunks, dtype, rows) : bwd_shape(nchunks, dtype, rows);
+    const auto with = [&](const Shape& sh) {
         const int64_t slots = bwd_slots(plan_rows(T, static_cast<int64_t>(kNumCU) * sh.per_cu, sh.R), 1);
         if (slots > most) most = slots;
-    }
+    };
+    const auto with_rules = [&](const auto& rules) {
+        for (const SizeRule& r : rules)
+            if (nchunks >= r.first && nchunks <= r.last) with(r.sh);
+    };
+    for (const int64_t rows : {int64_t(0), int64_t(1), kNarrowBwdBytes / (nchunks * 16) + 1})
+        with(recompute ? rc_bwd_table(nchunks, dtype, rows) : bwd_table(nchunks, dtype, rows));
+    if (dtype == 0 && recompute) with_rules(kRcBwdRules);
+    else if (dtype == 0) with_rules(kBwdRules);
+    else if (!recompute) with_rules(kBwdRules32);
     return most;
 }
 

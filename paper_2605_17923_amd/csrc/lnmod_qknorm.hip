@@ -36,13 +36,13 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 6144
             {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
-        // size classes (see launch_mb): 510 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
-        if (N > 0 && launch_mb(N, nchunks, 0, 20)) {
-            if (nchunks > 128 && nchunks < 160) return {1, 3, 2, 16};        // D = 1032 ... 1272: 0.945, 0.985
-            if (nchunks == 320) return {3, 2, 2, 8};                         // D = 2560: 0.945, 1.01
-            if (nchunks == 384) return {3, 2, 2, 6};                         // D = 3072: 0.96, 1.0
-        }
-        if (nchunks == 512 && launch_mb(N, nchunks, 20, 72)) return {4, 2, 2, 3};       // D = 4096: 0.965, 0.995
+        // size classes (see SizeRule): 510 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+        static const SizeRule rules[] = {
+            {129, 159, 0, 20, {1, 3, 2, 16}},        // D = 1032 ... 1272: 0.945, 0.985
+            {320, 320, 0, 20, {3, 2, 2, 8}},         // D = 2560: 0.945, 1.01
+            {384, 384, 0, 20, {3, 2, 2, 6}},         // D = 3072: 0.96, 1.0
+            {512, 512, 20, 72, {4, 2, 2, 3}}};       // D = 4096: 0.965, 0.995
+        if (const Shape* sh = size_rule(rules, nchunks, N)) return *sh;
         // two tensors are read: beyond D = 3840 the short entries lost 3 to 8 % at 62 MB (D = 5128 44.4 -> 48.1 us),
         // below it they still win there at most widths (1808 53.1 -> 47.0, 3136 48.7 -> 43.5)
         const bool few = short_launch(N, nchunks) && (nchunks <= 480 || N * nchunks * 16 <= 36000000);
@@ -60,14 +60,15 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
         // the table was timed at 150 MB; 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
-        const int col = (nchunks + 63) / 64;
-        if (N > 0 && launch_mb(N, nchunks, 0, 72)) {
-            if (col == 5) return {1, 6, 2, 6};                               // D = 1028 ... 1280: 0.92, 0.98
-            if (col == 7 || col == 8) return {2, 4, 2, launch_mb(N, nchunks, 0, 20) ? 4 : 6};    // D = 1540 ... 2048: 0.90, 0.98
-            if (col == 9 || nchunks == 768) return {3, 4, 2, 3};             // D = 2052 ... 2304: 0.935, 0.98; 3072: 0.88, 0.95
-            if (nchunks == 1536 && launch_mb(N, nchunks, 20, 72)) return {8, 4, 2, 2};       // D = 6144: 0.92, 0.97
-        }
-        if (N > 0 && col == 14 && launch_mb(N, nchunks, 0, 300)) return {4, 4, 2, 2};        // D = 3332 ... 3584: 0.90, 0.95
+        static const SizeRule rules32[] = {
+            {257, 320, 0, 72, {1, 6, 2, 6}},         // D = 1028 ... 1280: 0.92, 0.98
+            {385, 512, 0, 20, {2, 4, 2, 4}},         // D = 1540 ... 2048: 0.90, 0.98
+            {385, 512, 20, 72, {2, 4, 2, 6}},
+            {513, 576, 0, 72, {3, 4, 2, 3}},         // D = 2052 ... 2304: 0.935, 0.98
+            {768, 768, 0, 72, {3, 4, 2, 3}},         // D = 3072: 0.88, 0.95
+            {1536, 1536, 20, 72, {8, 4, 2, 2}},      // D = 6144: 0.92, 0.97
+            {833, 896, 0, 300, {4, 4, 2, 2}}};       // D = 3332 ... 3584: 0.90, 0.95
+        if (const Shape* sh = size_rule(rules32, nchunks, N)) return *sh;
         return fine_entry(tab32, nchunks, dtype);
     }
     if (dtype == 0) {
@@ -81,8 +82,8 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
-        // D = 3336 ... 3584 up to 20 MB: 0.92, 0.98 of the time
-        if (N > 0 && nchunks > 416 && nchunks <= 448 && launch_mb(N, nchunks, 0, 20)) return {4, 2, 2, 1};
+        static const SizeRule rules[] = {{417, 448, 0, 20, {4, 2, 2, 1}}};       // D = 3336 ... 3584: 0.92, 0.98
+        if (const Shape* sh = size_rule(rules, nchunks, N)) return *sh;
         // D = 1800 ... 1984: the entry was timed at 2048 (1920, 62, 95 and 173 MB: 67.7, 99.1, 176 us against 70.1, 103, 186)
         if (nchunks > 224 && nchunks <= 248) return {2, 2, 2, 3};
         // D = 3080 ... 3320 from 62 MB on: 0.94 to 0.985 of the time (3160 190 against 203 us); aligned rows 4 to 6 % slower
@@ -92,17 +93,17 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
     static const Shape tab32[33] = {
         {1, 1, 2, 6},
         {1, 1, 2, 6}, {1, 2, 2, 4}, {1, 3, 2, 4}, {1, 4, 2, 4},   // D <= 1024
-        {2, 4, 2, 3}, {1, 6, 2, 4}, {2, 4, 2, 3}, {2, 4, 2, 3},   // D <= 2048
+        {2, 4, 2, 3}, {2, 4, 2, 3}, {2, 4, 2, 3}, {2, 4, 2, 3},   // D <= 2048
         {3, 4, 2, 2}, {3, 4, 2, 2}, {3, 4, 2, 2}, {3, 4, 2, 2},   // D <= 3072
-        {4, 4, 2, 2}, {4, 4, 2, 1}, {4, 4, 2, 1}, {4, 4, 2, 1},   // D <= 4096
+        {4, 4, 2, 2}, {4, 4, 2, 2}, {4, 4, 2, 1}, {4, 4, 2, 1},   // D <= 4096
         {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 1}, {5, 4, 2, 1},   // D <= 5120
         {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
-    // 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
-    // D = 1284 ... 1536: 0.95, 0.985 (two blocks up to 20 MB: 2008 rows 20.1 us, with three 21.2)
-    if (nchunks > 320 && nchunks <= 384) return {2, 4, 2, N > 0 && launch_mb(N, nchunks, 0, 20) ? 2 : 3};
-    if (nchunks > 832 && nchunks <= 896 && (N == 0 || launch_mb(N, nchunks, 20, kAnyMB))) return {4, 4, 2, 2};   // D = 3332 ... 3584: 0.96, 0.985
+    // D = 1284 ... 1536 and 3332 ... 3584 as timed on 4 to 300 MB; up to 20 MB 2008 rows of 1536 take 20.1 us with two blocks
+    // per CU and 21.2 with three
+    static const SizeRule rules32[] = {{321, 384, 0, 20, {2, 4, 2, 2}}, {833, 896, 0, 20, {4, 4, 2, 1}}};
+    if (const Shape* sh = size_rule(rules32, nchunks, N)) return *sh;
     return fine_entry(tab32, nchunks, dtype);
 }
 

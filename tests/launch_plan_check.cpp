@@ -1,5 +1,6 @@
 // Host-side invariants of the launch planning in csrc/lnmod_launch.hpp (compiled and run by
 // test_launch_plan_cpu.py; no device code, no GPU).
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <random>
@@ -43,6 +44,26 @@ int main() {
                 check_shape("tok_bwd", dtype, D, n, six);
                 check_shape("tok_bwd without dshift", dtype, D, n, five);
                 CHECK(six.K == five.K && six.VPL == five.VPL, "dtype %d D %d T %lld: the two add a row in another order", dtype, D, (long long)T);
+            }
+        }
+    }
+    // on both sides of every line between size classes: shapes that are compiled, and the bound on one sample's slots
+    for (int dtype = 0; dtype < 2; ++dtype) {
+        const int E = dtype == 0 ? 8 : 4;
+        for (int D = E; D <= kMaxD; D += E) {
+            const int n = D / E;
+            int64_t before[2] = {0, 0};
+            for (int mb = 1; mb <= 1000; mb += mb < 320 ? 1 : 20) {
+                for (int64_t T = std::max<int64_t>(1, mb * int64_t(1000000) / (n * 16)), last = T + 1; T <= last; ++T) {
+                    check_shape("fwd", dtype, D, n, fwd_shape(n, dtype, T));
+                    for (int rc = 0; rc < 2; ++rc) {
+                        check_shape(rc ? "rc_bwd" : "bwd", dtype, D, n, rc ? rc_bwd_shape(n, dtype, T) : bwd_shape(n, dtype, T));
+                        const int64_t most = bwd_most_slots_one_sample(T, D, dtype, rc != 0);
+                        const int64_t own = bwd_slots(bwd_plan(T, 1, D, dtype, rc != 0), 1);
+                        CHECK(own <= most && most >= before[rc], "D %d T %lld rc %d: %lld slots, bound %lld, before %lld", D, (long long)T, rc, (long long)own, (long long)most, (long long)before[rc]);
+                        before[rc] = most;
+                    }
+                }
             }
         }
     }
