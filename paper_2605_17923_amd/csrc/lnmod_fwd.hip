@@ -180,7 +180,7 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
     Shape sh = fwd_shape(L.nchunks, p.dtype);                      // the comparators' starting point
     if (mode == kModToken) sh = pick_shape(p.force, tok_fwd_shape(L.nchunks, p.dtype));
     if (mode == kModSegment || mode == kModFlat) {
-        Shape tab = fwd_shape(L.nchunks, p.dtype, p.T);
+        Shape tab = fwd_shape(L.nchunks, p.dtype, p.T, p.nseg);
         // D = 1536, flat: four blocks per CU at every token count (24 mixed segments, 152 880 rows:
         // 159 us against 182 with three)
         if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0 && !short_launch(p.T, L.nchunks)) tab.per_cu = 4;

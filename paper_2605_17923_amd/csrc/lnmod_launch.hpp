@@ -281,26 +281,32 @@ inline bool launch_mb(int64_t T, int nchunks, int64_t lo, int64_t hi) {      // 
     return bytes > lo * 1000000 && bytes <= hi * 1000000;
 }
 
+constexpr int64_t kAnySegs = int64_t(1) << 40;
 struct SizeRule {
     int first, last;               // chunks of a row
     int32_t over, to;              // x of more than `over` and at most `to` MB
     Shape sh;
+    int64_t segs_from = 0;         // samples or segments
+    int64_t segs_to = kAnySegs;
     int rows_per_seg = 0;          // only where samples or segments have at least that many rows in the mean
+    bool unaligned = false;        // only rows that are not whole 128-byte lines
 };
+
+// Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
+// share lines with their neighbours, and at a few widths that turns the order of the shapes around, so the
+// entries there were timed on such rows too, at six to eleven widths of each column (the unaligned_rows lines below).
+inline bool unaligned_rows(int nchunks) { return nchunks % 8 != 0; }
 
 // The shape of the first rule that holds, or nullptr.  T: the token count if known (0: not known, no rule holds).
 template <int N>
 inline const Shape* size_rule(const SizeRule (&rules)[N], int nchunks, int64_t T, int64_t nseg = 0) {
     if (T <= 0) return nullptr;
     for (const SizeRule& r : rules)
-        if (nchunks >= r.first && nchunks <= r.last && launch_mb(T, nchunks, r.over, r.to) && T >= r.rows_per_seg * nseg) return &r.sh;
+        if (nchunks >= r.first && nchunks <= r.last && launch_mb(T, nchunks, r.over, r.to) && nseg >= r.segs_from &&
+            nseg <= r.segs_to && T >= r.rows_per_seg * nseg && !(r.unaligned && !unaligned_rows(nchunks)))
+            return &r.sh;
     return nullptr;
 }
-
-// Rows that are not whole 128-byte lines (16-byte chunks, eight to a line): a wave's pieces of a row then
-// share lines with their neighbours, and at a few widths that turns the order of the shapes around, so the
-// entries there were timed on such rows too, at six to eleven widths of each column (the unaligned_rows lines below).
-inline bool unaligned_rows(int nchunks) { return nchunks % 8 != 0; }
 
 // A forward whose rows all find a block of their own takes one row per step: 366 rows at D = 2680 4.8 us
 // against 5.5 with two.
@@ -325,8 +331,8 @@ inline Shape fwd_short_entry(int nchunks) {
     return fine_entry(tab_short, nchunks, 0);
 }
 
-// T: the token count if known (0: not known, a long launch).
-inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
+// T: the token count if known (0: not known, a long launch); nseg: samples or segments (0: not known, or one).
+inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) {
     if (dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 2, 16},
@@ -354,7 +360,7 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
             {481, 511, 72, 300, {4, 2, 1, 3}},       // D = 3848 ... 4088: 0.80, 0.80
             // D = 4872 ... 5112: 0.71, 0.77; 400 MB 0.70, 800 MB 0.72 (4976: 386 -> 271 us)
             {609, 639, 72, kAnyMB, {4, 3, 1, 2}}};
-        if (const Shape* sh = size_rule(rules, nchunks, T)) return one_step(*sh, T);
+        if (const Shape* sh = size_rule(rules, nchunks, T, nseg)) return one_step(*sh, T);
         const int col = (nchunks + 31) / 32;
         if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
         // D = 2632 ... 2808: 100 MB 1 to 3 % slower, 300 MB 1 to 5 % faster; narrower (2568, 2616) 2 to 5 % slower at both
@@ -394,9 +400,9 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0) {
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 1, 1},   // D <= 7168
         {8, 4, 1, 1}, {8, 4, 2, 1}, {8, 4, 2, 2}, {8, 4, 2, 2}};   // D <= 8192
     static const SizeRule rules32[] = {
-        {577, 640, 0, 72, {3, 4, 2, 3}},             // D = 2308 ... 2560: 0.91, 1.01
-        {1536, 1536, 20, 72, {6, 4, 2, 1}}};         // D = 6144: 0.92, 0.94
-    if (const Shape* sh = size_rule(rules32, nchunks, T)) return one_step(*sh, T);
+        {577, 640, 12, 72, {3, 4, 2, 3}},            // D = 2308 ... 2560: 0.888, 1.02 (236)
+        {1536, 1536, 20, 72, {6, 4, 2, 1}, 6}};      // D = 6144: 0.942, 1.02 (65); on one to four samples 1.04, up to 1.21
+    if (const Shape* sh = size_rule(rules32, nchunks, T, nseg)) return one_step(*sh, T);
     if (short_launch(T, nchunks)) return one_step(fine_entry(tab32_short, nchunks, dtype), T);
     return fine_entry(tab32, nchunks, dtype);
 }
@@ -411,11 +417,11 @@ constexpr SizeRule kBwdRules[] = {
     {257, 287, 20, 72, {5, 1, 2, 2}},            // D = 2056 ... 2296: 0.95, 0.99
     {97, 127, 72, 150, {1, 2, 2, 6}},            // D = 776 ... 1016: 0.85, 1.0
     // D = 3584: 0.93, 1.0; on segments of fewer than 512 rows in the mean up to 1.09
-    {448, 448, 72, 300, {8, 1, 2, 1}, 512},
+    {448, 448, 72, 300, {8, 1, 2, 1}, 0, kAnySegs, 512},
     {640, 640, 72, 300, {5, 2, 2, 1}},           // D = 5120: 0.98, 1.0
     {97, 127, 150, kAnyMB, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.87, 0.92; 800 MB 0.80
     {161, 191, 72, kAnyMB, {3, 1, 2, 3}},        // D = 1288 ... 1528: 0.95, 1.05; 800 MB 0.91
-    {417, 447, 72, kAnyMB, {8, 1, 2, 1}, 512},   // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
+    {417, 447, 72, kAnyMB, {8, 1, 2, 1}, 0, kAnySegs, 512},     // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
     {609, 639, 72, kAnyMB, {6, 2, 2, 1}},        // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
     {768, 768, 72, kAnyMB, {8, 2, 1, 1}}};       // D = 6144: 0.975, 0.99; 800 MB 0.98
 // D = 516 ... 764: 0.90, 0.95 up to 150 MB, the same within 1 % of the best beyond
@@ -729,7 +735,7 @@ inline int64_t bwd_most_slots_one_sample(int64_t T, int64_t D, int dtype, bool r
     };
     const auto with_rules = [&](const auto& rules) {
         for (const SizeRule& r : rules)
-            if (nchunks >= r.first && nchunks <= r.last) with(r.sh);
+            if (nchunks >= r.first && nchunks <= r.last && r.segs_from <= 1) with(r.sh);
     };
     for (const int64_t rows : {int64_t(0), int64_t(1), kNarrowBwdBytes / (nchunks * 16) + 1})
         with(recompute ? rc_bwd_table(nchunks, dtype, rows) : bwd_table(nchunks, dtype, rows));

@@ -22,7 +22,7 @@ def rows_of(mb, D, dtype):
     (F, 784, 0, 100, (1, 2, 1, 12)), (F, 904, 0, 100, (1, 2, 2, 4)), (F, 1640, 0, 140, (2, 2, 2, 4)), (F, 1792, 0, 140, (2, 2, 1, 6)),
     (F, 5120, 0, 140, (5, 2, 1, 2)), (F, 5120, 0, 160, (5, 2, 2, 1)), (F, 5112, 0, 160, (4, 3, 1, 2)), (F, 4872, 0, 900, (4, 3, 1, 2)),
     (F, 4088, 0, 290, (4, 2, 1, 3)), (F, 4088, 0, 310, (4, 2, 2, 1)), (F, 4400, 0, 149, (4, 3, 2, 2)), (F, 4400, 0, 151, (4, 3, 1, 2)),
-    (F, 2560, 1, 40, (3, 4, 2, 3)), (F, 2304, 1, 40, (3, 4, 2, 4)), (F, 6144, 1, 40, (6, 4, 2, 1)), (F, 6144, 1, 19, (6, 4, 1, 2)),
+    (F, 2560, 1, 40, (3, 4, 2, 3)), (F, 2304, 1, 40, (3, 4, 2, 4)), (F, 6144, 1, 40, (6, 4, 1, 2)), (F, 6144, 1, 19, (6, 4, 1, 2)), (F, 2560, 1, 11, (3, 4, 1, 8)), (F, 2560, 1, 13, (3, 4, 2, 3)),
     # backward
     (B, 1040, 0, 19, (3, 1, 1, 4)), (B, 1152, 0, 19, (3, 1, 2, 2)), (B, 1152, 0, 21, (3, 1, 1, 4)), (B, 5120, 0, 19, (8, 2, 1, 1)), (B, 5120, 0, 21, (5, 2, 2, 1)),
     (B, 5120, 0, 299, (5, 2, 2, 1)), (B, 5120, 0, 301, (4, 3, 2, 1)), (B, 4872, 0, 900, (6, 2, 2, 1)), (B, 4864, 0, 900, (6, 2, 2, 1)),
@@ -50,6 +50,18 @@ def rows_of(mb, D, dtype):
 ])
 def test_entry_on_both_sides_of_a_size(family, D, dtype, mb, shape):
     assert T.lnmod_table_shape(family, D, dtype, rows_of(mb, D, dtype)) == (0, shape)
+
+
+# what, D, dtype, MB, segments on one side and the other, (waves, chunks per lane, rows per step) of each
+@pytest.mark.parametrize("family,D,dtype,mb,segments,shapes", [
+    (F, 6144, 1, 40, (5, 6), ((6, 4, 1), (6, 4, 2))),
+    (F, 6144, 1, 71, (1, 8), ((6, 4, 1), (6, 4, 2))),
+])
+def test_entry_on_both_sides_of_a_segment_count(family, D, dtype, mb, segments, shapes):
+    for n, shape in zip(segments, shapes):
+        text = T.lnmod_describe_launch(family != F, None, n, rows_of(mb, D, dtype), True, D, dtype, 0, family == RC)
+        v, k, r = (int(t) for t in text.split("_io, ")[1].split(", ")[:3])
+        assert (k, v, r) == shape, text
 
 
 def test_backward_of_many_short_segments_keeps_the_other_shape():
