@@ -424,8 +424,9 @@ constexpr SizeRule kBwdRules[] = {
     {417, 447, 72, kAnyMB, {8, 1, 2, 1}, 0, kAnySegs, 512},     // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
     {609, 639, 72, kAnyMB, {6, 2, 2, 1}},        // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
     {768, 768, 72, kAnyMB, {8, 2, 1, 1}}};       // D = 6144: 0.975, 0.99; 800 MB 0.98
-// D = 516 ... 764: 0.90, 0.95 up to 150 MB, the same within 1 % of the best beyond
-constexpr SizeRule kBwdRules32[] = {{129, 191, 72, 300, {1, 3, 2, 4}}};
+constexpr SizeRule kBwdRules32[] = {
+    {129, 159, 80, 300, {1, 3, 2, 4}},           // D = 516 ... 636: 0.875, 1.07 (238)
+    {160, 191, 80, 300, {1, 3, 2, 4}, 0, 4}};    // D = 640 ... 764: 0.937, 1.03 (155); on more segments up to 1.27, and at 75 MB 1.06
 // Without saved statistics.  Up to 20 MB a block has one to four steps: one chunk per lane and one block per CU halve the
 // slots and shorten the chain of the first row.
 constexpr SizeRule kRcBwdRules[] = {

@@ -29,7 +29,7 @@ def rows_of(mb, D, dtype):
     (B, 1000, 0, 21, (1, 2, 2, 4)), (B, 1000, 0, 149, (1, 2, 2, 6)), (B, 1000, 0, 151, (1, 2, 2, 4)), (B, 1024, 0, 160, (1, 2, 2, 3)),
     (B, 2264, 0, 21, (5, 1, 2, 2)), (B, 2264, 0, 19, (5, 1, 2, 1)), (B, 1400, 0, 80, (3, 1, 2, 3)), (B, 1536, 0, 80, (3, 1, 1, 3)),
     (B, 3584, 0, 290, (8, 1, 2, 1)), (B, 3584, 0, 310, (4, 2, 1, 3)), (B, 3400, 0, 900, (8, 1, 2, 1)), (B, 6144, 0, 80, (8, 2, 1, 1)),
-    (B, 640, 1, 80, (1, 3, 2, 4)), (B, 640, 1, 70, (1, 3, 2, 3)),
+    (B, 640, 1, 81, (1, 3, 2, 4)), (B, 640, 1, 79, (1, 4, 1, 3)), (B, 640, 1, 70, (1, 3, 2, 3)),
     # backward without saved statistics
     (RC, 1536, 0, 19, (3, 1, 2, 2)), (RC, 1536, 0, 21, (1, 3, 2, 4)), (RC, 2048, 0, 19, (4, 1, 2, 1)), (RC, 2048, 0, 149, (4, 1, 2, 2)),
     (RC, 2048, 0, 151, (2, 2, 1, 4)), (RC, 1544, 0, 71, (4, 1, 2, 2)), (RC, 1544, 0, 73, (2, 2, 1, 6)), (RC, 2560, 0, 19, (5, 1, 1, 1)),
@@ -56,6 +56,9 @@ def test_entry_on_both_sides_of_a_size(family, D, dtype, mb, shape):
 @pytest.mark.parametrize("family,D,dtype,mb,segments,shapes", [
     (F, 6144, 1, 40, (5, 6), ((6, 4, 1), (6, 4, 2))),
     (F, 6144, 1, 71, (1, 8), ((6, 4, 1), (6, 4, 2))),
+    (B, 640, 1, 100, (4, 5), ((1, 3, 2), (1, 4, 1))),
+    (B, 636, 1, 100, (4, 5), ((1, 3, 2), (1, 3, 2))),
+    (B, 712, 1, 153, (1, 28), ((1, 3, 2), (1, 4, 1))),
 ])
 def test_entry_on_both_sides_of_a_segment_count(family, D, dtype, mb, segments, shapes):
     for n, shape in zip(segments, shapes):
