@@ -20,7 +20,7 @@ int blocks_per_cu(int K) {
 // Against the rule with overrides per 512 features that stood here: bf16 0.96 of the time in the mean over 32
 // widths, short launches 0.94, fp32 0.95 (D = 768 167 -> 136 us, 1280 150 -> 136, 5888 145 -> 138; 32 MB: D =
 // 768 31.5 -> 25.5, 4352 28.6 -> 25.3; fp32 D = 1280 113 -> 102, with one row per step as in bf16).
-Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
+Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T, int64_t nseg) {
     if (ln && dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 1, 16},
@@ -45,13 +45,15 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T = 0) {
         // size classes and widths between two multiples of 256 (see SizeRule): 480 random problems of 4 to 300 MB, every
         // compiled shape, the shares of the entry's time (mean, worst)
         static const SizeRule rules[] = {
-            {65, 95, 0, 20, {1, 2, 2, 12}},          // D = 520 ... 760: 0.93, 0.98
-            {65, 95, 20, 150, {1, 2, 2, 8}},         // the same: 0.94, 0.99
-            {97, 127, 72, 300, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.965, 0.985
-            {225, 255, 72, 150, {2, 2, 1, 4}},       // D = 1800 ... 2040: 0.95, 0.965
-            {289, 320, 0, 20, {4, 2, 1, 3}},         // D = 2312 ... 2560: 0.955, 0.995
-            {448, 448, 20, 72, {4, 2, 1, 3}}};       // D = 3584: 0.97, 0.995
-        if (const Shape* sh = size_rule(rules, nchunks, T)) return *sh;
+            {65, 95, 4, 20, {1, 2, 2, 12}},          // D = 520 ... 760: 0.918, 1.04 (237); below 1.035, up to 1.30
+            {65, 95, 20, 72, {1, 2, 2, 8}},          // the same: 0.953, 1.03 (267)
+            {65, 95, 72, 150, {1, 2, 2, 8}, 5},      // the same: 0.964, 1.03 (129); on one to four samples 1.00, up to 1.06
+            {97, 127, 72, 200, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.96, 1.02 (282)
+            {97, 127, 200, 300, {1, 2, 2, 4}, 5},    // the same: 0.952, 1.01 (111); on one to four samples up to 1.05
+            {225, 255, 72, 150, {2, 2, 1, 4}},       // D = 1800 ... 2040: 0.943, 1.01 (327)
+            {289, 320, 2, 20, {4, 2, 1, 3}},         // D = 2312 ... 2560: 0.958, 1.04 (267)
+            {448, 448, 20, 72, {4, 2, 1, 3}, 0, 8}};     // D = 3584: 0.962, 1.03 (310); on more segments 1.01, up to 1.04
+        if (const Shape* sh = size_rule(rules, nchunks, T, nseg)) return *sh;
         // D = 4360 ... 6656: two tensors are read, and at 71 MB the short entries lost 3 to 8 % (5048 52.5 -> 56.4 us);
         // elsewhere they win up to 72 MB at most widths (2568 56.2 against 60.3 us, 7096 44.9 against 47.2)
         if (short_launch(T, nchunks) && (nchunks <= 544 || nchunks > 832 || T * nchunks * 16 <= 48000000))
@@ -177,7 +179,7 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.eps = p.eps;
     a.inv_D = 1.0f / static_cast<float>(p.D);
-    const Shape sh = gated_fwd_shape(a.nchunks, p.dtype, LN, p.T);
+    const Shape sh = gated_fwd_shape(a.nchunks, p.dtype, LN, p.T, p.nseg);
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     // bytes of x, u, h and y at 6 TB/s
     const double stream_us = static_cast<double>(p.T) * static_cast<double>(p.D) * (p.dtype == 0 ? 8.0 : 16.0) / 6.0e6;
@@ -196,7 +198,7 @@ hipError_t launch(const Problem& p, const void* x, const void* u, const void* ga
 
 }  // namespace
 
-Shape gated_fwd_table_shape(int nchunks, int dtype, int64_t T) { return gated_fwd_shape(nchunks, dtype, true, T); }
+Shape gated_fwd_table_shape(int nchunks, int dtype, int64_t T) { return gated_fwd_shape(nchunks, dtype, true, T, 0); }
 
 hipError_t launch_gated_fwd(const Problem& p, const void* x, const void* u, const void* gate,
                             const void* shift, const void* scale, void* h, void* y, float* mean,

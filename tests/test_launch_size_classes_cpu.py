@@ -38,7 +38,7 @@ def rows_of(mb, D, dtype):
     (RC, 6136, 0, 19, (4, 3, 1, 1)), (RC, 6144, 0, 19, (4, 3, 2, 1)), (RC, 640, 0, 35, (1, 2, 2, 4)), (RC, 640, 0, 37, (1, 2, 2, 8)),
     (RC, 1000, 0, 290, (1, 2, 1, 8)), (RC, 1000, 0, 310, (1, 2, 2, 4)), (RC, 4088, 0, 290, (4, 2, 1, 2)), (RC, 4088, 0, 310, (4, 2, 2, 1)),
     # gated
-    (GF, 760, 0, 19, (1, 2, 2, 12)), (GF, 520, 0, 149, (1, 2, 2, 8)), (GF, 768, 0, 100, (1, 2, 1, 6)), (GF, 1016, 0, 290, (1, 2, 2, 4)),
+    (GF, 760, 0, 19, (1, 2, 2, 12)), (GF, 696, 0, 3, (1, 2, 1, 6)), (GF, 520, 0, 71, (1, 2, 2, 8)), (GF, 520, 0, 149, (1, 2, 1, 6)), (GF, 768, 0, 100, (1, 2, 1, 6)), (GF, 1016, 0, 199, (1, 2, 2, 4)), (GF, 1016, 0, 290, (2, 2, 1, 4)), (GF, 2560, 0, 1, (3, 2, 1, 2)),
     (GF, 1800, 0, 140, (2, 2, 1, 4)), (GF, 2560, 0, 19, (4, 2, 1, 3)), (GF, 2560, 0, 21, (3, 2, 1, 2)), (GF, 3584, 0, 71, (4, 2, 1, 3)),
     (GB, 1016, 0, 50, (2, 1, 2, 2)), (GB, 1024, 0, 50, (2, 1, 1, 2)), (GB, 2040, 0, 50, (4, 1, 2, 1)), (GB, 2568, 0, 50, (6, 1, 2, 1)),
     # query / key normalisation
