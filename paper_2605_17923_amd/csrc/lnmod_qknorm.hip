@@ -38,10 +38,10 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
         // size classes (see SizeRule): 510 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
         static const SizeRule rules[] = {
-            {129, 159, 0, 20, {1, 3, 2, 16}},        // D = 1032 ... 1272: 0.945, 0.985
-            {320, 320, 0, 20, {3, 2, 2, 8}},         // D = 2560: 0.945, 1.01
-            {384, 384, 0, 20, {3, 2, 2, 6}},         // D = 3072: 0.96, 1.0
-            {512, 512, 20, 72, {4, 2, 2, 3}}};       // D = 4096: 0.965, 0.995
+            {129, 159, 4, 20, {1, 3, 2, 16}},        // D = 1032 ... 1272: 0.958, 1.04 (149); below 1.00, up to 1.06
+            {320, 320, 4, 20, {3, 2, 2, 8}},         // D = 2560: 0.971, 1.02 (147); below 1.00, up to 1.05
+            {384, 384, 4, 20, {3, 2, 2, 6}},         // D = 3072: 0.964, 1.03 (150); below 1.00, up to 1.07
+            {512, 512, 20, 72, {4, 2, 2, 3}}};       // D = 4096: 0.969, 1.01 (215)
         if (const Shape* sh = size_rule(rules, nchunks, N)) return *sh;
         // two tensors are read: beyond D = 3840 the short entries lost 3 to 8 % at 62 MB (D = 5128 44.4 -> 48.1 us),
         // below it they still win there at most widths (1808 53.1 -> 47.0, 3136 48.7 -> 43.5)
@@ -61,13 +61,14 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
         // the table was timed at 150 MB; 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
         static const SizeRule rules32[] = {
-            {257, 320, 0, 72, {1, 6, 2, 6}},         // D = 1028 ... 1280: 0.92, 0.98
-            {385, 512, 0, 20, {2, 4, 2, 4}},         // D = 1540 ... 2048: 0.90, 0.98
-            {385, 512, 20, 72, {2, 4, 2, 6}},
-            {513, 576, 0, 72, {3, 4, 2, 3}},         // D = 2052 ... 2304: 0.935, 0.98
-            {768, 768, 0, 72, {3, 4, 2, 3}},         // D = 3072: 0.88, 0.95
-            {1536, 1536, 20, 72, {8, 4, 2, 2}},      // D = 6144: 0.92, 0.97
-            {833, 896, 0, 300, {4, 4, 2, 2}}};       // D = 3332 ... 3584: 0.90, 0.95
+            {257, 320, 0, 72, {1, 6, 2, 6}},         // D = 1028 ... 1280: 0.954, 1.02 (215)
+            {385, 512, 4, 20, {2, 4, 2, 4}},         // D = 1540 ... 2048: 0.906, 1.02 (139)
+            {385, 512, 20, 36, {2, 4, 2, 6}},        // the same: 0.953, 1.02 (118); beyond 1.00, up to 1.06
+            {513, 576, 4, 7, {3, 4, 2, 3}},          // D = 2052 ... 2304: 0.921, 1.02 (46)
+            {513, 576, 10, 72, {3, 4, 2, 3}},        // the same: 0.942, 1.02 (98); between them up to 1.06
+            {768, 768, 4, 72, {3, 4, 2, 3}},         // D = 3072: 0.889, 1.05 (145)
+            {1536, 1536, 20, 36, {8, 4, 2, 2}},      // D = 6144: 0.912, 1.02 (147); beyond 1.00, up to 1.04
+            {833, 896, 10, 150, {4, 4, 2, 2}}};      // D = 3332 ... 3584: 0.913, 1.02 (150); beyond 1.00, up to 1.07
         if (const Shape* sh = size_rule(rules32, nchunks, N)) return *sh;
         return fine_entry(tab32, nchunks, dtype);
     }
@@ -82,7 +83,7 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1}, {6, 2, 2, 1},   // D <= 6144
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
-        static const SizeRule rules[] = {{417, 448, 0, 20, {4, 2, 2, 1}}};       // D = 3336 ... 3584: 0.92, 0.98
+        static const SizeRule rules[] = {{417, 448, 0, 20, {4, 2, 2, 1}}};       // D = 3336 ... 3584: 0.935, 1.04 (164)
         if (const Shape* sh = size_rule(rules, nchunks, N)) return *sh;
         // D = 1800 ... 1984: the entry was timed at 2048 (1920, 62, 95 and 173 MB: 67.7, 99.1, 176 us against 70.1, 103, 186)
         if (nchunks > 224 && nchunks <= 248) return {2, 2, 2, 3};
@@ -100,9 +101,11 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
         {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
         {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
-    // D = 1284 ... 1536 and 3332 ... 3584 as timed on 4 to 300 MB; up to 20 MB 2008 rows of 1536 take 20.1 us with two blocks
-    // per CU and 21.2 with three
-    static const SizeRule rules32[] = {{321, 384, 0, 20, {2, 4, 2, 2}}, {833, 896, 0, 20, {4, 4, 2, 1}}};
+    // D = 1284 ... 1536: three blocks per CU of two waves take 0.94 of the time of one wave with six chunks (90 problems of 2.5
+    // to 21 MB; 1.07 at 2032 rows of 1536); two blocks per CU are 0.89 of three at 769 ... 1024 rows but 1.17 at 521 ... 703,
+    // and a size at which the slots fell as the rows grow would break a workspace sized for more rows.
+    // D = 3332 ... 3584: 0.968, 1.01 (218) beyond 20 MB, below the same
+    static const SizeRule rules32[] = {{833, 896, 0, 20, {4, 4, 2, 1}}};
     if (const Shape* sh = size_rule(rules32, nchunks, N)) return *sh;
     return fine_entry(tab32, nchunks, dtype);
 }

@@ -44,8 +44,9 @@ def rows_of(mb, D, dtype):
     # query / key normalisation
     (QF, 1152, 0, 19, (1, 3, 2, 16)), (QF, 1152, 0, 21, (2, 2, 2, 8)), (QF, 2560, 0, 19, (3, 2, 2, 8)), (QF, 3072, 0, 19, (3, 2, 2, 6)),
     (QF, 4096, 0, 71, (4, 2, 2, 3)), (QF, 4096, 0, 73, (4, 3, 2, 1)), (QF, 1152, 1, 71, (1, 6, 2, 6)), (QF, 2048, 1, 19, (2, 4, 2, 4)),
-    (QF, 2048, 1, 21, (2, 4, 2, 6)), (QF, 3072, 1, 71, (3, 4, 2, 3)), (QF, 3072, 1, 73, (3, 4, 2, 1)), (QF, 3584, 1, 290, (4, 4, 2, 2)),
-    (QF, 6144, 1, 40, (8, 4, 2, 2)), (QB, 3584, 0, 19, (4, 2, 2, 1)), (QB, 3584, 0, 21, (4, 2, 2, 2)), (QB, 1536, 1, 50, (2, 4, 2, 3)), (QB, 1536, 1, 19, (2, 4, 2, 2)),
+    (QF, 2048, 1, 21, (2, 4, 2, 6)), (QF, 3072, 1, 71, (3, 4, 2, 3)), (QF, 3072, 1, 73, (3, 4, 2, 1)), (QF, 3584, 1, 149, (4, 4, 2, 2)), (QF, 3584, 1, 290, (4, 4, 2, 1)), (QF, 3584, 1, 9, (4, 4, 2, 1)),
+    (QF, 6144, 1, 35, (8, 4, 2, 2)), (QF, 6144, 1, 40, (6, 4, 2, 1)), (QF, 1152, 0, 3, (2, 2, 2, 8)), (QF, 2200, 1, 6, (3, 4, 2, 3)), (QF, 2200, 1, 8, (3, 4, 2, 2)),
+    (QF, 2048, 1, 37, (2, 4, 2, 2)), (QB, 3584, 0, 19, (4, 2, 2, 1)), (QB, 3584, 0, 21, (4, 2, 2, 2)), (QB, 1536, 1, 50, (2, 4, 2, 3)), (QB, 1536, 1, 19, (2, 4, 2, 3)), (QB, 1536, 1, 4, (2, 4, 2, 3)),
     (QB, 3584, 1, 21, (4, 4, 2, 2)), (QB, 3584, 1, 19, (4, 4, 2, 1)),
 ])
 def test_entry_on_both_sides_of_a_size(family, D, dtype, mb, shape):
