@@ -163,10 +163,11 @@ struct FwdLaunch {
 //   D <  1536  the entry with one row: 0.74 ... 1.04 (tab: up to 1.22)
 //   D = 1536   the entry with one row: 0.85 ... 1.02; tab on large launches (the entry there: up to 1.07)
 Shape many_short_shape(const Problem& p, int nchunks, Shape tab) {
-    if (launch_mb(p.T, nchunks, 20, 72) && nchunks > 160) return tab;      // fwd_shape's rule holds here too
+    // fwd_shape's size rules hold here too: D = 1288 ... 1536 0.898, 1.01 (84)
+    if (nchunks > 128 && launch_mb(p.T, nchunks, 20, nchunks > 160 ? 72 : 36)) return tab;
     Shape sh = fwd_short_entry(nchunks);
     if (nchunks <= 96) return one_step(sh, p.T);
-    if (nchunks == 192 && launch_mb(p.T, nchunks, 0, 20)) return one_step(sh, p.T);   // two rows: 0.97, 1.01
+    if (nchunks == 192 && launch_mb(p.T, nchunks, 10, 20)) return sh;      // two rows: 0.927, 1.02 (128); up to 10 MB 1.04, up to 1.14
     sh.R = 1;
     if (nchunks <= 128) return large_launch(p, nchunks) && p.T > 384 * p.nseg ? tab : sh;
     if (nchunks <= 160) return p.T > 192 * p.nseg ? tab : sh;
@@ -184,12 +185,7 @@ FwdLaunch plan_fwd(const Problem& p, int mode) {
         // D = 1536, flat: four blocks per CU at every token count (24 mixed segments, 152 880 rows:
         // 159 us against 182 with three)
         if (mode == kModFlat && L.nchunks == 192 && p.dtype == 0 && !short_launch(p.T, L.nchunks)) tab.per_cu = 4;
-        // D = 5120, flat: two blocks of one row, 0.965 of the time (worst 1.0) from 150 to 300 MB
-        if (mode == kModFlat && L.nchunks == 640 && p.dtype == 0 && launch_mb(p.T, L.nchunks, 72, 300)) tab = {5, 2, 1, 2};
-        // D = 1032 ... 1280, flat, 20 to 36 MB: 0.91, worst 0.97 (beyond 0.99, up to 1.045; one sample up to 1.06)
-        const bool middle5 = mode == kModFlat && p.dtype == 0 && L.nchunks > 128 && L.nchunks <= 160 && launch_mb(p.T, L.nchunks, 20, 36);
-        if (middle5) tab = {1, 3, 2, 12};
-        if (mode == kModFlat && L.nchunks <= 192 && p.dtype == 0 && many_short(p) && !middle5) tab = many_short_shape(p, L.nchunks, tab);
+        if (mode == kModFlat && L.nchunks <= 192 && p.dtype == 0 && many_short(p)) tab = many_short_shape(p, L.nchunks, tab);
         // short launches at D = 5184 ... 5376, aligned: on fewer than eight segments the entry (see fwd_short_entry), from
         // eight on six blocks per CU (20 segments, 30 MB: 16.4 us against 19.2; 3 segments, 64 MB 29.1 against 26.8)
         if (mode == kModFlat && p.dtype == 0 && p.nseg >= 8 && L.nchunks > 640 && L.nchunks <= 672 &&

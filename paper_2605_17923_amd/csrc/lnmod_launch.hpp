@@ -345,21 +345,25 @@ inline Shape fwd_shape(int nchunks, int dtype, int64_t T = 0, int64_t nseg = 0) 
             {8, 2, 1, 2}, {8, 2, 2, 2}, {5, 3, 1, 1}, {5, 3, 1, 1},   // D <= 7168
             {8, 2, 1, 2}, {5, 3, 1, 1}, {6, 3, 1, 1}, {6, 3, 1, 1}};   // D <= 8192
         static const SizeRule rules[] = {
-            {161, 192, 20, 72, {1, 3, 2, 12}},       // D = 1288 ... 1536: 0.935, 0.99
-            {353, 384, 20, 72, {2, 3, 2, 6}},        // D = 2824 ... 3072: 0.93, 1.03
-            {512, 512, 24, 72, {4, 2, 1, 3}},        // D = 4096: 0.975, 1.005
-            {353, 384, 12, 20, {2, 3, 1, 6}},        // D = 2824 ... 3072: 0.90, 0.97
-            {448, 448, 12, 72, {4, 2, 1, 4}},        // D = 3584: 0.965, 1.01
-            {737, 767, 0, 72, {4, 3, 2, 3}},         // D = 5896 ... 6136: 0.94, 0.99
-            {97, 112, 72, 150, {1, 2, 1, 12}},       // D = 776 ... 896: 0.935, 1.0
-            {193, 223, 72, 150, {2, 2, 2, 4}},       // D = 1544 ... 1784: 0.97, 0.995
-            {545, 575, 72, 150, {4, 3, 2, 2}},       // D = 4360 ... 4600: 0.96, 1.03
-            {512, 512, 72, 150, {4, 2, 1, 3}},       // D = 4096: 0.94, 0.98
-            {640, 640, 72, 150, {5, 2, 1, 2}},       // D = 5120: 0.93, 0.96
-            {353, 384, 72, 300, {2, 3, 1, 4}},       // D = 2824 ... 3072: 0.955, 0.995
-            {481, 511, 72, 300, {4, 2, 1, 3}},       // D = 3848 ... 4088: 0.80, 0.80
-            // D = 4872 ... 5112: 0.71, 0.77; 400 MB 0.70, 800 MB 0.72 (4976: 386 -> 271 us)
-            {609, 639, 72, kAnyMB, {4, 3, 1, 2}}};
+            {129, 160, 20, 36, {1, 3, 2, 12}, 2},    // D = 1032 ... 1280: 0.937, 1.01 (216); one sample up to 1.06, beyond 36 MB up to 1.045
+            {161, 192, 20, 72, {1, 3, 2, 12}},       // D = 1288 ... 1536: 0.952, 1.01 (298)
+            {353, 384, 20, 72, {2, 3, 2, 6}},        // D = 2824 ... 3072: 0.917, 1.03 (327)
+            {512, 512, 24, 72, {4, 2, 1, 3}, 0, 4},  // D = 4096: 0.968, 1.04 (293); on more segments 1.00, up to 1.07
+            {353, 384, 12, 20, {2, 3, 1, 6}},        // D = 2824 ... 3072: 0.898, 1.01 (324)
+            {448, 448, 12, 50, {4, 2, 1, 4}},        // D = 3584: 0.964, 1.02 (290)
+            {737, 767, 16, 24, {4, 3, 2, 3}},        // D = 5896 ... 6136: 0.925, 1.02 (111); one sample elsewhere up to 72 MB 1.01, up to 1.18
+            {737, 767, 12, 30, {4, 3, 2, 3}, 2},     // the same: 0.94, 1.02 (89)
+            {97, 108, 72, 150, {1, 2, 1, 12}},       // D = 776 ... 864: 0.889, 1.01 (229)
+            {112, 112, 72, 150, {1, 2, 1, 12}},      // D = 896: 0.87, 0.92 (25); between them up to 1.05
+            // D = 1544 ... 1784, unaligned: 0.967, 1.02 (312); aligned up to 1.06
+            {193, 223, 72, 150, {2, 2, 2, 4}, 0, kAnySegs, 0, true},
+            {545, 575, 72, 150, {4, 3, 2, 2}, 13},   // D = 4360 ... 4600: 0.923, 0.99 (110); on fewer segments 1.01, up to 1.06
+            {512, 512, 72, 150, {4, 2, 1, 3}},       // D = 4096: 0.935, 1.00 (325)
+            {640, 640, 72, 150, {5, 2, 1, 2}},       // D = 5120: 0.959, 1.01 (327)
+            {640, 640, 150, 200, {5, 2, 1, 2}, 2},   // the same: 0.962, 1.01 (131); beyond 0.99, up to 1.03
+            {384, 384, 72, 300, {2, 3, 1, 4}},       // D = 3072: 0.96, 1.00 (285); 2824 ... 3064 1.00, up to 1.11
+            {481, 511, 72, 300, {4, 2, 1, 3}},       // D = 3848 ... 4088: 0.871, 1.01 (327)
+            {609, 639, 72, kAnyMB, {4, 3, 1, 2}}};   // D = 4872 ... 5112: 0.709, 0.82 (327)
         if (const Shape* sh = size_rule(rules, nchunks, T, nseg)) return one_step(*sh, T);
         const int col = (nchunks + 31) / 32;
         if (short_launch(T, nchunks)) return one_step(fwd_short_entry(nchunks), T);
