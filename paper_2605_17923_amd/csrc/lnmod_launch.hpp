@@ -415,19 +415,21 @@ constexpr int64_t kNarrowBwdBytes = 40000000;        // the line of the backward
 
 // Size rules of the backwards.  Their shapes all count in bwd_most_slots_one_sample.
 constexpr SizeRule kBwdRules[] = {
-    {131, 159, 0, 20, {3, 1, 2, 2}},             // D = 1048 ... 1272: 0.90, 1.01
-    {609, 640, 0, 20, {8, 2, 1, 1}},             // D = 4872 ... 5120: 0.96, 0.99
-    {97, 127, 20, 72, {1, 2, 2, 4}},             // D = 776 ... 1016: 0.94, 1.04
-    {257, 287, 20, 72, {5, 1, 2, 2}},            // D = 2056 ... 2296: 0.95, 0.99
-    {97, 127, 72, 150, {1, 2, 2, 6}},            // D = 776 ... 1016: 0.85, 1.0
-    // D = 3584: 0.93, 1.0; on segments of fewer than 512 rows in the mean up to 1.09
+    {131, 159, 0, 1, {3, 1, 2, 2}, 0, 1},        // D = 1048 ... 1272: 0.944, 1.01 (116)
+    {131, 159, 1, 20, {3, 1, 2, 2}},             // the same: 0.869, 1.06 (292)
+    {609, 640, 6, 20, {8, 2, 1, 1}},             // D = 4872 ... 5120: 0.978, 1.06 (229); below 1.01, up to 1.21
+    {97, 127, 24, 72, {1, 2, 2, 4}},             // D = 776 ... 1016: 0.938, 1.04 (302)
+    {257, 287, 40, 72, {5, 1, 2, 2}},            // D = 2056 ... 2296: 0.935, 1.08 (233); below 0.99, up to 1.09
+    {97, 127, 72, 150, {1, 2, 2, 6}},            // D = 776 ... 1016: 0.875, 1.03 (327)
+    // D = 3584: 0.932, 1.02 (325); on segments of fewer than 512 rows in the mean up to 1.09
     {448, 448, 72, 300, {8, 1, 2, 1}, 0, kAnySegs, 512},
-    {640, 640, 72, 300, {5, 2, 2, 1}},           // D = 5120: 0.98, 1.0
-    {97, 127, 150, kAnyMB, {1, 2, 2, 4}},        // D = 776 ... 1016: 0.87, 0.92; 800 MB 0.80
-    {161, 191, 72, kAnyMB, {3, 1, 2, 3}},        // D = 1288 ... 1528: 0.95, 1.05; 800 MB 0.91
-    {417, 447, 72, kAnyMB, {8, 1, 2, 1}, 0, kAnySegs, 512},     // D = 3336 ... 3576: 0.96, 1.0; 800 MB 0.95
-    {609, 639, 72, kAnyMB, {6, 2, 2, 1}},        // D = 4872 ... 5112: 0.965, 0.99; 800 MB 0.94
-    {768, 768, 72, kAnyMB, {8, 2, 1, 1}}};       // D = 6144: 0.975, 0.99; 800 MB 0.98
+    {640, 640, 72, 300, {5, 2, 2, 1}},           // D = 5120: 0.981, 1.01 (326)
+    {97, 127, 150, kAnyMB, {1, 2, 2, 4}, 0, 80},     // D = 776 ... 1016: 0.843, 1.08 (257); on more segments 0.92, up to 1.10
+    // D = 1288 ... 1528, unaligned: 0.93, 1.04 (209); aligned 1.03, up to 1.08, more segments 0.98, up to 1.10
+    {161, 191, 72, kAnyMB, {3, 1, 2, 3}, 0, 4, 0, true},
+    {417, 447, 72, 500, {8, 1, 2, 1}, 0, kAnySegs, 700},     // D = 3336 ... 3576: 0.941, 1.03 (281); beyond 0.97, up to 1.05
+    {609, 639, 72, kAnyMB, {6, 2, 2, 1}},        // D = 4872 ... 5112: 0.954, 1.00 (327)
+    {768, 768, 72, kAnyMB, {8, 2, 1, 1}}};       // D = 6144: 0.976, 1.02 (327)
 constexpr SizeRule kBwdRules32[] = {
     {129, 159, 80, 300, {1, 3, 2, 4}},           // D = 516 ... 636: 0.875, 1.07 (238)
     {160, 191, 80, 300, {1, 3, 2, 4}, 0, 4}};    // D = 640 ... 764: 0.937, 1.03 (155); on more segments up to 1.27, and at 75 MB 1.06
