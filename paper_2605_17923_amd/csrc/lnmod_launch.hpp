@@ -436,19 +436,30 @@ constexpr SizeRule kBwdRules32[] = {
 // Without saved statistics.  Up to 20 MB a block has one to four steps: one chunk per lane and one block per CU halve the
 // slots and shorten the chain of the first row.
 constexpr SizeRule kRcBwdRules[] = {
-    {161, 192, 0, 20, {3, 1, 2, 2}},             // D = 1288 ... 1536: 0.87, 1.0
-    {256, 256, 0, 20, {4, 1, 2, 1}},             // D = 2048: 0.75, 0.80
-    {193, 255, 0, 20, {4, 1, 2, 2}},             // D = 1544 ... 2040: 0.82, 0.87
-    {320, 320, 0, 20, {5, 1, 1, 1}},             // D = 2560: 0.83, 0.95
-    {257, 319, 0, 20, {5, 1, 1, 2}},             // D = 2056 ... 2552: 0.90, 0.97
-    {321, 384, 0, 20, {6, 1, 2, 1}},             // D = 2568 ... 3072: 0.89, 1.07
-    {417, 448, 0, 20, {8, 1, 2, 1}},             // D = 3336 ... 3584: 0.82, 0.97
-    {513, 767, 0, 20, {4, 3, 1, 1}},             // D = 4104 ... 6136: 0.90, 0.97
-    {65, 96, 36, 72, {1, 2, 2, 8}},              // D = 520 ... 768: 0.95, 1.02 (27 MB 1.07)
-    {193, 256, 20, 72, {4, 1, 2, 2}},            // D = 1544 ... 2048: 0.905, 0.97
-    {256, 256, 72, 150, {4, 1, 2, 2}},           // D = 2048: 0.95, 0.97
-    {97, 127, 72, 300, {1, 2, 1, 8}},            // D = 776 ... 1016: 0.935, 0.965
-    {481, 511, 72, 300, {4, 2, 1, 2}}};          // D = 3848 ... 4088: 0.93, 0.95
+    {161, 192, 0, 20, {3, 1, 2, 2}},             // D = 1288 ... 1536: 0.895, 1.04 (325)
+    {256, 256, 0, 1, {4, 1, 2, 1}, 0, 1},        // D = 2048: 0.98, 1.02 (94); several samples 1.03, up to 1.12
+    {256, 256, 1, 20, {4, 1, 2, 1}},             // the same: 0.789, 1.06 (293)
+    {193, 255, 0, 1, {4, 1, 2, 2}, 0, 1},        // D = 1544 ... 2040: 0.957, 1.01 (123); several samples 1.00, up to 1.11
+    {193, 255, 1, 20, {4, 1, 2, 2}},             // the same: 0.819, 1.02 (294)
+    {320, 320, 0, 1, {5, 1, 1, 1}},              // D = 2560: 0.894, 1.01 (137)
+    {320, 320, 2, 20, {5, 1, 1, 1}},             // the same: 0.889, 1.07 (271); between them 0.98, up to 1.07
+    {257, 319, 0, 1, {5, 1, 1, 2}},              // D = 2056 ... 2552: 0.923, 1.03 (158)
+    {257, 319, 5, 20, {5, 1, 1, 2}},             // the same: 0.911, 1.02 (237); between them 1.04, up to 1.20
+    {321, 383, 0, 12, {6, 1, 2, 1}},             // D = 2568 ... 3064: 0.934, 1.04 (216); beyond 1.02, up to 1.12
+    {384, 384, 0, 2, {6, 1, 2, 1}},              // D = 3072: 0.963, 1.06 (178)
+    {384, 384, 4, 12, {6, 1, 2, 1}},             // the same: 0.886, 1.05 (153)
+    {384, 384, 12, 16, {6, 1, 2, 1}, 0, 4},      // the same: 0.957, 1.02 (36); elsewhere 1.00, up to 1.22
+    {417, 448, 2, 14, {8, 1, 2, 1}},             // D = 3336 ... 3584: 0.807, 0.99 (249); below 1.01, up to 1.24
+    {417, 448, 14, 20, {8, 1, 2, 1}, 0, 8},      // the same: 0.923, 1.03 (177); on more segments up to 1.12
+    {513, 704, 2, 20, {4, 3, 1, 1}, 0, 4},       // D = 4104 ... 5632: 0.899, 1.05 (236); on more segments 0.98, up to 1.10
+    {705, 767, 8, 20, {4, 3, 1, 1}},             // D = 5640 ... 6136: 0.95, 1.01 (170); below up to 1.21
+    {65, 96, 36, 50, {1, 2, 2, 8}, 2},           // D = 520 ... 768: 0.935, 1.04 (161); one sample 1.01, up to 1.08
+    {65, 96, 50, 72, {1, 2, 2, 8}},              // the same: 0.93, 1.02 (245)
+    {193, 255, 20, 50, {4, 1, 2, 2}},            // D = 1544 ... 2040: 0.946, 1.06 (216); beyond 1.02, up to 1.08
+    {256, 256, 20, 72, {4, 1, 2, 2}},            // D = 2048: 0.882, 1.03 (259)
+    {256, 256, 72, 150, {4, 1, 2, 2}, 0, 64},    // the same: 0.957, 1.00 (322); on more segments 1.01, up to 1.05
+    {97, 127, 80, 300, {1, 2, 1, 8}},            // D = 776 ... 1016: 0.948, 1.06 (312)
+    {481, 511, 80, 300, {4, 2, 1, 2}}};          // D = 3848 ... 4088: 0.925, 1.03 (312)
 
 // The tables, without the size rules.
 inline Shape bwd_table(int nchunks, int dtype, int64_t T) {
