@@ -16,7 +16,7 @@ namespace {
 // every compiled shape on 32 and 200 MB tensors (fp32: 150 MB); against the rule with overrides per 512
 // features that stood here they take 0.97 of the time in the mean over 32 widths (200 MB bf16: D = 256 341 ->
 // 221 us, 768 267 -> 211, 1280 233 -> 207, 1792 244 -> 222; fp32 D = 1280 186 -> 154, 2304 178 -> 160).
-Shape gated_bwd_shape(int nchunks, int dtype) {
+Shape gated_bwd_shape(int nchunks, int dtype, int64_t T) {
     if (dtype == 0) {
         static const Shape tab[33] = {
             {1, 1, 2, 8},
@@ -28,11 +28,12 @@ Shape gated_bwd_shape(int nchunks, int dtype) {
             {6, 2, 1, 1}, {6, 2, 1, 1}, {6, 2, 1, 1}, {12, 1, 1, 1},   // D <= 6144
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 7168
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {16, 1, 1, 1}};   // D <= 8192
-        // widths below a multiple of 256, 4 to 300 MB, shares of the entry's time (mean, worst)
+        // widths below a multiple of 256, timed on 0.3 to 800 MB, shares of the entry's time (mean, worst, problems)
         const int col = (nchunks + 31) / 32;
-        if (col == 4 && nchunks < 128) return {2, 1, 2, 2};     // D = 776 ... 1016: 0.95, 0.98 (below 20 MB 0.97, 1.03)
-        if (col == 8 && nchunks < 256) return {4, 1, 2, 1};     // D = 1800 ... 2040: 0.95, 1.02
-        if (col == 11 && nchunks < 352) return {6, 1, 2, 1};    // D = 2568 ... 2808: 0.955, 1.0
+        if (col == 4 && nchunks < 128) return {2, 1, 2, 2};     // D = 776 ... 1016: 0.952, 1.05 (327)
+        if (col == 8 && nchunks < 256) return {4, 1, 2, 1};     // D = 1800 ... 2040: 0.953, 1.09 (327)
+        // D = 2568 ... 2808: 0.964, 1.02 (252); up to 20 MB 0.99, up to 1.11
+        if (col == 11 && nchunks < 352 && (T == 0 || launch_mb(T, nchunks, 20, kAnyMB))) return {6, 1, 2, 1};
         return fine_entry(tab, nchunks, dtype);
     }
     static const Shape tab32[33] = {
@@ -95,13 +96,13 @@ bool dispatch(const GatedBwdArgs& a, Shape sh, int64_t blocks, hipStream_t st) {
 
 }  // namespace
 
-Shape gated_bwd_table_shape(int nchunks, int dtype) {
-    return gated_bwd_shape(nchunks, dtype);
+Shape gated_bwd_table_shape(int nchunks, int dtype, int64_t T) {
+    return gated_bwd_shape(nchunks, dtype, T);
 }
 
 RowPlan gated_bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype) {
     const int E = dtype == 0 ? 8 : 4;
-    const Shape sh = gated_bwd_shape(static_cast<int>(D / E), dtype);
+    const Shape sh = gated_bwd_shape(static_cast<int>(D / E), dtype, T);
     // a row moves 6 D elements (dy, dh, h, u, dx, du), a slot 3 D floats written and read back
     const double elem = dtype == 0 ? 2.0 : 4.0;
     const double stream_us = static_cast<double>(T) * static_cast<double>(D) * 6.0 * elem / 5.8e6;
@@ -131,7 +132,7 @@ hipError_t launch_gated_bwd(const Problem& p, const void* dy, const void* dh, co
     a.D = static_cast<int32_t>(p.D);
     a.nchunks = static_cast<int32_t>(p.D / E);
     a.inv_D = 1.0f / static_cast<float>(p.D);
-    const Shape sh = gated_bwd_shape(a.nchunks, p.dtype);
+    const Shape sh = gated_bwd_shape(a.nchunks, p.dtype, p.T);
     if (!covers(sh, a.nchunks)) return hipErrorInvalidConfiguration;
     const RowPlan pl = gated_bwd_plan(p.T, p.nseg, p.D, p.dtype);
     a.rows_per_cluster = pl.rows_per_cluster;

@@ -843,7 +843,7 @@ hipError_t launch_stream_probe(const void* const* in, int reads, void* const* ou
 // Gated residual + LayerNorm-Modulate (per-sample / per-segment gate, shift, scale).
 RowPlan gated_bwd_plan(int64_t T, int64_t nseg, int64_t D, int dtype);
 Shape gated_fwd_table_shape(int nchunks, int dtype, int64_t T);  // the tables' entries, no override
-Shape gated_bwd_table_shape(int nchunks, int dtype);
+Shape gated_bwd_table_shape(int nchunks, int dtype, int64_t T);
 hipError_t launch_gated_fwd(const Problem& p, const void* x, const void* u, const void* gate,
                             const void* shift, const void* scale, void* h, void* y, float* mean,
                             float* rstd, hipStream_t st);

@@ -119,7 +119,7 @@ int lnmod_table_shape(int family, int64_t D, int dtype, int64_t tokens, int* out
         case LNMOD_FAMILY_TOKEN_BACKWARD_RECOMPUTE: sh = lnmod::tok_rc_bwd_shape(nchunks, dtype); break;
         case LNMOD_FAMILY_TOKEN_BACKWARD_NO_DSHIFT: sh = lnmod::tok_bwd_shape(nchunks, dtype, false, T); break;
         case LNMOD_FAMILY_GATED_FORWARD: sh = lnmod::gated_fwd_table_shape(nchunks, dtype, T); break;
-        case LNMOD_FAMILY_GATED_BACKWARD: sh = lnmod::gated_bwd_table_shape(nchunks, dtype); break;
+        case LNMOD_FAMILY_GATED_BACKWARD: sh = lnmod::gated_bwd_table_shape(nchunks, dtype, T); break;
         case LNMOD_FAMILY_QKNORM_FORWARD: sh = lnmod::qknorm_table_shape(nchunks, dtype, false, T); break;
         default: sh = lnmod::qknorm_table_shape(nchunks, dtype, true, T); break;
     }
