@@ -418,7 +418,8 @@ constexpr SizeRule kBwdRules[] = {
     {131, 159, 0, 1, {3, 1, 2, 2}, 0, 1},        // D = 1048 ... 1272: 0.944, 1.01 (116)
     {131, 159, 1, 20, {3, 1, 2, 2}},             // the same: 0.869, 1.06 (292)
     {609, 640, 6, 20, {8, 2, 1, 1}},             // D = 4872 ... 5120: 0.978, 1.06 (229); below 1.01, up to 1.21
-    {97, 127, 24, 72, {1, 2, 2, 4}},             // D = 776 ... 1016: 0.938, 1.04 (302)
+    {97, 127, 20, 24, {1, 2, 2, 4}, 9},          // D = 776 ... 1016: 0.949, 1.03 (70); on fewer segments up to 1.07
+    {97, 127, 24, 72, {1, 2, 2, 4}},             // the same: 0.938, 1.04 (302)
     {257, 287, 40, 72, {5, 1, 2, 2}},            // D = 2056 ... 2296: 0.935, 1.08 (233); below 0.99, up to 1.09
     {97, 127, 72, 150, {1, 2, 2, 6}},            // D = 776 ... 1016: 0.875, 1.03 (327)
     // D = 3584: 0.932, 1.02 (325); on segments of fewer than 512 rows in the mean up to 1.09
@@ -451,7 +452,7 @@ constexpr SizeRule kRcBwdRules[] = {
     {384, 384, 12, 16, {6, 1, 2, 1}, 0, 4},      // the same: 0.957, 1.02 (36); elsewhere 1.00, up to 1.22
     {417, 448, 2, 14, {8, 1, 2, 1}},             // D = 3336 ... 3584: 0.807, 0.99 (249); below 1.01, up to 1.24
     {417, 448, 14, 20, {8, 1, 2, 1}, 0, 8},      // the same: 0.923, 1.03 (177); on more segments up to 1.12
-    {513, 704, 2, 20, {4, 3, 1, 1}, 0, 4},       // D = 4104 ... 5632: 0.899, 1.05 (236); on more segments 0.98, up to 1.10
+    {513, 704, 2, 20, {4, 3, 1, 1}, 0, 8},       // D = 4104 ... 5632: 0.904, 1.05 (316); on more segments 1.03, up to 1.10
     {705, 767, 8, 20, {4, 3, 1, 1}},             // D = 5640 ... 6136: 0.95, 1.01 (170); below up to 1.21
     {65, 96, 36, 50, {1, 2, 2, 8}, 2},           // D = 520 ... 768: 0.935, 1.04 (161); one sample 1.01, up to 1.08
     {65, 96, 50, 72, {1, 2, 2, 8}},              // the same: 0.93, 1.02 (245)
