@@ -28,7 +28,7 @@ Shape gated_bwd_shape(int nchunks, int dtype, int64_t T) {
             {6, 2, 1, 1}, {6, 2, 1, 1}, {6, 2, 1, 1}, {12, 1, 1, 1},   // D <= 6144
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1},   // D <= 7168
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {16, 1, 1, 1}};   // D <= 8192
-        // widths below a multiple of 256, timed on 0.3 to 800 MB, shares of the entry's time (mean, worst, problems)
+        // widths below a multiple of 256, timed on 0.3 to 900 MB: shares of the entry's time (see SizeRule)
         const int col = (nchunks + 31) / 32;
         if (col == 4 && nchunks < 128) return {2, 1, 2, 2};     // D = 776 ... 1016: 0.952, 1.05 (327)
         if (col == 8 && nchunks < 256) return {4, 1, 2, 1};     // D = 1800 ... 2040: 0.953, 1.09 (327)

@@ -42,8 +42,7 @@ Shape gated_fwd_shape(int nchunks, int dtype, bool ln, int64_t T, int64_t nseg) 
             {4, 3, 1, 1}, {4, 3, 1, 2}, {4, 3, 1, 2}, {4, 3, 1, 2},   // D <= 6144
             {8, 2, 1, 2}, {8, 2, 1, 2}, {8, 2, 2, 1}, {8, 2, 1, 1},   // D <= 7168
             {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 1}, {8, 2, 1, 2}};   // D <= 8192
-        // size classes and widths between two multiples of 256 (see SizeRule): 480 random problems of 4 to 300 MB, every
-        // compiled shape, the shares of the entry's time (mean, worst)
+        // sizes and widths between two multiples of 256: shares of the entry's time (see SizeRule)
         static const SizeRule rules[] = {
             {65, 95, 4, 20, {1, 2, 2, 12}},          // D = 520 ... 760: 0.918, 1.04 (237); below 1.035, up to 1.30
             {65, 95, 20, 72, {1, 2, 2, 8}},          // the same: 0.953, 1.03 (267)

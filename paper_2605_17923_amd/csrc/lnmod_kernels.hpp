@@ -998,13 +998,15 @@ constexpr int kReduceFloats = 16;    // floats per lane a wave keeps in flight: 
 // blockIdx.x is the block of features, blockIdx.y the sum; the segments are blockIdx.z, blockIdx.z + grid_segs, ...,
 // so that any segment count the interface admits stays inside the launch limits.
 //
-// The kernel reads 1 to 40 MB that the main kernel has just written, in 4 to 5 us of which most is neither bytes nor
-// additions: it is instructions that every launch fetches anew (130 more of them in front of the loads cost 2 us) and a
-// chain of dependent round trips (arguments, segment table, slots, LDS).  So its code is kept short: no division
-// (Divider, and the grid has the sums and the segments as dimensions of their own), 32-bit offsets from a uniform base, a
-// slot beyond the last is read as the last one and not added, one LDS stage for waves and lane groups together.  With
-// 64-bit slot numbers and addresses, two divisions and a branch per load it took 4.5 us on 512 x 1536 fp32 rows, now 3.7;
-// on 32 760 x 1536 6.0, now 5.3; on 6449 x 2048 in ten samples 5.0, now 4.4.
+// The kernel reads what the main kernel has just written, slots x sums x 4 D bytes: 0.26 MB for one head's width (256 slots,
+// 2 sums, D = 128), 10.5 MB at D = 5120 and 256 slots, 40 MB and more for packed batches (12 us on the 24 mixed segments of
+// D = 5120).  Up to some 10 MB it takes 3 to 5 us of which most is neither bytes nor additions: it is instructions that every
+// launch fetches anew (130 more of them in front of the loads cost 2 us) and a chain of dependent round trips (arguments,
+// segment table, slots, LDS).  So its code is kept short: no division (Divider, and the grid has the sums and the segments
+// as dimensions of their own), 32-bit offsets from a uniform base, a slot beyond the last is read as the last one and not
+// added, one LDS stage for waves and lane groups together.  With 64-bit slot numbers and addresses, two divisions and a
+// branch per load it took (kernel trace, medians) 4.5 us on 512 x 1536 fp32 rows in two samples, now 3.5; on 32 760 x 1536
+// 5.8, now 5.0; on 6449 x 2048 in ten samples 5.0, now 4.0; on 12 297 x 3072 in three 5.4, now 4.6.
 //
 // One segment (a single sample, and the weight gradients of the query/key normalisation) has an instantiation without
 // table, clusters and loop.  While it shared the code for many, the query/key backward on rows of more than one head took

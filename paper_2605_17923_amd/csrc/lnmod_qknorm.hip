@@ -36,7 +36,7 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3}, {4, 3, 2, 3},   // D <= 6144
             {8, 2, 2, 2}, {8, 2, 2, 2}, {8, 2, 2, 1}, {8, 2, 2, 1},   // D <= 7168
             {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}, {8, 2, 2, 1}};   // D <= 8192
-        // size classes (see SizeRule): 510 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+        // shares of the entry's time (see SizeRule)
         static const SizeRule rules[] = {
             {129, 159, 4, 20, {1, 3, 2, 16}},        // D = 1032 ... 1272: 0.958, 1.04 (149); below 1.00, up to 1.06
             {320, 320, 4, 20, {3, 2, 2, 8}},         // D = 2560: 0.971, 1.02 (147); below 1.00, up to 1.05
@@ -59,7 +59,7 @@ Shape wide_table_shape(int nchunks, int dtype, bool backward, int64_t N = 0) {
             {6, 4, 2, 2}, {6, 4, 2, 1}, {6, 4, 2, 1}, {6, 4, 2, 1},   // D <= 6144
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1},   // D <= 7168
             {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}, {8, 4, 2, 1}};   // D <= 8192
-        // the table was timed at 150 MB; 130 random problems of 4 to 300 MB, shares of the entry's time (mean, worst)
+        // the table was timed at 150 MB; shares of the entry's time (see SizeRule)
         static const SizeRule rules32[] = {
             {257, 320, 0, 72, {1, 6, 2, 6}},         // D = 1028 ... 1280: 0.954, 1.02 (215)
             {385, 512, 4, 20, {2, 4, 2, 4}},         // D = 1540 ... 2048: 0.906, 1.02 (139)

@@ -341,7 +341,7 @@ __device__ inline float row16_sum(float v) {
     return v;                // every lane of the 16 holds the sum of its group
 }
 
-constexpr int kShortWaves = 4;               // waves per block (independent of each other)
+constexpr int kShortWaves = 4;               // waves per block (independent, but for the backward's sums at the end)
 
 template <typename Tag, int VPL, int R>
 __global__ __launch_bounds__(kShortWaves* kWave)
